@@ -129,13 +129,8 @@ struct Sizes {
   int n_dir;
   int n_copies;  // private tally copies
   bool fp32;
-  // DG sweep: table mode (per-(direction, material) coefficients staged in
-  // LDS, n_mat distinct sigma_e) or cell mode; dg_cw cells per chunk, dg_q
-  // of them per lane, dg_chunks chunks per sweep.
-  int n_mat;
-  bool dg_table;
-  int dg_cw, dg_q;
-  long long dg_chunks;
+  int n_mat;  // distinct sigma_e
+  DgPlan dg;  // the collided solve's sweep
   bool diffusion;  // diffusion closing stage: no direction planes, CG vectors instead
   bool dsa;        // S_N with the diffusion correction: planes, CG vectors and dnode
   // tracking materials: with at most kMaxMatIds distinct (sigma_s, sigma_a)
@@ -205,37 +200,6 @@ static size_t lds_limit() {
     cached[dev] = (size_t)v;
   }
   return cached[dev];
-}
-
-// Chooses the sweep.  n_mat < 0: the fields are not known (footprint bound).
-// Chunks of 1024 or 512 cells (four or two per lane: fewer barriers per
-// sweep) where the diagonals are that long, else of up to 256 cells, one per
-// lane; the table mode wherever its coefficients fit in LDS beside the chunk
-// slots and the face traces, else the cell mode.
-static void plan_dg(Sizes& z, const slh_problem* p, long long n_mat) {
-  const int diag = std::min(p->nx, p->ny);  // longest diagonal
-  std::vector<std::pair<int, int>> cand;    // (cells per lane, cells per chunk)
-  for (int q = 4; q > 1; q /= 2)
-    if (diag >= 256 * q) cand.emplace_back(q, 256 * q);
-  for (int cw = std::min(256, (diag + 63) / 64 * 64); cw >= 64; cw -= 64) cand.emplace_back(1, cw);
-  const size_t lim = lds_limit();
-  z.n_mat = n_mat < 0 ? (int)std::max<long long>(0, (long long)(lim / 256)) : (int)n_mat;
-  z.dg_q = 1;
-  z.dg_cw = 64;  // nothing fits: set-up reports the mesh as too large
-  z.dg_table = false;
-  bool chosen = false;
-  for (int table = n_mat > 0 ? 1 : 0; table >= 0 && !chosen; --table)
-    for (const auto& c : cand)
-      if ((table || c.first <= 2) &&  // four cell-mode solves per lane spill registers
-          dg_sweep_lds_bytes(table != 0, c.second, table ? z.n_mat : 0, p->nx, p->ny) <= lim) {
-        z.dg_q = c.first;
-        z.dg_cw = c.second;
-        z.dg_table = table != 0;
-        chosen = true;
-        break;
-      }
-  if (n_mat < 0) z.dg_table = true;  // bound: table storage counted
-  z.dg_chunks = dg_chunks(p->nx, p->ny, z.dg_cw);
 }
 
 static bool finite_nonneg(const double* p, long long n) {
@@ -364,7 +328,14 @@ static Sizes sizes_of(const slh_problem* p) {
   z.diffusion = p->closure == SLH_CLOSE_DIFFUSION;
   z.dsa = !z.diffusion && p->si_accel == SLH_ACCEL_DSA;
   const bool fields = p->sigma_s && p->sigma_a;
-  plan_dg(z, p, fields ? (long long)material_values(p).size() : -1);
+  double sig_max = 0.0;
+  z.n_mat = 0;
+  if (fields) {
+    const std::vector<double> mats = material_values(p);
+    z.n_mat = (int)mats.size();
+    sig_max = mats.back();
+  }
+  z.dg = dg_plan(p->nx, p->ny, z.n_dir, z.n_mat, sig_max, p->boundary != 0, lds_limit());
   if (fields) {
     const long long m = (long long)material_pairs(p).size();
     z.n_mc_mat = m <= kMaxMatIds ? (int)m : 0;
@@ -375,7 +346,7 @@ static Sizes sizes_of(const slh_problem* p) {
   const size_t srec = z.fp32 ? sizeof(SrcRec<float>) : sizeof(SrcRec<double>);
   size_t b = 0;
   const size_t nc = (size_t)z.n_cells;
-  b += nc * (16 + 8 + 8 + 16 + 8);           // mat64, mat32, sig_s, sig_e (two layouts), q
+  b += nc * (16 + 8 + 8 + 8);                // mat64, mat32, sig_s, q
   if (z.n_mc_mat) b += nc * 2 + (size_t)z.n_mc_mat * 24;  // material ids and tables
   if (p->n_s_cell) b += nc * 4;              // per-cell scatter limits
   if (p->boundary)                           // mirror indices, reflected traces
@@ -384,15 +355,18 @@ static Sizes sizes_of(const slh_problem* p) {
   b += (size_t)kMajGroups * kMajBins * 8;    // majorant histograms
   b += (size_t)z.n_faces * 8;                // inflow of the boundary faces
   b += nc * 8 * kTallyStride * 3 * (size_t)z.n_copies;  // tallies
-  b += nc * 8 * 3 + nc * 32 * 3;             // phi_pre/post/R, phi_c, DG source x2
-  b += (size_t)z.n_dir * 4;                  // directions of each sweep layout
-  if (!z.diffusion) b += nc * 64;            // per-layout direction sums
+  b += nc * 8 * 3 + nc * 32;                 // phi_pre/post/R, phi_c
   if (z.diffusion || z.dsa)
     b += nc * 8 * 9 + 4 * 1024 * 8;          // CG: diag, cE, cN, x, r, z, p x2, q; partials
   if (z.dsa) b += nc * 32;                   // nodal change of a sweep
-  if (!z.diffusion) b += (size_t)z.n_dir * nc * 32;  // direction planes
-  b += (size_t)z.n_dir * 256;                // element data
-  if (z.dg_table) b += nc * 8 + (size_t)z.n_mat * 8 + (size_t)z.n_dir * z.n_mat * 256;
+  if (!z.diffusion) {
+    b += nc * 128;                           // DG source of four quadrants
+    b += nc * (!fields || z.dg.table ? 16 : 8);  // table offsets or sigma_e
+    b += (size_t)4 * z.dg.n_grp * nc * 32;   // planes of the groups of directions
+    b += dg_hand_words(z.dg) * 8;            // traces between workgroups
+    if (z.dg.table) b += (size_t)z.n_mat * 8;
+    if (!fields) b += lds_limit() / 4;       // bound: as many materials as a table holds
+  }
   b += (size_t)z.n_dir * 24 + 1024 * 16 + 4096;
   b += (size_t)z.cap * bank * 2;             // census banks
   b += (size_t)(z.n_src_cap > 0 ? z.n_src_cap : 1) * srec;  // source bank
@@ -466,6 +440,7 @@ __global__ void k_snapshot(DevState* st, BalStore* out, int kind, int si_active)
 __global__ void k_state_init(DevState* st) {
   if (threadIdx.x == 0) {
     memset(st, 0, sizeof(DevState));
+    st->sweep_tag = 1u;  // the traces' words start as zeros
     st->thin_factor = 1.0;
   }
 }
@@ -546,13 +521,10 @@ struct slh_solver {
   int *refl_x = nullptr, *refl_y = nullptr;
   double* bnd = nullptr;
   std::vector<int> h_refl;
-  double* dirmat = nullptr;  // DG element data per direction
-  int* mat_id = nullptr;     // DG table mode: material of each cell (sweep layouts),
-  double *sig_e_mat = nullptr, *coef = nullptr;  // its sigma_e, coefficients
-  double* dg_src = nullptr;  // nodal source of a sweep (sweep layouts)
-  int* fam_dirs = nullptr;   // directions of layout A, then of layout B
-  int fam_n = 0;             // how many of them belong to layout A
-  double* phi_fam = nullptr; // per-layout direction sums of the reduction
+  int* mat_off = nullptr;         // DG table: offset of each cell's material in it
+  double* sig_e_mat = nullptr;    // and sigma_e of the materials
+  unsigned long long* hand = nullptr;  // traces between a sweep's workgroups
+  double* dg_src = nullptr;       // source of a sweep ([quadrant][mode][slot])
   int n_part = 1;
   void* bank_mem[2] = {nullptr, nullptr};
   void* stage_mem = nullptr;
@@ -665,7 +637,7 @@ static slh_status setup(slh_solver* s) {
                                            "to 256 bytes: " #ptr)                       \
                  : fail(SLH_E_OUT_OF_MEMORY, "device allocation failed: " #ptr);        \
   } while (0)
-  if (dg_sweep_lds_bytes(false, z.dg_cw, 0, p.nx, p.ny) > lds_limit())
+  if (dg_sweep_lds_bytes(z.dg, 0, p.boundary != 0) > lds_limit())
     return fail(SLH_E_INVALID_ARG, "nx + ny too large for the sweep's LDS traces");
   ALLOC(s->mat64, double2, nc);
   ALLOC(s->mat32, float2, nc);
@@ -675,7 +647,6 @@ static slh_status setup(slh_solver* s) {
     ALLOC(s->mtab32, float2, z.n_mc_mat);
   }
   ALLOC(s->sig_s, double, nc);
-  ALLOC(s->sig_e, double, 2 * nc);  // sweep layouts A and B
   ALLOC(s->q, double, nc);
   if (!s->h_ns.empty()) ALLOC(s->ns_cell, int, nc);
   s->tree_L = tree_leaves(nc + z.n_faces);
@@ -693,7 +664,17 @@ static slh_status setup(slh_solver* s) {
   ALLOC(s->phi_R, double, nc);
   ALLOC(s->phi_c, double, 4 * nc);
   if (z.dsa) ALLOC(s->dnode, double, 4 * nc);
-  if (!z.diffusion) ALLOC(s->psi, double, (size_t)z.n_dir * 4 * nc);
+  if (!z.diffusion) {
+    ALLOC(s->dg_src, double, 16 * nc);
+    ALLOC(s->psi, double, (size_t)4 * z.dg.n_grp * 4 * nc);
+    if (z.dg.n_blk > 1) ALLOC(s->hand, unsigned long long, dg_hand_words(z.dg));
+    if (z.dg.table) {
+      ALLOC(s->mat_off, int, 4 * nc);
+      ALLOC(s->sig_e_mat, double, z.n_mat);
+    } else {
+      ALLOC(s->sig_e, double, nc);
+    }
+  }
   if (z.diffusion || z.dsa) {
     ALLOC(s->cg_diag, double, nc);
     ALLOC(s->cg_e, double, nc);
@@ -706,16 +687,7 @@ static slh_status setup(slh_solver* s) {
     s->cg_npart = cg_partials(nc);
     ALLOC(s->cg_part, double, 4 * s->cg_npart);
   }
-  ALLOC(s->dirmat, double, (size_t)z.n_dir * 32);
-  if (z.dg_table) {
-    ALLOC(s->mat_id, int, 2 * nc);
-    ALLOC(s->sig_e_mat, double, z.n_mat);
-    ALLOC(s->coef, double, (size_t)z.n_dir * z.n_mat * 32);
-  }
-  ALLOC(s->dg_src, double, 8 * nc);
-  ALLOC(s->fam_dirs, int, z.n_dir);
-  if (!z.diffusion) ALLOC(s->phi_fam, double, 8 * nc);
-  s->n_part = dg_reduce_partials(4 * nc);
+  s->n_part = dg_reduce_partials(p.nx, p.ny);
   ALLOC(s->dg_part, double, 2 * s->n_part + 2);
   ALLOC(s->cmax, double, kCensusBlocks);
   if (p.boundary) {
@@ -790,23 +762,6 @@ static slh_status setup(slh_solver* s) {
                            hipMemcpyHostToDevice, st));
   }
   HIP_TRY(hipMemcpyAsync(s->sig_s, s->h_sig_s.data(), 8 * nc, hipMemcpyHostToDevice, st));
-  // sweep layouts: sigma_e in layouts A and B, and the directions of each
-  // layout (A: both components of one sign)
-  std::vector<double> se_l(2 * nc);
-  for (long long c = 0; c < nc; ++c) {
-    const int ci = (int)(c % p.nx), cj = (int)(c / p.nx);
-    se_l[lay_pos(p.nx, p.ny, ci, cj, true)] = se[c];
-    se_l[nc + lay_pos(p.nx, p.ny, ci, cj, false)] = se[c];
-  }
-  std::vector<int> fam;
-  for (int f = 0; f < 2; ++f)
-    for (int m = 0; m < z.n_dir; ++m)
-      if (((dirs[3 * m] > 0.0) == (dirs[3 * m + 1] > 0.0)) == (f == 0)) fam.push_back(m);
-  s->fam_n = 0;
-  for (int m = 0; m < z.n_dir; ++m)
-    if ((dirs[3 * m] > 0.0) == (dirs[3 * m + 1] > 0.0)) s->fam_n += 1;
-  HIP_TRY(hipMemcpyAsync(s->sig_e, se_l.data(), 16 * nc, hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(s->fam_dirs, fam.data(), 4 * fam.size(), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(s->q, s->h_q.data(), 8 * nc, hipMemcpyHostToDevice, st));
   if (s->ns_cell)
     HIP_TRY(hipMemcpyAsync(s->ns_cell, s->h_ns.data(), 4 * nc, hipMemcpyHostToDevice, st));
@@ -831,23 +786,23 @@ static slh_status setup(slh_solver* s) {
   }
   std::vector<int> mid;
   std::vector<double> mval;
-  if (z.dg_table) {
+  if (s->mat_off) {
     mval.assign(se.begin(), se.end());
     std::sort(mval.begin(), mval.end());
     mval.erase(std::unique(mval.begin(), mval.end()), mval.end());
     if ((long long)mval.size() != z.n_mat) return fail(SLH_E_STATE, "material count changed");
-    mid.resize(2 * nc);
+    mid.resize(4 * nc);
     for (long long c = 0; c < nc; ++c) {
       const int k = (int)(std::lower_bound(mval.begin(), mval.end(), se[c]) - mval.begin());
       const int ci = (int)(c % p.nx), cj = (int)(c / p.nx);
-      mid[lay_pos(p.nx, p.ny, ci, cj, true)] = k;
-      mid[nc + lay_pos(p.nx, p.ny, ci, cj, false)] = k;
+      for (int q = 0; q < 4; ++q)
+        mid[q * nc + dg_slot(p.nx, p.ny, z.dg.swap, z.dg.nu, z.dg.nv, q, ci, cj)] = 32 * k;
     }
-    HIP_TRY(hipMemcpyAsync(s->mat_id, mid.data(), 8 * nc, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(s->mat_off, mid.data(), 16 * nc, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(s->sig_e_mat, mval.data(), 8 * z.n_mat, hipMemcpyHostToDevice, st));
+  } else if (s->sig_e) {
+    HIP_TRY(hipMemcpyAsync(s->sig_e, se.data(), 8 * nc, hipMemcpyHostToDevice, st));
   }
-  HIP_TRY(launch_dg_tables(z.n_dir, z.dg_table ? z.n_mat : 0, s->dirs, s->sig_e_mat, s->hx,
-                           s->hy, s->dirmat, s->coef, st));
   // the diffusion correction takes the vacuum condition on every side (the
   // sweep's reflected inflow lags one iteration; a zero-current side there
   // makes the corrected iteration diverge)
@@ -863,6 +818,7 @@ static slh_status setup(slh_solver* s) {
   HIP_TRY(launch_fill_f64(s->ctreeR, 2 * s->tree_L, 0.0, st));
   hipLaunchKernelGGL(k_state_init, dim3(1), dim3(1), 0, st, s->st);
   HIP_TRY(launch_fill_f64(s->phi_c, 4 * nc, 0.0, st));
+  if (s->hand) HIP_TRY(launch_fill_u64(s->hand, (long long)dg_hand_words(z.dg), 0ull, st));
   HIP_TRY(launch_fill_f64(s->phi_pre, nc, 0.0, st));
   HIP_TRY(launch_fill_f64(s->phi_post, nc, 0.0, st));
   HIP_TRY(launch_fill_f64(s->phi_R, nc, 0.0, st));
@@ -970,14 +926,14 @@ static DgArgs dg_args(slh_solver* s) {
   const slh_problem& p = s->prob;
   const Sizes& z = s->z;
   DgArgs d;
+  static_cast<DgPlan&>(d) = s->z.dg;
   d.nx = p.nx;
   d.ny = p.ny;
   d.hx = s->hx;
   d.hy = s->hy;
   d.n_dir = z.n_dir;
   d.dir = s->dirs;
-  d.fam_dirs = s->fam_dirs;
-  d.fam_n = s->fam_n;
+  d.n_quad = z.n_dir / 4;
   d.sig_e = s->sig_e;
   d.sig_s = s->sig_s;
   d.phi_post = s->phi_post;
@@ -985,15 +941,11 @@ static DgArgs dg_args(slh_solver* s) {
   d.phi_c = s->phi_c;
   d.src = s->dg_src;
   d.psi = s->psi;
-  d.phi_fam = s->phi_fam;
   d.dnode = s->z.dsa && !s->skip_remap ? s->dnode : nullptr;
-  d.mat_id = s->mat_id;
+  d.mat_off = s->mat_off;
+  d.hand = s->hand;
   d.n_mat = z.n_mat;
-  d.cw = z.dg_cw;
-  d.coef = s->coef;
-  d.dirmat = s->dirmat;
-  d.n_chunks = (int)z.dg_chunks;
-  d.cells_per_lane = z.dg_q;
+  d.sig_e_mat = s->sig_e_mat;
   d.bc = s->prob.boundary;
   d.refl_x = s->refl_x;
   d.refl_y = s->refl_y;
@@ -1044,7 +996,7 @@ static slh_status enqueue_si(slh_solver* s, hipStream_t st, int n_it) {
     const DgArgs d = dg_args(s);
     const CgArgs c = cg_args(s);
     for (int it = 0; it < n_it; ++it) {
-      HIP_TRY(launch_dg_sweep(d, z.dg_table, st));
+      HIP_TRY(launch_dg_sweep(d, st));
       HIP_TRY(launch_dg_reduce(d, s->dg_part, s->n_part, s->si_tol, s->si_max, st));
       HIP_TRY(launch_dsa_start(c, s->sig_s, s->dnode, kDsaMaxIter, st));
       if (cg_one_block(z.n_cells)) {
@@ -1059,7 +1011,7 @@ static slh_status enqueue_si(slh_solver* s, hipStream_t st, int n_it) {
   } else {
     const DgArgs d = dg_args(s);
     for (int it = 0; it < n_it; ++it) {
-      HIP_TRY(launch_dg_sweep(d, z.dg_table, st));
+      HIP_TRY(launch_dg_sweep(d, st));
       HIP_TRY(launch_dg_reduce(d, s->dg_part, s->n_part, s->si_tol, s->si_max, st));
     }
   }

@@ -3,41 +3,51 @@
 // and a step-averaged time closure sigma_e = sigma_t + tau/(c dt).  One
 // transport sweep per direction and source-iteration sweep.
 //
-// Element matrices on a cell of size hx x hy, node k = kx + 2 ky at
-// (x_kx, y_ky), 1-D factors  M = h/6 [[2,1],[1,2]] (mass) and
-// K = 1/2 [[-1,1],[-1,1]] (K[i][j] = int L_i L_j'):
-//   A = a Kx(x)My + b Mx(x)Ky + sig_e Mx(x)My
-//     + |a| (e_f e_f^T)(x)My + |b| Mx(x)(e_g e_g^T)
-// where f (g) is the local index of the x (y) inflow face; the right side is
-// (Mx(x)My) S + F up with F up = |a| e_f (x) My up_x + |b| Mx up_y (x) e_g for
-// the upwind traces up = (up_x0, up_x1, up_y0, up_y1) (zero on the domain
-// boundary).  On the uniform mesh A0 = A - sig_e Mx(x)My and F depend on the
-// direction only.
+// The element equation.  On a cell of size hx x hy with nodal values
+// X[kx][ky], in coordinates mirrored so that both direction components are
+// positive (a = |Omega_x| / hx, b = |Omega_y| / hy), the element matrix divided
+// by the mass matrix is a sum of one-dimensional operators:
+//   a T X + b X T^t + sig_e X = S + a nu ux^t + b uy nu^t,
+//   T = [[3, 1], [-3, 1]],  nu = (4, -2),
+// ux[ky], uy[kx] the upwind traces on the x and y inflow faces (zero on a
+// vacuum side).  T has the eigenvalues lambda = 2 +- i sqrt 2 whatever the
+// direction, so its left eigenvector l (scaled to l.nu = 1) and right
+// eigenvector v (l.v = 1) turn the element's 4x4 system into two complex
+// scalar equations.  With the coefficients X1 = l_kx l_ky X (mode lambda,
+// lambda), X2 = l_kx conj(l_ky) X (mode lambda, conj lambda), S1 and S2 of the
+// source, and l.ux, l.uy of the traces:
+//   X1 = c1 (S1 + a ux + b uy),        c1 = 1 / ((a + b) lambda + sig_e),
+//   X2 = c2 (S2 + a conj(ux) + b uy),  c2 = 1 / (a lambda + b conj(lambda) + sig_e),
+// and the coefficients of the outflow traces, which the next cells take, are
+//   ux' = v1 X1 + conj(v1 X2),  uy' = v1 X1 + conj(v1) X2.
+// Sources and angular fluxes are kept as these coefficients in each quadrant
+// of directions; the reduction returns to nodal values.  A cell and direction
+// then takes about 30 FP64 operations and two complex numbers c1, c2 that
+// depend on the material alone, where the 4x4 block factorisation took about
+// 150 and a table of its inverses 32 numbers per material.
 //
-// Device layout: one workgroup per direction walks the cells in diagonal
-// wavefronts of the direction's upwind order, in chunks of CW cells (a
-// diagonal, or a piece of a long one).  Cells of one diagonal have distinct
-// rows and columns, so the outflow traces they hand to the next diagonal live
-// in two small LDS arrays (one trace per row for the x faces, one per column
-// for the y faces).  The workgroup has CW/64 sweeping waves and CW/(64 Q)
-// loader waves (Q cells per loader lane).  The loaders keep several chunks of
-// nodal sources and material keys in flight in registers and hand each chunk
-// over through a two-slot LDS buffer, so the sweeping waves never wait on
-// global memory: their only global accesses are the stores of psi_m (a
-// wave that mixed loads and stores would have to drain all of them before
-// using a loaded value).  After each barrier a sweeping lane turns the upwind
-// traces into its cell's solution with the element data prepared before the
-// barrier:
-//   table mode: psi = B S + G up with B = A^-1 Mx(x)My, G = A^-1 F taken from
-//     a per-(direction, material) table staged in LDS (few distinct sigma_e);
-//     the loader hands over B S instead of S;
-//   cell mode: A is LU-factorised before the barrier and solved after it.
-// The solution goes to a per-direction plane, and a second kernel sums
-// w_m psi_m over the directions in a fixed order, so the scalar flux does not
-// depend on scheduling.  The sources, sigma_e and the planes are stored in the
-// sweep's own layouts (anti-diagonals or diagonals, DgArgs), where the cells
-// of a chunk are contiguous: a diagonal of a row-major array would touch a
-// different cache line in every lane.
+// The sweep.  A wave owns a strip of 64 rows along one axis of the mesh (the
+// v axis) and walks it along the other (the u axis), lane l one column behind
+// lane l - 1: at step t lane l holds cell (u = t - l, v = 64 strip + l).  The
+// trace across a u face stays in the lane's registers, the trace across a v
+// face moves to the next lane by a lane shift, so a step needs no barrier and
+// no LDS exchange.  The strips of a direction are the waves of one workgroup
+// (a wave takes several when there are more than 16): the last lane of a strip
+// leaves its trace of every column in an LDS row, from which the first lane of
+// the next strip takes it, a few columns at a time, once the strip's progress
+// word says that they are there.  What bounds the sweep is the chain of nu +
+// nv dependent steps on small meshes (0.16 us each, the issue of a step's
+// instructions, where a workgroup barrier per diagonal took 0.45 us; 256^2,
+// S_8: 264 -> 88 us a sweep, 140^2, S_12: 130 -> 51) and the traffic of the planes
+// on large ones; there each wave sweeps four directions, which share the
+// sources and leave one plane: the sum of w_m psi_m over them.
+//
+// Every quadrant has its own copy of the source (and of the material ids) in
+// its own order of visits (dg_slot): the cells that a wave holds at one step
+// are neighbours in memory.  Cells outside the mesh take no storage: the
+// columns of a strip wrap around (slot row (u + l) mod nu).
+#include <algorithm>
+
 #include "slh_common.hpp"
 
 namespace slh {
@@ -51,17 +61,54 @@ __device__ __forceinline__ double recip(double a) {
   return r;
 }
 
+// lambda = 2 + i sqrt 2; l = (l0, l1), v = (v0, v1) as above
+constexpr double kSqrt2 = 1.4142135623730951;
+constexpr double kL0r = 5.0 / 18.0, kL0i = -kSqrt2 / 18.0;
+constexpr double kL1r = 1.0 / 18.0, kL1i = -2.0 * kSqrt2 / 18.0;
+constexpr double kV0r = 2.0, kV0i = -0.5 * kSqrt2;
+constexpr double kV1r = -1.0, kV1i = 2.5 * kSqrt2;
+
+// Coefficients of the mirrored nodal values s<ku><kv> of a cell.
+__device__ __forceinline__ void to_modes(double s00, double s01, double s10, double s11,
+                                         double2& m1, double2& m2) {
+  // the v transform at ku = 0, 1, then the u transform
+  const double q0r = kL0r * s00 + kL1r * s01, q0i = kL0i * s00 + kL1i * s01;
+  const double q1r = kL0r * s10 + kL1r * s11, q1i = kL0i * s10 + kL1i * s11;
+  const double rr = kL0r * q0r + kL1r * q1r, ii = kL0i * q0i + kL1i * q1i;
+  const double ri = kL0r * q0i + kL1r * q1i, ir = kL0i * q0r + kL1i * q1r;
+  m1 = make_double2(rr - ii, ir + ri);
+  m2 = make_double2(rr + ii, ir - ri);
+}
+
+// Mirrored nodal values s[2 ku + kv] of coefficients.
+__device__ __forceinline__ void from_modes(double2 m1, double2 m2, double s[4]) {
+  constexpr double vr[2] = {kV0r, kV1r}, vi[2] = {kV0i, kV1i};
+#pragma unroll
+  for (int kv = 0; kv < 2; ++kv) {
+    // v_kv m1 + conj(v_kv) m2
+    const double pr = vr[kv] * (m1.x + m2.x) - vi[kv] * (m1.y - m2.y);
+    const double pi = vr[kv] * (m1.y + m2.y) + vi[kv] * (m1.x - m2.x);
+#pragma unroll
+    for (int ku = 0; ku < 2; ++ku) s[2 * ku + kv] = 2.0 * (vr[ku] * pr - vi[ku] * pi);
+  }
+}
+
+// Index (node kx + 2 ky) of the mirrored node (ku, kv) of quadrant q (bit 0:
+// Omega_x < 0, bit 1: Omega_y < 0).
+__device__ __forceinline__ int quad_node(int q, int swap, int ku, int kv) {
+  return ((swap ? kv : ku) ^ (q & 1)) + 2 * ((swap ? ku : kv) ^ (q >> 1));
+}
+
 // Start of a step's source iteration: phi_c = 0, the iteration state reset
-// (block 0), the nodal source of the first iterate
-// S = sigma_s/(4 pi) (phi_c + phi_post) with phi_c = 0 (later iterates get
-// theirs from the flux reduction), and with reflective sides the buffer of
-// reflected traces that the first sweep reads set to zero.
-__global__ void k_si_start(int nx, int ny, const double* __restrict__ sig_s,
-                           const double* __restrict__ phi_post, double* __restrict__ phi_c,
-                           double* __restrict__ S, double* __restrict__ bnd0, long long n_bnd,
-                           DevState* st, int si_max) {
+// (block 0), the source of the first iterate S = sigma_s/(4 pi) (phi_c +
+// phi_post) with phi_c = 0, one value at the four nodes of a cell, in every
+// quadrant (later iterates get theirs from the flux reduction), and with
+// reflective sides the buffer of reflected traces that the first sweep reads
+// set to zero.
+__global__ void k_si_start(DgArgs g, double* __restrict__ bnd0, long long n_bnd, int si_max) {
+  DevState* st = g.st;
   if (st->halt) return;
-  const long long n = (long long)nx * ny;
+  const int n = g.nx * g.ny;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st->si.iter = 0;
     st->si.conv = si_max == 0 ? 1 : 0;
@@ -79,475 +126,527 @@ __global__ void k_si_start(int nx, int ny, const double* __restrict__ sig_s,
   const long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long str = (long long)gridDim.x * blockDim.x;
   for (long long i = i0; i < n; i += str) {
-    const double ssc = sig_s[i] * inv4pi;
-    const double v = ssc * (0.0 + phi_post[i]);
-    const int ci = (int)(i % nx), cj = (int)(i / nx);
-    reinterpret_cast<double4*>(phi_c)[i] = make_double4(0.0, 0.0, 0.0, 0.0);
-    reinterpret_cast<double4*>(S)[lay_pos(nx, ny, ci, cj, true)] = make_double4(v, v, v, v);
-    reinterpret_cast<double4*>(S)[n + lay_pos(nx, ny, ci, cj, false)] = make_double4(v, v, v, v);
+    const double ssc = g.sig_s[i] * inv4pi;
+    const double v = ssc * (0.0 + g.phi_post[i]);
+    const int ci = (int)i % g.nx, cj = (int)i / g.nx;
+    reinterpret_cast<double4*>(g.phi_c)[i] = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (!g.src) continue;  // no sweep in this solver
+    double2 m1, m2;
+    to_modes(v, v, v, v, m1, m2);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      double2* S = reinterpret_cast<double2*>(g.src) + (long long)q * 2 * n;
+      const int pos = dg_slot(g, q, ci, cj);
+      S[pos] = m1;
+      S[n + pos] = m2;
+    }
   }
   for (long long k = i0; k < n_bnd; k += str) bnd0[k] = 0.0;
 }
 
-// Direction part of the element: A0 and F (row-major 4x4 each) and the mass
-// matrix MM = Mx(x)My.
-__device__ void element(double a, double b, double hx, double hy, double A0[4][4],
-                        double F[4][4], double MM[4][4]) {
-  const int fx = a > 0.0 ? 0 : 1, fy = b > 0.0 ? 0 : 1;
-  const double aa = fabs(a), ab = fabs(b);
-  const double Mx[2][2] = {{hx / 3.0, hx / 6.0}, {hx / 6.0, hx / 3.0}};
-  const double My[2][2] = {{hy / 3.0, hy / 6.0}, {hy / 6.0, hy / 3.0}};
-  const double K[2][2] = {{-0.5, 0.5}, {-0.5, 0.5}};
-  for (int r = 0; r < 4; ++r) {
-    const int kx = r & 1, ky = r >> 1;
-    for (int l = 0; l < 4; ++l) {
-      const int lx = l & 1, ly = l >> 1;
-      double v = a * K[kx][lx] * My[ky][ly] + b * Mx[kx][lx] * K[ky][ly];
-      if (kx == fx && lx == fx) v += aa * My[ky][ly];
-      if (ky == fy && ly == fy) v += ab * Mx[kx][lx];
-      A0[r][l] = v;
-      MM[r][l] = Mx[kx][lx] * My[ky][ly];
-    }
-    F[r][0] = kx == fx ? aa * My[ky][0] : 0.0;
-    F[r][1] = kx == fx ? aa * My[ky][1] : 0.0;
-    F[r][2] = ky == fy ? ab * Mx[kx][0] : 0.0;
-    F[r][3] = ky == fy ? ab * Mx[kx][1] : 0.0;
-  }
+// The LDS row of traces has room for the columns that a strip's first and
+// last lanes touch before and after the mesh.
+constexpr int kDgAhead = 8;  // the most columns a strip takes at a time
+constexpr int kDgSplit = 4;  // directions per wave on large meshes
+constexpr int kDgFront = 63, kDgPad = kDgFront + kDgAhead;
+
+// The value of the lane below, `first` in lane 0.
+__device__ __forceinline__ double lane_shift(double first, double v) {
+  const long long o = __double_as_longlong(first), s = __double_as_longlong(v);
+  constexpr int kWaveShr1 = 0x138;
+  const int lo = __builtin_amdgcn_update_dpp((int)o, (int)s, kWaveShr1, 0xf, 0xf, false);
+  const int hi =
+      __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(s >> 32), kWaveShr1, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Per-direction element data [m][32]: A0 then F.
-__global__ void k_dg_dirmat(int n_dir, const double* __restrict__ dir, double hx, double hy,
-                            double* __restrict__ dm) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= n_dir) return;
-  double A0[4][4], F[4][4], MM[4][4];
-  element(dir[3 * m], dir[3 * m + 1], hx, hy, A0, F, MM);
-  for (int r = 0; r < 4; ++r)
-    for (int l = 0; l < 4; ++l) {
-      dm[32 * m + 4 * r + l] = A0[r][l];
-      dm[32 * m + 16 + 4 * r + l] = F[r][l];
-    }
+// Buffer loads and stores of the sweep: a lane's constant byte offset plus the
+// step's (uniform) one, so that an access takes no address arithmetic; an
+// access past the buffer's length reads zero or is dropped, so that lanes
+// without a cell store without a branch (a conditional store would make the
+// compiler's wait for a load drain the younger loads).
+using u32x4 = unsigned int __attribute__((ext_vector_type(4)));
+constexpr int kBufferFlags = 0x00020000;  // raw 32-bit data, no swizzle
+constexpr int kNoCell = 0x40000000;       // beyond any buffer of the sweep
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kBufferFlags);
+}
+__device__ __forceinline__ double2 buffer_load2(__amdgpu_buffer_rsrc_t r, int lane_off, int off) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0));
+}
+// NT: non-temporal (planes that do not fit the caches, read once)
+template <bool NT>
+__device__ __forceinline__ void buffer_store2(__amdgpu_buffer_rsrc_t r, int lane_off, int off,
+                                              double x, double y) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_double2(x, y)), r,
+                                         lane_off, off, NT ? 2 : 0);
 }
 
-// Table [m][material][32]: B = A^-1 MM then G = A^-1 F (row-major), by
-// Gauss-Jordan elimination of [A | MM | F]; the pivots do not vanish (the
-// symmetric part of the upwind element matrix is positive definite: mass and
-// inflow terms are SPD and the streaming term's symmetric part, the outflow
-// minus inflow face mass, becomes |Omega.n| face mass with the inflow term).
-__global__ void k_dg_coef(int n_dir, int n_mat, const double* __restrict__ dir,
-                          const double* __restrict__ sig_e_mat, double hx, double hy,
-                          double* __restrict__ coef) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long long)n_dir * n_mat) return;
-  const int m = (int)(t / n_mat), k = (int)(t % n_mat);
-  const double se = sig_e_mat[k];
-  double A[4][4], F[4][4], MM[4][4], R[4][8];
-  element(dir[3 * m], dir[3 * m + 1], hx, hy, A, F, MM);
-  for (int r = 0; r < 4; ++r)
-    for (int l = 0; l < 4; ++l) {
-      A[r][l] += se * MM[r][l];
-      R[r][l] = MM[r][l];
-      R[r][4 + l] = F[r][l];
-    }
-  for (int c = 0; c < 4; ++c) {
-    const double inv = 1.0 / A[c][c];
-    for (int l = 0; l < 4; ++l) A[c][l] *= inv;
-    for (int j = 0; j < 8; ++j) R[c][j] *= inv;
-    for (int r = 0; r < 4; ++r) {
-      if (r == c) continue;
-      const double f = A[r][c];
-      for (int l = 0; l < 4; ++l) A[r][l] -= f * A[c][l];
-      for (int j = 0; j < 8; ++j) R[r][j] -= f * R[c][j];
-    }
-  }
-  double* o = coef + t * 32;
-  for (int r = 0; r < 4; ++r)
-    for (int j = 0; j < 4; ++j) {
-      o[4 * r + j] = R[r][j];
-      o[16 + 4 * r + j] = R[r][4 + j];
-    }
+// c1 and c2 of a material: 1/z by Smith's division (the real part, at least
+// 2 (a + b), is never below the imaginary part in size, so nothing
+// overflows that the element matrix itself would not).
+__device__ __forceinline__ void mode_inverse(double a, double b, double se, double2& c1,
+                                             double2& c2) {
+  const double dr = 2.0 * (a + b) + se;
+  const double ir = recip(dr);
+  const double d1 = kSqrt2 * (a + b), d2 = kSqrt2 * (a - b);
+  const double r1 = d1 * ir, r2 = d2 * ir;
+  const double e1 = recip(fma(d1, r1, dr)), e2 = recip(fma(d2, r2, dr));
+  c1 = make_double2(e1, -r1 * e1);
+  c2 = make_double2(e2, -r2 * e2);
 }
 
-hipError_t launch_dg_tables(int n_dir, int n_mat, const double* dir, const double* sig_e_mat,
-                            double hx, double hy, double* dirmat, double* coef, hipStream_t s) {
-  hipLaunchKernelGGL(k_dg_dirmat, dim3((n_dir + 63) / 64), dim3(64), 0, s, n_dir, dir, hx, hy,
-                     dirmat);
-  if (n_mat > 0 && coef) {
-    const long long n = (long long)n_dir * n_mat;
-    hipLaunchKernelGGL(k_dg_coef, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, s, n_dir,
-                       n_mat, dir, sig_e_mat, hx, hy, coef);
-  }
-  return hipGetLastError();
-}
-
-// Chunks of the sweep: sum over diagonals of ceil(length / cw).
-long long dg_chunks(int nx, int ny, int cw) {
-  long long n = 0;
-  for (int d = 0; d < nx + ny - 1; ++d) {
-    const int lo = d - (ny - 1) > 0 ? d - (ny - 1) : 0;
-    const int hi = d < nx - 1 ? d : nx - 1;
-    n += (hi - lo + cw) / cw;
-  }
-  return n;
-}
-
-constexpr int kDgDepth = 4;  // chunks in flight in the loader wave
-constexpr int kDgRow = 34;   // LDS stride of a table row (32 values)
-
-// One chunk in a loader lane: Q cells (source, key, position in the chunk
-// or -1).
-template <int Q>
-struct DgStage {
-  double Sx[Q], Sy[Q], Sz[Q], Sw[Q];
-  double Kd[Q];  // cell mode: sigma_e
-  int Ki[Q];     // table mode: material
-  int C[Q];
-};
-
-// The sweep of one direction, compiled for each quadrant (APOS: Omega_x > 0,
-// BPOS: Omega_y > 0), so that the upwind order costs no selects.  A chunk has
-// CW cells; a sweeping lane takes Q of them (positions t, t + CW/Q, ...),
-// whose independent solves hide each other's latency, and so does a loader
-// lane.
-template <bool TABLE, int Q, bool REFL, bool APOS, bool BPOS>
-__device__ __forceinline__ void sweep_dir(const DgArgs& g) {
+// One workgroup sweeps the PER directions of one group of a quadrant, one
+// wave per strip (see the head of this file).  TABLE: c1, c2 of every material
+// in LDS (n_mat + 1 rows per direction, the last one zero, for lanes that have
+// not reached their first column); else they are computed per cell.  AHEAD:
+// columns whose sources are in flight; a strip takes at most eight at a time
+// from the one before.
+//
+// A step of a wave issues about 50 instructions (28 FP64 per direction); one
+// wave per SIMD issues one every four cycles or so, so on small meshes the
+// instruction count of a step is its time, and everything that can be is kept
+// out of it: addresses are uniform offsets, the lanes without a cell neither
+// branch nor store, the traces carry no factor, and with one direction per
+// wave the reduction applies the weight.
+//
+// With four directions per wave (large meshes, where the planes' traffic
+// counts: a plane then holds the sum of four directions) the strips of a group
+// are spread over several workgroups of four strips, one wave per SIMD.  The
+// trace rows between workgroups go through global memory in tagged words: each
+// 8-byte word holds half a double and the sweep's tag, so that a word that
+// carries the tag is there, whatever the order in which words arrive.  A
+// workgroup takes its task by a ticket of its class (the blocks that share an
+// XCD), first strips first: it waits only for tasks of smaller tickets, which
+// running workgroups hold, so every wait ends however the blocks are
+// dispatched.
+template <int PER, bool TABLE, bool REFL, int AHEAD, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
+  if (g.st->si.done) return;  // the whole workgroup: no barrier is left pending
+  constexpr bool SPLIT = PER == kDgSplit;
+  static_assert(!SPLIT || 2 * PER * AHEAD == 64, "a lane per double of a block of columns");
   extern __shared__ double smem[];
-  const int nx = g.nx, ny = g.ny;
-  const int CW = g.cw;            // cells per chunk, a multiple of 64 Q
-  const int n_sw = CW / (64 * Q); // sweeping waves; as many loader waves follow them
-  const int n_ld = n_sw;
-  const int m = blockIdx.x;
-  constexpr bool apos = APOS, bpos = BPOS;
-  // LDS: slots S [2][CW] as two double2 halves | keys [2][CW] | coef [n_mat][kDgRow] | faces
-  // (the source halves and the table rows are laid out so that a wave's
-  // accesses fall in distinct banks: 16-byte lane stride, rows offset by
-  // four banks)
-  double2* slotA = reinterpret_cast<double2*>(smem);  // S.x, S.y
-  double2* slotB = slotA + (size_t)2 * CW;             // S.z, S.w
-  double* slotK = smem + (size_t)2 * CW * 4;
-  double* coefL = slotK + (size_t)2 * CW;
-  const size_t n_coef = TABLE ? (size_t)g.n_mat * kDgRow : 0;
-  double* xf = coefL + n_coef;  // 16-byte aligned (80 CW + 272 n_mat bytes in), read as double2
-  double* yf = xf + 2 * ny;
-  const int n_diag = nx + ny - 1;
-  // barriers: one per chunk, padded to whole loader rounds (the padding
-  // chunks are empty), so the loader's rounds have no conditional steps
-  const int n_pad = (g.n_chunks + kDgDepth - 1) / kDgDepth * kDgDepth;
-  auto diag_hi = [&](int dd) __attribute__((always_inline)) { return dd < nx - 1 ? dd : nx - 1; };
-  auto diag_lo = [&](int dd) __attribute__((always_inline)) { return dd - (ny - 1) > 0 ? dd - (ny - 1) : 0; };
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const bool loader = wave >= n_sw;
-  const int lane = threadIdx.x & 63;
-  const int lw = wave - n_sw;  // loader wave index
-  // this direction's layout: A (anti-diagonals) when both components have the
-  // same sign; the chunk of upwind diagonal dd is run n_diag - 1 - dd of the
-  // layout when Omega_x < 0, and cell i sits at run start - lo + i
-  constexpr bool anti = APOS == BPOS;
-  const long long lay_base = anti ? 0 : (long long)nx * ny;
-  auto run_base = [&](int dd) __attribute__((always_inline)) {
-    const int r = apos ? dd : n_diag - 1 - dd;
-    return lay_run(nx, ny, r) - (long long)diag_lo(r) + lay_base;
-  };
-
-  // ---- loader state: ring of kDgDepth chunks, Q cells per lane ----
-  DgStage<Q> r0s, r1s, r2s, r3s;
-  int fd = 0, fp = 0;   // fetch front: diagonal, first position
-  // Every lane issues the same loads in every stage (a position without a
-  // cell reads cell 0 and is marked -1): with no branch around the loads the
-  // compiler can wait for one stage while the younger ones stay in flight.
-  auto fetch = [&](DgStage<Q>& st) __attribute__((always_inline)) {
-    const bool live = fd < n_diag;
-    const int hi = live ? diag_hi(fd) : -1;
-    const int dl = live ? fd : n_diag - 1;  // a real diagonal for the addresses
-    const int dlo = diag_lo(dl), dhi = diag_hi(dl);
-    const long long rb = run_base(dl);
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int tq = lane + 64 * (lw + n_ld * q);
-      const int ip = fp + tq;
-      const bool ok = ip <= hi;
-      // clamp the position onto the diagonal, so that every lane's address
-      // is a real cell and no branch guards the loads
-      const int ipc = ip < dlo ? dlo : (ip < dhi ? ip : dhi);
-      const int i = apos ? ipc : nx - 1 - ipc;
-      const long long c = rb + i;  // position in this direction's layout
-      st.C[q] = ok ? tq : -1;
-      if (TABLE) st.Ki[q] = g.mat_id[c];
-      else st.Kd[q] = g.sig_e[c];
-      const double4 v = reinterpret_cast<const double4*>(g.src)[c];
-      st.Sx[q] = v.x;
-      st.Sy[q] = v.y;
-      st.Sz[q] = v.z;
-      st.Sw[q] = v.w;
-    }
-    if (live) {
-      fp += CW;
-      if (fp > hi) {
-        ++fd;
-        fp = fd < n_diag ? diag_lo(fd) : 0;
-      }
-    }
-  };
-  // Table mode hands over B S (B from the staged table) instead of S, which
-  // takes a matrix-vector product off the sweeping lanes' critical path.
-  auto hand_over = [&](const DgStage<Q>& st, int slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-      if (st.C[q] >= 0) {
-        double4 v = make_double4(st.Sx[q], st.Sy[q], st.Sz[q], st.Sw[q]);
-        if (TABLE) {
-          const double* c = coefL + (size_t)st.Ki[q] * kDgRow;
-          v = make_double4(c[0] * st.Sx[q] + c[1] * st.Sy[q] + c[2] * st.Sz[q] + c[3] * st.Sw[q],
-                           c[4] * st.Sx[q] + c[5] * st.Sy[q] + c[6] * st.Sz[q] + c[7] * st.Sw[q],
-                           c[8] * st.Sx[q] + c[9] * st.Sy[q] + c[10] * st.Sz[q] + c[11] * st.Sw[q],
-                           c[12] * st.Sx[q] + c[13] * st.Sy[q] + c[14] * st.Sz[q] + c[15] * st.Sw[q]);
-        }
-        slotA[slot * CW + st.C[q]] = make_double2(v.x, v.y);
-        slotB[slot * CW + st.C[q]] = make_double2(v.z, v.w);
-        slotK[slot * CW + st.C[q]] = TABLE ? (double)st.Ki[q] : st.Kd[q];
-      }
-  };
-  if (loader) {
-    fetch(r0s);
-    fetch(r1s);
-    fetch(r2s);
-    fetch(r3s);
+  const int nu = g.nu, nv = g.nv, n = g.nx * g.ny;
+  // the workgroups of a quadrant on two XCDs, so that they share its sources
+  // in the L2 (1024^2, S_16: all four quadrants' sources through every L2
+  // otherwise)
+  const bool pairs = (g.n_grp & 1) == 0;
+  const int n_all = 4 * g.n_grp;
+  int task = (int)blockIdx.x, blk = 0;
+  if (SPLIT) {
+    int* const s_ticket = reinterpret_cast<int*>(smem);
+    const int cls = (int)blockIdx.x & 7;
+    if (threadIdx.x == 0)
+      *s_ticket = (int)__hip_atomic_fetch_add(&g.st->ticket[cls], 1u, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int ticket = __builtin_amdgcn_readfirstlane(*s_ticket);
+    __syncthreads();  // the word belongs to the trace row
+    const int n_cls = (n_all - cls + 7) / 8;  // the class's groups: cls, cls + 8, ...
+    blk = n_cls > 0 ? ticket / n_cls : g.n_blk;
+    if (blk >= g.n_blk) return;
+    task = cls + 8 * (ticket - blk * n_cls);
   }
-  // upwind faces: zero (vacuum) or, on a reflective side, the previous
-  // iteration's outflow of the mirrored direction
-  // (REFL: some side reflects and g.bnd holds the traces)
-  const size_t sb = (size_t)2 * (nx + ny);  // boundary traces per direction
-  const int it = REFL ? g.st->si.iter : 0;
-  const bool rx_in = REFL && (g.bc & (apos ? 1 : 2)) != 0;
-  const bool ry_in = REFL && (g.bc & (bpos ? 4 : 8)) != 0;
-  const bool rx_out = REFL && (g.bc & (apos ? 2 : 1)) != 0;
-  const bool ry_out = REFL && (g.bc & (bpos ? 8 : 4)) != 0;
-  const double* b_in = REFL ? g.bnd + (size_t)((it + 1) & 1) * g.n_dir * sb : nullptr;
-  double* b_out = REFL ? g.bnd + ((size_t)(it & 1) * g.n_dir + m) * sb : nullptr;
-  if (rx_in || ry_in) {
-    for (int k = threadIdx.x; k < 2 * (nx + ny); k += blockDim.x) {
-      double v = 0.0;
-      if (k < 2 * ny) {
-        if (rx_in) v = b_in[(size_t)g.refl_x[m] * sb + k];
-      } else if (ry_in) {
-        v = b_in[(size_t)g.refl_y[m] * sb + k];
-      }
-      xf[k] = v;  // yf = xf + 2 ny
-    }
-  } else {
-    for (int k = threadIdx.x; k < 2 * (nx + ny); k += blockDim.x) xf[k] = 0.0;
+  const int q = pairs ? (task & 7) >> 1 : task / g.n_grp;
+  const int grp = pairs ? (task >> 3) * 2 + (task & 1) : task - q * g.n_grp;
+  const int m0 = q * g.n_quad + grp * PER;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const int n_waves = blockDim.x >> 6;
+  // LDS: table [n_mat + 1][PER] of c1, c2 (SPLIT: 1/|z1|^2, 1/|z2|^2 for c =
+  // conj(z)/|z|^2, half the space, and [n_mat + 1] sigma_e) | row of v-face traces [nu
+  // + kDgPad][PER] and room for idle lanes' traces | reflective sides: traces of the u side [PER][rows] | progress
+  // word of each strip
+  const int n_row = TABLE ? g.n_mat + 1 : 0;
+  const int n_col = nu + kDgPad;
+  const int n_xf = SPLIT ? 64 * n_waves : nv;  // rows of the workgroup
+  double2* const yf = reinterpret_cast<double2*>(smem);
+  double2* const idle = yf + PER * n_col;
+  double2* const xf = idle + PER * 64;
+  double2* const tab = xf + (REFL ? PER * n_xf : 0);
+  double* const tab_se = reinterpret_cast<double*>(tab + (SPLIT ? PER : 2 * PER) * n_row);
+  int* const prog = reinterpret_cast<int*>(tab_se + (SPLIT ? n_row : 0));
+
+  double a[PER], b[PER], w[PER];
+  int md[PER];
+#pragma unroll
+  for (int d = 0; d < PER; ++d) {
+    // a group past the end of its quadrant repeats the last direction with weight 0
+    const int m = m0 + d < (q + 1) * g.n_quad ? m0 + d : (q + 1) * g.n_quad - 1;
+    md[d] = m;
+    const double x = fabs(g.dir[3 * m]) / g.hx, y = fabs(g.dir[3 * m + 1]) / g.hy;
+    a[d] = g.swap ? y : x;
+    b[d] = g.swap ? x : y;
+    w[d] = m == m0 + d ? g.dir[3 * m + 2] : 0.0;
+  }
+  double dr0[PER], d1[PER], d2[PER];  // z1 = dr0 + sig_e + i d1, z2 = dr0 + sig_e + i d2
+#pragma unroll
+  for (int d = 0; d < PER; ++d) {
+    dr0[d] = 2.0 * (a[d] + b[d]);
+    d1[d] = kSqrt2 * (a[d] + b[d]);
+    d2[d] = kSqrt2 * (a[d] - b[d]);
   }
   if (TABLE) {
-    const double* src = g.coef + (size_t)m * g.n_mat * 32;
-    for (int k = threadIdx.x; k < g.n_mat * 32; k += blockDim.x)
-      coefL[(k >> 5) * kDgRow + (k & 31)] = src[k];
+    for (int k = threadIdx.x; k < n_row; k += blockDim.x) {
+      const double se = k < g.n_mat ? g.sig_e_mat[k] : 0.0;
+      if (SPLIT) tab_se[k] = se;
+#pragma unroll
+      for (int d = 0; d < PER; ++d) {
+        double2 c1 = make_double2(0.0, 0.0), c2 = c1;
+        if (SPLIT) {
+          const double dr = dr0[d] + se;
+          if (k < g.n_mat)
+            c1 = make_double2(recip(fma(dr, dr, d1[d] * d1[d])), recip(fma(dr, dr, d2[d] * d2[d])));
+          tab[PER * k + d] = c1;
+        } else {
+          if (k < g.n_mat) mode_inverse(a[d], b[d], se, c1, c2);
+          tab[2 * k] = c1;
+          tab[2 * k + 1] = c2;
+        }
+      }
+    }
   }
-  __syncthreads();  // faces zeroed, table staged
-  if (loader) {
-    hand_over(r0s, 0);
-    fetch(r0s);
-  }
-  __syncthreads();  // chunk 0 in slot 0
-
-  if (loader) {
-    // before barrier k, chunk k + 1 goes to slot (k + 1) & 1; it sits in
-    // ring entry (k + 1) % depth, loaded depth - 1 rounds earlier
-    for (int k0 = 0; k0 < n_pad; k0 += kDgDepth) {
-#define SLH_DG_LOAD_STEP(U, R)    \
-  hand_over(R, (k0 + U + 1) & 1); \
-  fetch(R);                       \
+  // reflective sides: the inflow is the outflow of the mirrored direction in
+  // the previous iteration, at the same place along the side
+  const int it = REFL ? g.st->si.iter : 0;
+  const bool unegative = (q & (g.swap ? 2 : 1)) != 0, vnegative = (q & (g.swap ? 1 : 2)) != 0;
+  const int ubc = g.swap ? g.bc >> 2 : g.bc, vbc = g.swap ? g.bc : g.bc >> 2;
+  const bool u_in = REFL && (ubc & (unegative ? 2 : 1)), u_out = REFL && (ubc & (unegative ? 1 : 2));
+  const bool v_in = REFL && (vbc & (vnegative ? 2 : 1)), v_out = REFL && (vbc & (vnegative ? 1 : 2));
+  const int* const ru = g.swap ? g.refl_y : g.refl_x;
+  const int* const rv = g.swap ? g.refl_x : g.refl_y;
+  const double2* const b_in =
+      REFL ? reinterpret_cast<const double2*>(g.bnd) + (size_t)((it + 1) & 1) * g.n_dir * (nu + nv)
+           : nullptr;
+  double2* const b_out =
+      REFL ? reinterpret_cast<double2*>(g.bnd) + (size_t)(it & 1) * g.n_dir * (nu + nv) : nullptr;
+#pragma unroll
+  for (int d = 0; d < PER; ++d)
+    for (int k = threadIdx.x; k < n_col; k += blockDim.x) {
+      const int u = k - kDgFront;
+      yf[k * PER + d] = REFL && v_in && u >= 0 && u < nu
+                              ? b_in[(size_t)rv[md[d]] * (nu + nv) + nv + u]
+                              : make_double2(0.0, 0.0);
+    }
+  for (int k = threadIdx.x; k < (SPLIT ? n_waves : g.n_strips); k += blockDim.x) prog[k] = 0;
   __syncthreads();
-      SLH_DG_LOAD_STEP(0, r1s)
-      SLH_DG_LOAD_STEP(1, r2s)
-      SLH_DG_LOAD_STEP(2, r3s)
-      SLH_DG_LOAD_STEP(3, r0s)
-#undef SLH_DG_LOAD_STEP
-    }
-    return;
+
+  const unsigned half = 16u * (unsigned)n;  // bytes of one mode of a source or plane (n < 2^23)
+  const double2* const src = reinterpret_cast<const double2*>(g.src) + (size_t)q * 2 * n;
+  double2* const out = reinterpret_cast<double2*>(g.psi) + (size_t)(q * g.n_grp + grp) * 2 * n;
+  const __amdgpu_buffer_rsrc_t src1 = buffer_of(src, half), src2 = buffer_of(src + n, half);
+  const __amdgpu_buffer_rsrc_t out1 = buffer_of(out, half), out2 = buffer_of(out + n, half);
+  const __amdgpu_buffer_rsrc_t ids =
+      TABLE ? buffer_of(g.mat_off + (size_t)q * n, 4u * n) : buffer_of(g.sig_e, 8u * n);
+  constexpr double kap = kV1i;  // v1 = -1 + i kap
+
+  // SPLIT: this lane's double of a block of columns, two tagged words
+  unsigned long long *take = nullptr, *give = nullptr;  // at column 0
+  const unsigned long long tag = SPLIT ? (unsigned long long)g.st->sweep_tag << 32 : 0ull;
+  const int h_d = lane / (2 * AHEAD), h_k = lane / 2 % AHEAD;  // direction, column in the block
+  double* const h_row = reinterpret_cast<double*>(yf) + 2 * (kDgFront * PER + h_d) + (lane & 1);
+  if (SPLIT) {
+    // [group][boundary][column][direction][part][word]
+    const size_t row = (size_t)nu * (4 * PER);
+    unsigned long long* const h =
+        g.hand + (size_t)(q * g.n_grp + grp) * (g.n_blk - 1) * row + 4 * h_d + 2 * (lane & 1);
+    if (wave == 0 && blk > 0) take = h + (blk - 1) * row;
+    if (wave == n_waves - 1 && blk < g.n_blk - 1) give = h + blk * row;
   }
 
-  // ---- sweeping lanes: Q cells each ----
-  const int t = threadIdx.x;
-  const int span = CW / Q;  // chunk positions t + r span, r < Q
-  double dmA[16], dmF[16];  // cell mode: direction element data
-  if (!TABLE) {
+  const int s0 = SPLIT ? blk * n_waves : 0;  // the workgroup's first strip
+  const int s_end = SPLIT && s0 + n_waves < g.n_strips ? s0 + n_waves : g.n_strips;
+  for (int s = s0 + wave; s < s_end; s += n_waves) {
+    const int rows = nv - 64 * s < 64 ? nv - 64 * s : 64;
+    const int lr = lane < rows ? lane : rows - 1;  // a real row for every lane's loads
+    const int first = lane < rows ? lane : 1 << 30;  // the step of the lane's first column
+    const int steps = nu + rows - 1;
+    const bool last = s + 1 == g.n_strips;
+    // The lane whose v traces go to the LDS row, for the next strip or for a
+    // reflective side; the others write to a word of their own (masking them
+    // off would split the step's schedule).
+    const bool leaves = last ? (v_out && lane == rows - 1) : lane == 63;
+    double2* leave_at = leaves ? yf + PER * (kDgFront - lane) : idle + PER * lane;
+    const int leave_by = leaves ? PER : 0;
+    // without a table, row-major sigma_e: cell (u, v) at cell0 + u cell_u
+    int cell0 = 0, cell_u = 0;
+    if (!TABLE) {
+      const int v = 64 * s + lr;
+      const int x0 = g.swap ? v : 0, y0 = g.swap ? 0 : v;
+      const int i0 = (q & 1) ? g.nx - 1 - x0 : x0, j0 = (q & 2) ? g.ny - 1 - y0 : y0;
+      cell0 = j0 * g.nx + i0;
+      cell_u = g.swap ? ((q & 2) ? -g.nx : g.nx) : ((q & 1) ? -1 : 1);
+    }
+    double2 r1[AHEAD], r2[AHEAD];  // sources in flight
+    int rk[AHEAD];                 // byte offsets of the materials' table rows
+    double re[AHEAD];              // sigma_e
+    int ro[AHEAD];                 // byte offset of the step's slot row
+    const int row_bytes = 16 * rows, o_begin = 16 * 64 * s * nu, o_end = o_begin + nu * row_bytes;
+    int f_t = 0, f_off = o_begin;  // next step to fetch
+    auto fetch = [&](int k) __attribute__((always_inline)) {
+      r1[k] = buffer_load2(src1, 16 * lr, f_off);
+      r2[k] = buffer_load2(src2, 16 * lr, f_off);
+      if (TABLE) {
+        rk[k] = (int)__builtin_amdgcn_raw_buffer_load_b32(ids, 4 * lr, f_off >> 2, 0);
+      } else {
+        const int u = f_t - lane;
+        const int c = cell0 + (u < 0 ? 0 : (u < nu ? u : nu - 1)) * cell_u;
+        re[k] = __builtin_bit_cast(double,
+                                   __builtin_amdgcn_raw_buffer_load_b64(ids, 8 * c, 0, 0));
+      }
+      ro[k] = f_off;
+      ++f_t;
+      f_off += row_bytes;
+      if (f_off == o_end) f_off = o_begin;
+    };
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      dmA[k] = g.dirmat[32 * m + k];
-      dmF[k] = g.dirmat[32 * m + 16 + k];
+    for (int k = 0; k < AHEAD; ++k) fetch(k);
+    // traces of the lane's cell: u face of its previous column, v face
+    double uxr[PER], uxi[PER], uyr[PER], uyi[PER];
+    double2 ui[PER];  // reflected inflow on the u side
+#pragma unroll
+    for (int d = 0; d < PER; ++d) {
+      uxr[d] = uxi[d] = uyr[d] = uyi[d] = 0.0;
+      if (REFL)
+        ui[d] = u_in ? b_in[(size_t)ru[md[d]] * (nu + nv) + 64 * s + lr] : make_double2(0.0, 0.0);
+    }
+    // the next step: whether the lane has a cell, and with a table its c1 and
+    // c2, read a step early
+    bool next_act = false;
+    double2 n1[PER], n2[PER];
+    double n_se = 0.0;
+    auto look_up = [&](int t, int k) __attribute__((always_inline)) {
+      next_act = (unsigned)(t - first) < (unsigned)nu;
+      if (!TABLE) return;
+      const int off = next_act ? rk[k] : 32 * g.n_mat;
+      const double2* const row = reinterpret_cast<const double2*>(
+          reinterpret_cast<const char*>(tab) + (SPLIT ? PER / 2 : 1) * off);
+      if (SPLIT) {
+        n_se = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(tab_se) + (off >> 2));
+#pragma unroll
+        for (int d = 0; d < PER; ++d) n1[d] = row[d];
+      } else {
+        n1[0] = row[0];
+        n2[0] = row[1];
+      }
+    };
+    // every source has arrived: the loop's waits then count its own accesses
+    // only, and leave the younger ones in flight (vmcnt 0)
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    look_up(0, 0);
+    // the words of the block of columns at t0 (a column past the mesh: the last)
+    unsigned long long in0 = 0ull, in1 = 0ull;
+    auto peek = [&](int t0) __attribute__((always_inline)) {
+      const int u = t0 + h_k < nu ? t0 + h_k : nu - 1;
+      in0 = __hip_atomic_load(take + (size_t)u * (4 * PER), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+      in1 = __hip_atomic_load(take + (size_t)u * (4 * PER) + 1, __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (SPLIT && take) peek(0);
+    // After the traces of all steps before t have been left (columns before
+    // t - 63): for the next workgroup, its last eight columns; for the next
+    // strip, how many there are.
+    auto publish = [&](int t) __attribute__((always_inline)) {
+      if (SPLIT && give) {
+        const int u = t - 63 - AHEAD + h_k;
+        if (u >= 0 && u < nu) {
+          const unsigned long long v = (unsigned long long)__double_as_longlong(h_row[2 * PER * u]);
+          __hip_atomic_store(give + (size_t)u * (4 * PER), tag | v >> 32, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(give + (size_t)u * (4 * PER) + 1, tag | (v & 0xffffffffull),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      } else if (!last) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0)
+          __hip_atomic_store(&prog[s - s0], t - 63, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    };
+    for (int t0 = 0; t0 < steps; t0 += AHEAD) {
+      if (SPLIT && take) {
+        if (t0 < nu) {
+          // the workgroup before has left the traces of these columns; those of
+          // the next block are looked at a block early
+          while (!__all((in0 >> 32 << 32) == tag && (in1 >> 32 << 32) == tag)) {
+            __builtin_amdgcn_s_sleep(1);
+            peek(t0);
+          }
+          if (t0 + h_k < nu)
+            h_row[2 * PER * (t0 + h_k)] = __longlong_as_double((long long)(in0 << 32 |
+                                                                      (in1 & 0xffffffffull)));
+          peek(t0 + AHEAD < nu ? t0 + AHEAD : t0);
+        }
+      } else if (s > s0 && t0 < nu) {
+        // the strip before has left the traces of these columns
+        const int need = t0 + AHEAD < nu ? t0 + AHEAD : nu;
+        while (__hip_atomic_load(&prog[s - s0 - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <
+               need)
+          __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+      }
+      // the first lane's v trace of the next step, read a step early too
+      const double2* const yin = yf + PER * (kDgFront + (t0 < nu ? t0 : nu));
+      double2 y0[PER], y1[PER];
+#pragma unroll
+      for (int d = 0; d < PER; ++d) y1[d] = yin[d];
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k) {
+        const bool act = next_act;
+        double2 c1[PER], c2[PER];
+#pragma unroll
+        for (int d = 0; d < PER; ++d) {
+          if (TABLE && SPLIT) {
+            const double dr = dr0[d] + n_se;
+            c1[d] = make_double2(dr * n1[d].x, -d1[d] * n1[d].x);
+            c2[d] = make_double2(dr * n1[d].y, -d2[d] * n1[d].y);
+          } else if (TABLE) {
+            c1[d] = n1[d];
+            c2[d] = n2[d];
+          } else {
+            mode_inverse(a[d], b[d], re[k], c1[d], c2[d]);
+            // no flux before the lane's first column
+            c1[d] = make_double2(act ? c1[d].x : 0.0, act ? c1[d].y : 0.0);
+            c2[d] = make_double2(act ? c2[d].x : 0.0, act ? c2[d].y : 0.0);
+          }
+        }
+        look_up(t0 + k + 1, (k + 1) % AHEAD);
+#pragma unroll
+        for (int d = 0; d < PER; ++d) {
+          y0[d] = y1[d];
+          if (k + 1 < AHEAD) y1[d] = yin[PER * (k + 1) + d];
+        }
+        // the reads for the next step stay ahead of this step's arithmetic
+        __builtin_amdgcn_sched_barrier(0);
+        const double2 S1 = r1[k], S2 = r2[k];
+        double2 acc1, acc2;
+#pragma unroll
+        for (int d = 0; d < PER; ++d) {
+          const double yr = lane_shift(y0[d].x, uyr[d]);
+          const double yi = lane_shift(y0[d].y, uyi[d]);
+          if (REFL && u_in && t0 + k < rows) {  // uniform: some lane's first column
+            const bool now = t0 + k == lane;
+            uxr[d] = now ? ui[d].x : uxr[d];
+            uxi[d] = now ? ui[d].y : uxi[d];
+          }
+          const double sr = fma(a[d], uxr[d], b[d] * yr);
+          const double t1r = S1.x + sr, t1i = fma(a[d], uxi[d], fma(b[d], yi, S1.y));
+          const double t2r = S2.x + sr, t2i = fma(-a[d], uxi[d], fma(b[d], yi, S2.y));
+          const double X1r = c1[d].x * t1r - c1[d].y * t1i, X1i = c1[d].x * t1i + c1[d].y * t1r;
+          const double X2r = c2[d].x * t2r - c2[d].y * t2i, X2i = c2[d].x * t2i + c2[d].y * t2r;
+          const double Pr = X1r + X2r, Pi = X1i + X2i, Qr = X1r - X2r, Qi = X1i - X2i;
+          uxr[d] = fma(-kap, Pi, -Pr);
+          uxi[d] = fma(kap, Qr, -Qi);
+          uyr[d] = fma(-kap, Qi, -Pr);
+          uyi[d] = fma(kap, Qr, -Pi);
+          if (PER == 1) {  // the reduction applies the weight
+            acc1 = make_double2(X1r, X1i);
+            acc2 = make_double2(X2r, X2i);
+          } else if (d == 0) {
+            acc1 = make_double2(w[d] * X1r, w[d] * X1i);
+            acc2 = make_double2(w[d] * X2r, w[d] * X2i);
+          } else {
+            acc1.x += w[d] * X1r;
+            acc1.y += w[d] * X1i;
+            acc2.x += w[d] * X2r;
+            acc2.y += w[d] * X2i;
+          }
+        }
+        const int lane_off = act ? 16 * lane : kNoCell;
+        buffer_store2<SPLIT>(out1, lane_off, ro[k], acc1.x, acc1.y);
+        buffer_store2<SPLIT>(out2, lane_off, ro[k], acc2.x, acc2.y);
+#pragma unroll
+        for (int d = 0; d < PER; ++d) leave_at[d] = make_double2(uyr[d], uyi[d]);
+        leave_at += leave_by;
+        if (REFL && u_out && t0 + k >= nu - 1) {  // uniform: some lane's last column
+          if (t0 + k - first == nu - 1) {
+#pragma unroll
+            for (int d = 0; d < PER; ++d)
+              xf[d * n_xf + 64 * (s - s0) + lane] = make_double2(uxr[d], uxi[d]);
+          }
+        }
+        fetch(k);  // after the last use of the stage's registers
+      }
+      publish(t0 + AHEAD);
     }
   }
-  const double hx = g.hx, hy = g.hy;
-  const double MM[4][4] = {
-      {hx * hy / 9.0, hx * hy / 18.0, hx * hy / 18.0, hx * hy / 36.0},
-      {hx * hy / 18.0, hx * hy / 9.0, hx * hy / 36.0, hx * hy / 18.0},
-      {hx * hy / 18.0, hx * hy / 36.0, hx * hy / 9.0, hx * hy / 18.0},
-      {hx * hy / 36.0, hx * hy / 18.0, hx * hy / 18.0, hx * hy / 9.0}};
-  double4* __restrict__ out = reinterpret_cast<double4*>(g.psi + (long long)m * 4 * nx * ny);
-  int cd = 0, cp = 0;  // next chunk to prepare
-  // the prepared cells: present, indices (0 for an absent cell, whose
-  // arithmetic runs on stale data and is dropped) and layout position
-  bool c_has[Q];
-  int c_i[Q], c_j[Q];
-  long long c_pos[Q];
-  double P[Q][16];    // table: G; cell mode: B^-1, D, S^-1, G of the block factorisation
-  double r0[Q][4];    // table: B S; cell mode: MM S
-  auto prepare = [&](int slot) __attribute__((always_inline)) {
-    const bool live = cd < n_diag;
-    const int hi = live ? diag_hi(cd) : -1;
-    const long long rb = run_base(live ? cd : n_diag - 1);
+  if (REFL) {  // the outflow traces on reflective sides, for the mirrored directions
+    __syncthreads();
 #pragma unroll
-    for (int r = 0; r < Q; ++r) {
-      const int tr = t + r * span;
-      const int ip = cp + tr;
-      const bool h = ip <= hi;
-      const int jp = cd - ip;
-      c_has[r] = h;
-      c_i[r] = h ? (apos ? ip : nx - 1 - ip) : 0;
-      c_j[r] = h ? (bpos ? jp : ny - 1 - jp) : 0;
-      c_pos[r] = rb + c_i[r];
-      const double2 sa = slotA[slot * CW + tr], sb = slotB[slot * CW + tr];
-      const double4 S = make_double4(sa.x, sa.y, sb.x, sb.y);
-      const double key = slotK[slot * CW + tr];
-      if (TABLE) {
-        const double* c = coefL + (size_t)(h ? (int)key : 0) * kDgRow;
-        r0[r][0] = S.x;  // B S, formed by the loader
-        r0[r][1] = S.y;
-        r0[r][2] = S.z;
-        r0[r][3] = S.w;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) P[r][k] = c[16 + k];
-      } else {
-        double A[4][4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-#pragma unroll
-          for (int l = 0; l < 4; ++l) A[a][l] = dmA[4 * a + l] + key * MM[a][l];
-          r0[r][a] = MM[a][0] * S.x + MM[a][1] * S.y + MM[a][2] * S.z + MM[a][3] * S.w;
-        }
-        // Block factorisation over the node pairs {0,1} and {2,3}: the
-        // leading block B by its adjugate, G = B^-1 C, the Schur complement
-        // S = E - D G and its inverse.  Every principal block and Schur
-        // complement of the element matrix keeps a positive definite
-        // symmetric part (see k_dg_coef), and a 2x2 matrix with one has a
-        // determinant at least that of its symmetric part, so both
-        // determinants are positive: two reciprocals per cell, where the
-        // scalar factorisation takes four in sequence.
-        const double ib = recip(A[0][0] * A[1][1] - A[0][1] * A[1][0]);
-        const double B00 = A[1][1] * ib, B01 = -A[0][1] * ib;
-        const double B10 = -A[1][0] * ib, B11 = A[0][0] * ib;
-        const double G00 = B00 * A[0][2] + B01 * A[1][2], G01 = B00 * A[0][3] + B01 * A[1][3];
-        const double G10 = B10 * A[0][2] + B11 * A[1][2], G11 = B10 * A[0][3] + B11 * A[1][3];
-        const double S00 = A[2][2] - (A[2][0] * G00 + A[2][1] * G10);
-        const double S01 = A[2][3] - (A[2][0] * G01 + A[2][1] * G11);
-        const double S10 = A[3][2] - (A[3][0] * G00 + A[3][1] * G10);
-        const double S11 = A[3][3] - (A[3][0] * G01 + A[3][1] * G11);
-        const double is = recip(S00 * S11 - S01 * S10);
-        P[r][0] = B00; P[r][1] = B01; P[r][2] = B10; P[r][3] = B11;
-        P[r][4] = A[2][0]; P[r][5] = A[2][1]; P[r][6] = A[3][0]; P[r][7] = A[3][1];
-        P[r][8] = S11 * is; P[r][9] = -S01 * is; P[r][10] = -S10 * is; P[r][11] = S00 * is;
-        P[r][12] = G00; P[r][13] = G01; P[r][14] = G10; P[r][15] = G11;
-      }
+    for (int d = 0; d < PER; ++d) {
+      double2* const o = b_out + (size_t)md[d] * (nu + nv);
+      if (u_out)
+        for (int k = threadIdx.x; k < n_xf && 64 * s0 + k < nv; k += blockDim.x)
+          o[64 * s0 + k] = xf[d * n_xf + k];
+      if (v_out && s_end == g.n_strips)
+        for (int k = threadIdx.x; k < nu; k += blockDim.x)
+          o[nv + k] = yf[PER * (kDgFront + k) + d];
     }
-    if (live) {
-      cp += CW;
-      if (cp > hi) {
-        ++cd;
-        cp = cd < n_diag ? diag_lo(cd) : 0;
-      }
-    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Plan of the sweep
+// ---------------------------------------------------------------------------
+constexpr int kDgMaxWaves = 16;
+constexpr int kDgSplitWaves = 4;  // strips of a workgroup with four directions per wave
+
+size_t dg_sweep_lds_bytes(const DgPlan& p, int n_mat, bool refl) {
+  const size_t rows = n_mat > 0 ? (size_t)n_mat + 1 : 0;
+  const bool split = p.per == kDgSplit;
+  return sizeof(double2) * (size_t)p.per *
+             (p.nu + kDgPad + 64 + (refl ? (split ? 64 * p.n_waves : p.nv) : 0) +
+              (split ? 1 : 2) * rows) +
+         sizeof(double) * (split ? rows : 0) +
+         sizeof(int) * (size_t)(split ? p.n_waves : p.n_strips);
+}
+
+DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool refl, size_t lds) {
+  DgPlan p;
+  // wave-steps of a direction with the lanes along y or along x
+  auto cost = [](int nu, int nv) {
+    return (long long)((nv + 63) / 64) * (nu + (nv < 64 ? nv : 64) - 1);
   };
-  prepare(0);
-  for (int k = 0; k < n_pad; ++k) {
-    __syncthreads();  // traces of chunk k - 1 written, chunk k + 1 in its slot
-    double x[Q][4];
-#pragma unroll
-    for (int r = 0; r < Q; ++r) {
-      // a face's two traces as one 16-byte word (neighbouring lanes hold
-      // neighbouring cells: consecutive words, no bank conflicts)
-      const double2 ux = reinterpret_cast<const double2*>(xf)[c_j[r]];
-      const double2 uy = reinterpret_cast<const double2*>(yf)[c_i[r]];
-      const double u0 = ux.x, u1 = ux.y, u2 = uy.x, u3 = uy.y;
-      const double* Pr = P[r];
-      if (TABLE) {
-        x[r][0] = r0[r][0] + Pr[0] * u0 + Pr[1] * u1 + Pr[2] * u2 + Pr[3] * u3;
-        x[r][1] = r0[r][1] + Pr[4] * u0 + Pr[5] * u1 + Pr[6] * u2 + Pr[7] * u3;
-        x[r][2] = r0[r][2] + Pr[8] * u0 + Pr[9] * u1 + Pr[10] * u2 + Pr[11] * u3;
-        x[r][3] = r0[r][3] + Pr[12] * u0 + Pr[13] * u1 + Pr[14] * u2 + Pr[15] * u3;
-      } else {
-        // F couples node (kx, ky) to the x-face traces only when kx is the
-        // inflow column and to the y-face traces only when ky is the inflow
-        // row: the other half of its entries are zero and are skipped
-        double yv[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          double acc = r0[r][e];
-          if ((e & 1) == (apos ? 0 : 1)) acc = acc + dmF[4 * e] * u0 + dmF[4 * e + 1] * u1;
-          if ((e >> 1) == (bpos ? 0 : 1)) acc = acc + dmF[4 * e + 2] * u2 + dmF[4 * e + 3] * u3;
-          yv[e] = acc;
-        }
-        // w = B^-1 y_top, z = y_bot - D w, x_bot = S^-1 z, x_top = w - G x_bot
-        const double w0 = Pr[0] * yv[0] + Pr[1] * yv[1], w1 = Pr[2] * yv[0] + Pr[3] * yv[1];
-        const double z0 = yv[2] - (Pr[4] * w0 + Pr[5] * w1);
-        const double z1 = yv[3] - (Pr[6] * w0 + Pr[7] * w1);
-        x[r][2] = Pr[8] * z0 + Pr[9] * z1;
-        x[r][3] = Pr[10] * z0 + Pr[11] * z1;
-        x[r][0] = w0 - (Pr[12] * x[r][2] + Pr[13] * x[r][3]);
-        x[r][1] = w1 - (Pr[14] * x[r][2] + Pr[15] * x[r][3]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < Q; ++r) {
-      if (!c_has[r]) continue;
-      const double x0 = x[r][0], x1 = x[r][1], x2 = x[r][2], x3 = x[r][3];
-      const int ci = c_i[r], cj = c_j[r];
-      reinterpret_cast<double2*>(xf)[cj] = make_double2(apos ? x1 : x0, apos ? x3 : x2);
-      reinterpret_cast<double2*>(yf)[ci] = make_double2(bpos ? x2 : x0, bpos ? x3 : x1);
-      // outflow on a reflective downwind side, for the mirrored direction
-      if (REFL && rx_out) {
-        if (ci == (apos ? nx - 1 : 0)) {
-          b_out[2 * cj] = apos ? x1 : x0;
-          b_out[2 * cj + 1] = apos ? x3 : x2;
-        }
-      }
-      if (REFL && ry_out) {
-        if (cj == (bpos ? ny - 1 : 0)) {
-          b_out[2 * ny + 2 * ci] = bpos ? x2 : x0;
-          b_out[2 * ny + 2 * ci + 1] = bpos ? x3 : x1;
-        }
-      }
-      // the plane is read once, by the direction sum: non-temporal stores
-      double* po = reinterpret_cast<double*>(out + (c_pos[r] - lay_base));
-      __builtin_nontemporal_store(x0, po);
-      __builtin_nontemporal_store(x1, po + 1);
-      __builtin_nontemporal_store(x2, po + 2);
-      __builtin_nontemporal_store(x3, po + 3);
-    }
-    prepare((k + 1) & 1);
-  }
-  // Drain this wave's stores before the sweeping and loader paths join: the
-  // compiler's wait counting cannot follow a mix of pending loads and stores,
-  // and would otherwise wait for every load of the loader's ring.
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-}
-
-template <bool TABLE, int Q, bool REFL>
-__global__ __launch_bounds__(512) void k_dg_sweep_pc(DgArgs g) {
-  if (g.st->si.done) return;  // the whole workgroup: no barrier is left pending
-  const int m = blockIdx.x;
-  const bool apos = g.dir[3 * m + 0] > 0.0, bpos = g.dir[3 * m + 1] > 0.0;
-  if (apos) {
-    if (bpos) sweep_dir<TABLE, Q, REFL, true, true>(g);
-    else sweep_dir<TABLE, Q, REFL, true, false>(g);
+  p.swap = cost(ny, nx) < cost(nx, ny) ? 1 : 0;
+  p.nu = p.swap ? ny : nx;
+  p.nv = p.swap ? nx : ny;
+  p.n_strips = (p.nv + 63) / 64;
+  const long long nc = (long long)nx * ny;
+  auto fill = [&](int per) {
+    p.per = per;
+    const int most = per == kDgSplit ? kDgSplitWaves : kDgMaxWaves;
+    p.n_waves = p.n_strips < most ? p.n_strips : most;
+    p.n_blk = per == kDgSplit ? (p.n_strips + most - 1) / most : 1;
+    p.n_grp = (n_dir / 4 + per - 1) / per;
+    // A table entry costs about 60 operations per material and direction in
+    // each sweep's workgroup, the inverses per cell about 25 per step and
+    // wave: the table where it is the cheaper of the two and fits (and, with
+    // 1/|z|^2 in it, where that does not underflow).
+    p.table = n_mat > 0 && n_mat * 60 <= 25ll * 64 * p.n_waves * (p.nu + p.nv) &&
+              (per == 1 || sig_max < 1e100) &&
+              dg_sweep_lds_bytes(p, (int)std::min<long long>(n_mat, 1 << 20), refl) <= lds;
+    return dg_sweep_lds_bytes(p, p.table ? (int)n_mat : 0, refl) <= lds;
+  };
+  // Four directions per wave quarter the planes, which a sweep writes at about
+  // 6 TB/s and the reduction reads at 3.2, but a step takes 0.55 us instead of
+  // 0.16 (times the waves that share a SIMD).  1024^2, S_16: 1.2 + 0.6 ms per
+  // sweep and reduction against 2.45 + 2.65 ms with one direction; 256^2, S_8:
+  // 0.29 + 0.01 ms estimated against 0.09 + 0.045 measured.
+  auto us = [&]() {
+    const double share = p.per == kDgSplit || p.n_waves <= 8 ? 1.0 : p.n_waves / 8.0;
+    return (p.nu + 72.0 * p.n_strips) * (p.per == kDgSplit ? 0.55 : 0.16 * share) +
+           128.0 * p.n_grp * (double)nc * (1.0 / 6e6 + 1.0 / 3.2e6);
+  };
+  if (n_dir >= 4 * kDgSplit && fill(kDgSplit)) {
+    const double split_us = us();
+    fill(1);
+    if (split_us < us()) fill(kDgSplit);
   } else {
-    if (bpos) sweep_dir<TABLE, Q, REFL, false, true>(g);
-    else sweep_dir<TABLE, Q, REFL, false, false>(g);
+    fill(1);
   }
-}
-
-size_t dg_sweep_lds_bytes(bool table, int cw, int n_mat, int nx, int ny) {
-  return sizeof(double) * ((size_t)2 * cw * 5 + (table ? (size_t)n_mat * kDgRow : 0) +
-                           (size_t)2 * (nx + ny));
+  return p;
 }
 
 hipError_t launch_si_start(const DgArgs& a, int si_max, hipStream_t s) {
@@ -555,8 +654,8 @@ hipError_t launch_si_start(const DgArgs& a, int si_max, hipStream_t s) {
   long long b = (nc + 255) / 256;
   const int grid = (int)(b < 2048 ? (b < 1 ? 1 : b) : 2048);
   const long long nb = a.bnd ? (long long)a.n_dir * 2 * (a.nx + a.ny) : 0;
-  hipLaunchKernelGGL(k_si_start, dim3(grid), dim3(256), 0, s, a.nx, a.ny, a.sig_s,
-                     a.phi_post, a.phi_c, a.src, a.bnd ? a.bnd + nb : nullptr, nb, a.st, si_max);
+  hipLaunchKernelGGL(k_si_start, dim3(grid), dim3(256), 0, s, a, a.bnd ? a.bnd + nb : nullptr, nb,
+                     si_max);
   return hipGetLastError();
 }
 
@@ -584,212 +683,118 @@ hipError_t launch_si_check(DevState* st, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_dg_sweep(const DgArgs& a, bool table, hipStream_t s) {
-  const size_t lds = dg_sweep_lds_bytes(table, a.cw, a.n_mat, a.nx, a.ny);
-  const int q = a.cells_per_lane;  // cells per sweeping and per loader lane
-  if ((q != 1 && q != 2 && q != 4) || a.cw % (64 * q) || a.cw / (64 * q) > 4)
+// Sixteen waves leave 128 vector registers to each, eight 256: sources of
+// four or of eight columns in flight.
+template <bool TABLE, bool REFL>
+static void sweep_launch(const DgArgs& a, size_t lds, hipStream_t s) {
+  const dim3 block(64 * a.n_waves);
+  const int n_all = 4 * a.n_grp;
+  if (a.per == kDgSplit)  // a grid that gives every class its tasks
+    hipLaunchKernelGGL((k_dg_sweep<kDgSplit, TABLE, REFL, 8, 64 * kDgSplitWaves>),
+                       dim3((n_all + 7) / 8 * 8 * a.n_blk), block, lds, s, a);
+  else if (a.n_waves <= 8)
+    hipLaunchKernelGGL((k_dg_sweep<1, TABLE, REFL, 8, 512>), dim3(n_all), block, lds, s, a);
+  else
+    hipLaunchKernelGGL((k_dg_sweep<1, TABLE, REFL, 4, 1024>), dim3(n_all), block, lds, s, a);
+}
+
+hipError_t launch_dg_sweep(const DgArgs& a, hipStream_t s) {
+  const bool table = a.mat_off != nullptr;
+  const bool refl = a.bc != 0 && a.bnd != nullptr, split = a.per == kDgSplit;
+  const size_t lds = dg_sweep_lds_bytes(a, table ? a.n_mat : 0, refl);
+  if ((a.per != 1 && !split) || a.n_waves < 1 || a.n_strips != (a.nv + 63) / 64 ||
+      a.n_waves > (split ? kDgSplitWaves : kDgMaxWaves) || a.n_grp * a.per < a.n_quad ||
+      a.n_blk * a.n_waves < (split ? a.n_strips : 1) || (split && a.n_blk > 1 && !a.hand) ||
+      (!split && a.n_blk != 1) || a.nx * a.ny >= 1 << 23)
     return hipErrorInvalidValue;
-  const dim3 block(2 * a.cw / q);  // as many loader waves as sweeping waves
-  const bool refl = a.bc != 0 && a.bnd != nullptr;
-#define SLH_DG_SWEEP(T_, Q_)                                                                  \
-  do {                                                                                        \
-    if (refl) hipLaunchKernelGGL((k_dg_sweep_pc<T_, Q_, true>), dim3(a.n_dir), block, lds, s, a); \
-    else hipLaunchKernelGGL((k_dg_sweep_pc<T_, Q_, false>), dim3(a.n_dir), block, lds, s, a);     \
-  } while (0)
   if (table) {
-    if (q == 1) SLH_DG_SWEEP(true, 1);
-    else if (q == 2) SLH_DG_SWEEP(true, 2);
-    else SLH_DG_SWEEP(true, 4);
+    if (refl) sweep_launch<true, true>(a, lds, s);
+    else sweep_launch<true, false>(a, lds, s);
   } else {
-    if (q == 1) SLH_DG_SWEEP(false, 1);
-    else if (q == 2) SLH_DG_SWEEP(false, 2);
-    else SLH_DG_SWEEP(false, 4);
+    if (refl) sweep_launch<false, true>(a, lds, s);
+    else sweep_launch<false, false>(a, lds, s);
   }
-#undef SLH_DG_SWEEP
   return hipGetLastError();
 }
 
-// The reduction of a source iteration, in two kernels.  k_dg_famsum: at
-// every node of each layout, the sum of w_m psi_m over that layout's
-// directions in their order (every plane read once, in whole cache lines).
-// k_dg_combine, per row-major cell: phi_new = sum over layout A + sum over
-// layout B, in place (the sweep read only S); the next iterate's nodal source
-// S = sigma_s/(4 pi) (phi_new + phi_post) in both layouts (unused when the
+size_t dg_hand_words(const DgPlan& p) {
+  return (size_t)4 * p.n_grp * (p.n_blk - 1) * p.nu * 4 * p.per;
+}
+
+// The reduction of a source iteration (k_dg_combine): phi_new = the nodal
+// values of the four quadrants' sums over their planes, in place (the sweep
+// read only the sources); the next iterate's source S = sigma_s/(4 pi)
+// (phi_new + phi_post) in every quadrant's coefficients (unused when the
 // iteration stops here); block partials of |phi_new - phi_old|^2 and
 // |phi_new|^2, or |phi_new + phi_pre + phi_post|^2 when phi_pre is given (the
 // step's whole flux as the reference of the stopping test).  With the
 // diffusion correction the combine keeps phi_new - phi_old in dnode instead
-// and leaves the source and the residual to k_dsa_apply.
-constexpr int kRedBlock = 256;
+// and leaves the source and the residual to k_dsa_apply.  The last block of a
+// grid to leave its partials takes the iteration's decision.
+constexpr int kRedWaves = 4;  // a wave per quadrant
+constexpr int kRedBlock = 64 * kRedWaves;
 
-int dg_reduce_partials(long long n_nodes) {
-  long long b = (n_nodes + kRedBlock - 1) / kRedBlock;
-  return (int)(b < 1024 ? (b < 1 ? 1 : b) : 1024);
+int dg_reduce_partials(int nx, int ny) {
+  const long long tiles = (long long)((nx + 7) / 8) * ((ny + 7) / 8);
+  return (int)(tiles < 1024 ? tiles : 1024);
 }
 
-__global__ __launch_bounds__(kRedBlock) void k_dg_famsum(
-    const int* __restrict__ fam_dirs, int n_a, int n_dir, long long n_nodes,
-    const double* __restrict__ psi, const double* __restrict__ dir,
-    double* __restrict__ phi_fam, const DevState* st) {
-  if (st->si.done) return;
-  // the first half of the grid sums layout A, the second layout B
-  const int half = (int)(gridDim.x >> 1);
-  const bool fb = (int)blockIdx.x >= half;
-  const int u0 = fb ? n_a : 0, u1 = fb ? n_dir : n_a;
-  double2* __restrict__ out = reinterpret_cast<double2*>(phi_fam + (fb ? n_nodes : 0));
-  // two nodes per thread (16-byte loads; n_nodes = 4 cells is even)
-  const long long n2 = n_nodes >> 1;
-  for (long long k = (long long)(blockIdx.x - (fb ? half : 0)) * kRedBlock + threadIdx.x;
-       k < n2; k += (long long)half * kRedBlock) {
-    // sixteen planes' loads in flight per step, added in direction order
-    double vx = 0.0, vy = 0.0;
-    int u = u0;
-    for (; u + 16 <= u1; u += 16) {
-      double2 t[16];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {  // read once: non-temporal loads
-        const double* pp = psi + (long long)fam_dirs[u + e] * n_nodes + 2 * k;
-        t[e].x = __builtin_nontemporal_load(pp);
-        t[e].y = __builtin_nontemporal_load(pp + 1);
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const double w = dir[3 * fam_dirs[u + e] + 2];
-        vx += w * t[e].x;
-        vy += w * t[e].y;
-      }
+__device__ __forceinline__ double wave_sum(double v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
+// Leaves the block's partials (the first wave's sums, in a fixed order) and,
+// in the last block of the grid to do so, sums all of them in a fixed order
+// (strided per-thread sums, wave sums, the waves in order) and takes the
+// iteration's decision: done when |phi_new - phi_old| <= tol |phi_new|
+// (converged), when the iteration limit is reached, or when the residual is
+// not finite.  After a diffusion correction (dsa) it also books that
+// correction's conjugate-gradient iterations and whether they reached their
+// tolerance.  The partials cross the XCDs as agent-scope stores and loads;
+// the stores have reached memory when the block counts itself.  (As a launch
+// of its own the decision took 3-4 us of every iteration.)
+__device__ __forceinline__ void residual(double dsum, double nsum, double* partials, DevState* st,
+                                         double si_tol, int si_max, int dsa) {
+  __shared__ double s_d[kRedWaves], s_n[kRedWaves];
+  __shared__ int s_last;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (wave == 0) {
+    dsum = wave_sum(dsum);
+    nsum = wave_sum(nsum);
+    if (lane == 0) {
+      __hip_atomic_store(&partials[2 * blockIdx.x], dsum, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&partials[2 * blockIdx.x + 1], nsum, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const unsigned before = __hip_atomic_fetch_add(&st->red_blocks, 1u, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+      s_last = before == gridDim.x - 1;
     }
-    for (; u < u1; ++u) {
-      const int m = fam_dirs[u];
-      const double2 t = reinterpret_cast<const double2*>(psi + (long long)m * n_nodes)[k];
-      vx += dir[3 * m + 2] * t.x;
-      vy += dir[3 * m + 2] * t.y;
-    }
-    out[k] = make_double2(vx, vy);
   }
-}
-
-// Partials of a block: tree sum of the threads' values in a fixed order.
-__device__ __forceinline__ void block_partials(double dsum, double nsum, double* partials) {
-  __shared__ double s_d[kRedBlock], s_n[kRedBlock];
-  s_d[threadIdx.x] = dsum;
-  s_n[threadIdx.x] = nsum;
   __syncthreads();
-  for (int off = kRedBlock / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      s_d[threadIdx.x] += s_d[threadIdx.x + off];
-      s_n[threadIdx.x] += s_n[threadIdx.x + off];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    partials[2 * blockIdx.x] = s_d[0];
-    partials[2 * blockIdx.x + 1] = s_n[0];
-  }
-}
-
-// The next iterate's nodal source of cell (ci, cj) in both layouts, and the
-// cell's contribution to the stopping test.
-__device__ __forceinline__ void next_source(int nx, int ny, long long c,
-                                            double4 v, double4 d, double ssc, double pp,
-                                            const double* phi_pre, double* S, double& dsum,
-                                            double& nsum) {
-  const long long n = (long long)nx * ny;
-  const int ci = (int)(c % nx), cj = (int)(c / nx);
-  const double4 sv = make_double4(ssc * (v.x + pp), ssc * (v.y + pp), ssc * (v.z + pp),
-                                  ssc * (v.w + pp));
-  reinterpret_cast<double4*>(S)[lay_pos(nx, ny, ci, cj, true)] = sv;
-  reinterpret_cast<double4*>(S)[n + lay_pos(nx, ny, ci, cj, false)] = sv;
-  const double r = phi_pre ? phi_pre[c] + pp : 0.0;
-  dsum += d.x * d.x + d.y * d.y + d.z * d.z + d.w * d.w;
-  nsum += (v.x + r) * (v.x + r) + (v.y + r) * (v.y + r) + (v.z + r) * (v.z + r) +
-          (v.w + r) * (v.w + r);
-}
-
-__global__ __launch_bounds__(kRedBlock) void k_dg_combine(
-    int nx, int ny, const double* __restrict__ phi_fam,
-    double* __restrict__ phi, const double* __restrict__ sig_s,
-    const double* __restrict__ phi_post, const double* __restrict__ phi_pre,
-    double* __restrict__ S, double* __restrict__ partials, double* __restrict__ dnode,
-    const DevState* st) {
-  if (st->si.done) return;
-  const double inv4pi = 0.25 / M_PI;
-  const long long n = (long long)nx * ny;
-  const double4* fam = reinterpret_cast<const double4*>(phi_fam);
-  double dsum = 0.0, nsum = 0.0;
-  for (long long c = (long long)blockIdx.x * kRedBlock + threadIdx.x; c < n;
-       c += (long long)gridDim.x * kRedBlock) {
-    const int ci = (int)(c % nx), cj = (int)(c / nx);
-    const double4 a = fam[lay_pos(nx, ny, ci, cj, true)];
-    const double4 b = fam[n + lay_pos(nx, ny, ci, cj, false)];
-    const double4 v = make_double4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
-    const double4 o = reinterpret_cast<const double4*>(phi)[c];
-    const double4 d = make_double4(v.x - o.x, v.y - o.y, v.z - o.z, v.w - o.w);
-    reinterpret_cast<double4*>(phi)[c] = v;
-    if (dnode) {  // the correction, the source and the residual come later
-      reinterpret_cast<double4*>(dnode)[c] = d;
-      continue;
-    }
-    next_source(nx, ny, c, v, d, sig_s[c] * inv4pi, phi_post[c], phi_pre, S, dsum, nsum);
-  }
-  if (dnode) return;  // the same for the whole grid
-  block_partials(dsum, nsum, partials);
-}
-
-// phi += delta (per cell) at every node, the next source, and partials of
-// |dnode + delta|^2 and |phi|^2 (or of the whole-flux norm) for k_dg_residual.
-__global__ __launch_bounds__(kRedBlock) void k_dsa_apply(
-    int nx, int ny, double* __restrict__ phi,
-    const double* __restrict__ dnode, const double* __restrict__ delta,
-    const double* __restrict__ sig_s, const double* __restrict__ phi_post,
-    const double* __restrict__ phi_pre, double* __restrict__ S, double* __restrict__ partials,
-    const DevState* st) {
-  if (st->si.done) return;
-  const double inv4pi = 0.25 / M_PI;
-  const long long n = (long long)nx * ny;
-  double dsum = 0.0, nsum = 0.0;
-  for (long long c = (long long)blockIdx.x * kRedBlock + threadIdx.x; c < n;
-       c += (long long)gridDim.x * kRedBlock) {
-    const double dl = delta[c];
-    const double4 o = reinterpret_cast<const double4*>(phi)[c];
-    const double4 dn = reinterpret_cast<const double4*>(dnode)[c];
-    const double4 v = make_double4(o.x + dl, o.y + dl, o.z + dl, o.w + dl);
-    const double4 d = make_double4(dn.x + dl, dn.y + dl, dn.z + dl, dn.w + dl);
-    reinterpret_cast<double4*>(phi)[c] = v;
-    next_source(nx, ny, c, v, d, sig_s[c] * inv4pi, phi_post[c], phi_pre, S, dsum, nsum);
-  }
-  block_partials(dsum, nsum, partials);
-}
-
-// Sums the block partials with a fixed association order (strided
-// per-thread sums, then a tree) and takes the iteration's decision: done
-// when |phi_new - phi_old| <= tol |phi_new| (converged), when the iteration
-// limit is reached, or when the residual is not finite.  After a diffusion
-// correction (dsa) it also books that correction's conjugate-gradient
-// iterations and whether they reached their tolerance.
-__global__ __launch_bounds__(256) void k_dg_residual(const double* partials, int n_part,
-                                                     DevState* st, double si_tol, int si_max,
-                                                     int dsa) {
-  if (st->si.done) return;
-  __shared__ double s_d[256], s_n[256];
+  if (!s_last) return;
   double d = 0.0, n = 0.0;
-  for (int b = threadIdx.x; b < n_part; b += 256) {
-    d += partials[2 * b];
-    n += partials[2 * b + 1];
+  for (int b = threadIdx.x; b < (int)gridDim.x; b += kRedBlock) {
+    d += __hip_atomic_load(&partials[2 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    n += __hip_atomic_load(&partials[2 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  s_d[threadIdx.x] = d;
-  s_n[threadIdx.x] = n;
+  d = wave_sum(d);
+  n = wave_sum(n);
+  if (lane == 0) {
+    s_d[wave] = d;
+    s_n[wave] = n;
+  }
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      s_d[threadIdx.x] += s_d[threadIdx.x + off];
-      s_n[threadIdx.x] += s_n[threadIdx.x + off];
-    }
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    const double dn2 = s_d[0], nrm2 = s_n[0];
+    double dn2 = s_d[0], nrm2 = s_n[0];
+    for (int k = 1; k < kRedWaves; ++k) {
+      dn2 += s_d[k];
+      nrm2 += s_n[k];
+    }
     const double dn = sqrt(dn2), nrm = sqrt(nrm2);
+    st->red_blocks = 0u;
     st->si.dn2_prev = st->si.iter > 0 ? st->si.dn2 : 0.0;
     st->si.dn2 = dn2;
     st->si.nrm2 = nrm2;
@@ -808,28 +813,203 @@ __global__ __launch_bounds__(256) void k_dg_residual(const double* partials, int
   }
 }
 
+// A cell's contribution to the stopping test.
+__device__ __forceinline__ void add_norms(double4 v, double4 d, double r, double& dsum,
+                                          double& nsum) {
+  dsum += d.x * d.x + d.y * d.y + d.z * d.z + d.w * d.w;
+  nsum += (v.x + r) * (v.x + r) + (v.y + r) * (v.y + r) + (v.z + r) * (v.z + r) +
+          (v.w + r) * (v.w + r);
+}
+
+// A block takes tiles of 8 x 8 cells; wave q works in quadrant q: it sums the
+// quadrant's planes at the lane's cell, the four nodal sums meet in LDS, and
+// after the cells' update (wave 0) it forms the quadrant's next source.  The
+// cells of a slot row lie on a diagonal of the mesh, so a wave takes its tile
+// along the diagonals of its quadrant: eight lanes then read, and write, one
+// cache line (cells in row-major order took a line for every lane: 75 us a
+// reduction against 18 us, 140x140, S_12).
+constexpr int kTile = 8;
+constexpr int kRedCells = kTile * kTile;
+constexpr int kNodeRow = kRedCells + 1;  // LDS stride of a node: [node][cell]
+
+// Tiles of the mesh, and tile cell of lane l in quadrant q: column (d - e) mod
+// 8 of the u axis and row e of the v axis, d and e the lane's octal digits,
+// u and v mirrored as the quadrant is.
+struct TileCell {
+  int cell, slot, at;  // the cell, its slot, its place in the tile (row-major)
+  bool ok;
+};
+__device__ __forceinline__ TileCell tile_cell(const DgArgs& g, int tile, int q, int lane) {
+  const int tx = (g.nx + kTile - 1) / kTile;
+  const int e = lane & 7, d = lane >> 3, f = (d - e) & 7;
+  const int x = g.swap ? e : f, y = g.swap ? f : e;
+  const int i = (q & 1) ? kTile - 1 - x : x, j = (q & 2) ? kTile - 1 - y : y;
+  const int ci = tile % tx * kTile + i, cj = tile / tx * kTile + j;
+  TileCell t;
+  t.ok = ci < g.nx && cj < g.ny;
+  // a real cell for every lane's loads
+  const int ri = ci < g.nx ? ci : g.nx - 1, rj = cj < g.ny ? cj : g.ny - 1;
+  t.cell = rj * g.nx + ri;
+  t.slot = dg_slot(g, q, ri, rj);
+  t.at = j * kTile + i;
+  return t;
+}
+
+__device__ __forceinline__ int dg_tiles(const DgArgs& g) {
+  return ((g.nx + kTile - 1) / kTile) * ((g.ny + kTile - 1) / kTile);
+}
+
+// The quadrant's next source at the lane's cell from the nodal one in LDS.
+__device__ __forceinline__ void put_source(const DgArgs& g, int q, const TileCell& t,
+                                           const double* s_src) {
+  const int n = g.nx * g.ny;
+  double2 m1, m2;
+  to_modes(s_src[quad_node(q, g.swap, 0, 0) * kNodeRow + t.at],
+           s_src[quad_node(q, g.swap, 0, 1) * kNodeRow + t.at],
+           s_src[quad_node(q, g.swap, 1, 0) * kNodeRow + t.at],
+           s_src[quad_node(q, g.swap, 1, 1) * kNodeRow + t.at], m1, m2);
+  double2* const S = reinterpret_cast<double2*>(g.src) + (size_t)q * 2 * n;
+  S[t.slot] = m1;
+  S[n + t.slot] = m2;
+}
+
+// Nodal source of a cell into LDS (wave 0).
+__device__ __forceinline__ void nodal_source(double* s_src, int at, double ssc, double4 v,
+                                             double pp) {
+  s_src[0 * kNodeRow + at] = ssc * (v.x + pp);
+  s_src[1 * kNodeRow + at] = ssc * (v.y + pp);
+  s_src[2 * kNodeRow + at] = ssc * (v.z + pp);
+  s_src[3 * kNodeRow + at] = ssc * (v.w + pp);
+}
+
+__global__ __launch_bounds__(kRedBlock) void k_dg_combine(DgArgs g, double* partials,
+                                                          double si_tol, int si_max) {
+  DevState* const st = g.st;
+  if (st->si.done) return;
+  if (blockIdx.x == 0 && threadIdx.x < 8) {  // ready for the next sweep
+    st->ticket[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) st->sweep_tag += 1u;
+  }
+  __shared__ double s_phi[4][4 * kNodeRow];  // nodal sums of each quadrant
+  __shared__ double s_src[4 * kNodeRow];     // nodal source
+  const double inv4pi = 0.25 / M_PI;
+  const int n = g.nx * g.ny;
+  const int lane = threadIdx.x & 63;
+  const int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const double2* const plane = reinterpret_cast<const double2*>(g.psi) + (size_t)q * g.n_grp * 2 * n;
+  const double* const dir = g.dir + 3 * (size_t)q * g.n_quad;
+  const int n_tiles = dg_tiles(g);
+  double dsum = 0.0, nsum = 0.0;
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    const TileCell t = tile_cell(g, tile, q, lane);
+    double2 m1 = make_double2(0.0, 0.0), m2 = m1;
+    auto add = [&](int u, double2 t1, double2 t2) __attribute__((always_inline)) {
+      const double w = g.per == 1 ? dir[3 * u + 2] : 1.0;
+      m1.x += w * t1.x;
+      m1.y += w * t1.y;
+      m2.x += w * t2.x;
+      m2.y += w * t2.y;
+    };
+    int u = 0;
+    for (; u + 8 <= g.n_grp; u += 8) {  // eight planes' loads in flight
+      double2 t1[8], t2[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        t1[e] = plane[(size_t)(u + e) * 2 * n + t.slot];
+        t2[e] = plane[(size_t)(u + e) * 2 * n + n + t.slot];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) add(u + e, t1[e], t2[e]);
+    }
+    if (u < g.n_grp) {  // the rest as one batch too (past the end, loads of the last one)
+      double2 t1[7], t2[7];
+#pragma unroll
+      for (int e = 0; e < 7; ++e) {
+        const int v = u + e < g.n_grp ? u + e : g.n_grp - 1;
+        t1[e] = plane[(size_t)v * 2 * n + t.slot];
+        t2[e] = plane[(size_t)v * 2 * n + n + t.slot];
+      }
+#pragma unroll
+      for (int e = 0; e < 7; ++e)
+        if (u + e < g.n_grp) add(u + e, t1[e], t2[e]);
+    }
+    double x[4];
+    from_modes(m1, m2, x);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      s_phi[q][quad_node(q, g.swap, k >> 1, k & 1) * kNodeRow + t.at] = x[k];
+    __syncthreads();
+    if (q == 0 && t.ok) {
+      double f[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int o = k * kNodeRow + t.at;
+        f[k] = (s_phi[0][o] + s_phi[3][o]) + (s_phi[1][o] + s_phi[2][o]);
+      }
+      const double4 v = make_double4(f[0], f[1], f[2], f[3]);
+      const double4 o = reinterpret_cast<const double4*>(g.phi_c)[t.cell];
+      const double4 d = make_double4(v.x - o.x, v.y - o.y, v.z - o.z, v.w - o.w);
+      reinterpret_cast<double4*>(g.phi_c)[t.cell] = v;
+      if (g.dnode) {  // the correction, the source and the residual come later
+        reinterpret_cast<double4*>(g.dnode)[t.cell] = d;
+      } else {
+        const double pp = g.phi_post[t.cell];
+        nodal_source(s_src, t.at, g.sig_s[t.cell] * inv4pi, v, pp);
+        add_norms(v, d, g.phi_pre ? g.phi_pre[t.cell] + pp : 0.0, dsum, nsum);
+      }
+    }
+    __syncthreads();
+    if (!g.dnode && t.ok) put_source(g, q, t, s_src);
+  }
+  if (g.dnode) return;  // the same for the whole grid
+  residual(dsum, nsum, partials, st, si_tol, si_max, 0);
+}
+
+// phi += delta (per cell) at every node, the next source, and the residual of
+// |dnode + delta|^2 and |phi|^2 (or of the whole-flux norm).
+__global__ __launch_bounds__(kRedBlock) void k_dsa_apply(DgArgs g,
+                                                         const double* __restrict__ delta,
+                                                         double* partials, double si_tol,
+                                                         int si_max) {
+  DevState* const st = g.st;
+  if (st->si.done) return;
+  __shared__ double s_src[4 * kNodeRow];
+  const double inv4pi = 0.25 / M_PI;
+  const int lane = threadIdx.x & 63;
+  const int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int n_tiles = dg_tiles(g);
+  double dsum = 0.0, nsum = 0.0;
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    const TileCell t = tile_cell(g, tile, q, lane);
+    if (q == 0 && t.ok) {
+      const double dl = delta[t.cell];
+      const double4 o = reinterpret_cast<const double4*>(g.phi_c)[t.cell];
+      const double4 dn = reinterpret_cast<const double4*>(g.dnode)[t.cell];
+      const double4 v = make_double4(o.x + dl, o.y + dl, o.z + dl, o.w + dl);
+      const double4 d = make_double4(dn.x + dl, dn.y + dl, dn.z + dl, dn.w + dl);
+      reinterpret_cast<double4*>(g.phi_c)[t.cell] = v;
+      const double pp = g.phi_post[t.cell];
+      nodal_source(s_src, t.at, g.sig_s[t.cell] * inv4pi, v, pp);
+      add_norms(v, d, g.phi_pre ? g.phi_pre[t.cell] + pp : 0.0, dsum, nsum);
+    }
+    __syncthreads();
+    if (t.ok) put_source(g, q, t, s_src);
+    __syncthreads();
+  }
+  residual(dsum, nsum, partials, st, si_tol, si_max, 1);
+}
+
 hipError_t launch_dg_reduce(const DgArgs& a, double* partials, int n_part, double si_tol,
                             int si_max, hipStream_t s) {
-  const long long n_nodes = 4ll * a.nx * a.ny;
-  hipLaunchKernelGGL(k_dg_famsum, dim3(2 * dg_reduce_partials(n_nodes / 2)), dim3(kRedBlock), 0, s,
-                     a.fam_dirs, a.fam_n, a.n_dir, n_nodes, (const double*)a.psi, a.dir,
-                     a.phi_fam, (const DevState*)a.st);
-  hipLaunchKernelGGL(k_dg_combine, dim3(n_part), dim3(kRedBlock), 0, s, a.nx, a.ny,
-                     (const double*)a.phi_fam, a.phi_c, a.sig_s, a.phi_post, a.phi_pre, a.src,
-                     partials, a.dnode, (const DevState*)a.st);
-  if (!a.dnode)
-    hipLaunchKernelGGL(k_dg_residual, dim3(1), dim3(256), 0, s, (const double*)partials, n_part,
-                       a.st, si_tol, si_max, 0);
+  hipLaunchKernelGGL(k_dg_combine, dim3(n_part), dim3(kRedBlock), 0, s, a, partials, si_tol,
+                     si_max);
   return hipGetLastError();
 }
 
 hipError_t launch_dsa_apply(const DgArgs& a, const double* delta, double* partials, int n_part,
                             double si_tol, int si_max, hipStream_t s) {
-  hipLaunchKernelGGL(k_dsa_apply, dim3(n_part), dim3(kRedBlock), 0, s, a.nx, a.ny,
-                     a.phi_c, (const double*)a.dnode, delta, a.sig_s, a.phi_post, a.phi_pre,
-                     a.src, partials, (const DevState*)a.st);
-  hipLaunchKernelGGL(k_dg_residual, dim3(1), dim3(256), 0, s, (const double*)partials, n_part,
-                     a.st, si_tol, si_max, 1);
+  hipLaunchKernelGGL(k_dsa_apply, dim3(n_part), dim3(kRedBlock), 0, s, a, delta, partials, si_tol,
+                     si_max);
   return hipGetLastError();
 }
 

@@ -319,7 +319,10 @@ struct DevState {
   // ended with a non-finite weight or tally, 4 the plan exceeded the source
   // bank (clamped to it)
   int numeric;
-  int pad2;
+  unsigned int red_blocks;      // blocks of the running reduction that left their partials
+  unsigned int ticket[8];       // tasks taken of the running sweep, per class of blocks
+  unsigned int sweep_tag;       // tag of the next sweep's traces between workgroups
+  unsigned int pad2;
   unsigned long long bal[2 * B_NFIELDS];
   unsigned long long step;      // time step being computed (point streams, history ids)
   // source iteration of the collided solve (or the conjugate gradients of
@@ -451,76 +454,75 @@ hipError_t launch_qmc_points(uint64_t stream, uint32_t dim0, uint32_t nd, uint32
                              hipStream_t s);
 const uint32_t* sobol_table_host();
 
-// Start of run d of a sweep layout (see DgArgs): the number of cells of an
-// nx x ny mesh on the runs before it, sum over t < d of
-// min(t, nx - 1) - max(0, t - (ny - 1)) + 1, in closed form.
-__host__ __device__ __forceinline__ long long lay_run(int nx, int ny, int d) {
-  const long long D = d, X = nx, Y = ny;
-  const long long a = D <= X ? D * (D + 1) / 2 : X * (X + 1) / 2 + (D - X) * X;
-  const long long b = D <= Y ? 0 : (D - Y) * (D - Y + 1) / 2;
-  return a - b;
-}
+// How the collided solve sweeps a mesh: the u axis a wave walks along and the
+// v axis its lanes lie on (swap 0: u = x, v = y; 1: the other way round),
+// strips of 64 rows along v, waves per workgroup and workgroups per group of
+// directions, directions per wave and groups per quadrant, and whether the
+// materials' inverses come from a table.
+struct DgPlan {
+  int swap, nu, nv, n_strips, n_waves, n_blk, per, n_grp;
+  bool table;
+};
 
-// Position of cell (i, j) in sweep layout A (anti = true) or B.
-__host__ __device__ __forceinline__ long long lay_pos(int nx, int ny, int i, int j, bool anti) {
-  const int d = anti ? i + j : i - j + ny - 1;
-  const int lo = d - (ny - 1) > 0 ? d - (ny - 1) : 0;
-  return lay_run(nx, ny, d) + (i - lo);
-}
-
-struct DgArgs {
+struct DgArgs : DgPlan {
   int nx, ny;
   double hx, hy;
-  int n_dir;
-  const double* dir;     // [m][3]: ox, oy, w
-  // Sweep layouts: the cells of a direction whose components have the same
-  // sign are visited along anti-diagonals (i + j constant), the others along
-  // diagonals (i - j constant).  Layout A stores the cells anti-diagonal by
-  // anti-diagonal (index d = i + j), layout B diagonal by diagonal (index
-  // d = i - j + ny - 1); within either, cell i - lo(d) of the run, lo(d) =
-  // max(0, d - (ny - 1)), and the run starts at lay_run(nx, ny, d).  A chunk
-  // of a sweep is then a contiguous piece of its layout, so the sweep's loads
-  // and its plane stores are whole cache lines.
-  const int* fam_dirs;   // the directions of layout A in order, then those of B
-  int fam_n;             // how many belong to layout A
-  const double* sig_e;   // per cell, layout A then layout B (2 nx ny)
+  int n_dir, n_quad;     // directions, and directions of each quadrant
+  const double* dir;     // [m][3]: ox, oy, w, the quadrants one after the other
+                         // (bit 0 of the quadrant: ox < 0, bit 1: oy < 0)
+  const double* sig_e;   // per cell (row-major), without a table
   const double* sig_s;   // per cell (row-major)
   const double* phi_post;// per cell
   const double* phi_pre; // per cell, or null: the stopping test's norm is then
                          // over phi_c alone, else over phi_c + phi_pre + phi_post
   double* phi_c;         // nodal [cell][4] (row-major): the collided iterate, updated in place
-  double* src;           // nodal sigma_s/(4 pi)(phi_c + phi_post), layout A then B (8 nx ny)
-  double* psi;           // [m][position][4] in the layout of direction m (psi_m;
-                         // the reduction applies w_m)
-  double* phi_fam;       // nodal sums of w_m psi_m over each layout's directions,
-                         // layout A then B (8 nx ny)
+  double* src;           // sigma_s/(4 pi)(phi_c + phi_post) as coefficients of the
+                         // element's modes: [quadrant][mode][slot], complex
+  double* psi;           // psi_m of each direction (one per group) or sums of w_m
+                         // psi_m over the directions of a group, as coefficients:
+                         // [quadrant][group][mode][slot], complex
   double* dnode;         // nodal phi^{k+1/2} - phi^k (row-major) for the diffusion
                          // correction (diffusion synthetic acceleration), or null
-  const double* dirmat;  // [m][32]: A0 then F (uniform mesh)
-  // table mode: material of each cell (layout A then B) and
-  // [m][material][32] = B then G
-  const int* mat_id;
+  // with a table: byte offset of each cell's material in it (32 bytes each),
+  // [quadrant][slot], and sigma_e of each material (null without one)
+  const int* mat_off;
   int n_mat;
-  const double* coef;
-  int cw;                // cells per chunk (a multiple of 64 cells_per_lane, at
-                         // most 256 cells_per_lane)
-  int n_chunks;          // dg_chunks(nx, ny, cw)
-  int cells_per_lane;    // cells per sweeping and per loader lane: 1, 2 or 4
+  const double* sig_e_mat;
   // reflective sides (1 x_lo, 2 x_hi, 4 y_lo, 8 y_hi): the inflow of a
   // direction on such a side is the outflow of its mirror image (refl_x,
   // refl_y) from the previous iteration.  bnd holds two buffers of [n_dir]
-  // [2 ny x traces | 2 nx y traces], written in iterations of the parity of
-  // their index (null when no side reflects)
+  // [nv traces of u faces | nu traces of v faces], complex coefficients,
+  // written in iterations of the parity of their index (null when no side
+  // reflects)
   int bc;
   const int* refl_x;
   const int* refl_y;
   double* bnd;
+  unsigned long long* hand;  // traces between the workgroups of a group
+                             // (dg_hand_words tagged words), or null
   DevState* st;          // si.done: skip the iteration; the reduction's decision
 };
-hipError_t launch_dg_tables(int n_dir, int n_mat, const double* dir, const double* sig_e_mat,
-                            double hx, double hy, double* dirmat, double* coef, hipStream_t s);
-long long dg_chunks(int nx, int ny, int cw);
-size_t dg_sweep_lds_bytes(bool table, int cw, int n_mat, int nx, int ny);
+
+// Place of cell (i, j) in the order of visits of quadrant q: strips of 64
+// rows along v, in a strip the slot row (u + l) mod nu of the step at which
+// lane l holds column u, then the lanes.
+__host__ __device__ __forceinline__ int dg_slot(int nx, int ny, int swap, int nu, int nv, int q,
+                                                int i, int j) {
+  const int x = (q & 1) ? nx - 1 - i : i, y = (q & 2) ? ny - 1 - j : j;
+  const int u = swap ? y : x, v = swap ? x : y;
+  const int l = v & 63, v0 = v - l;
+  const int rows = nv - v0 < 64 ? nv - v0 : 64;
+  return v0 * nu + (u + l) % nu * rows + l;
+}
+__device__ __forceinline__ int dg_slot(const DgArgs& g, int q, int i, int j) {
+  return dg_slot(g.nx, g.ny, g.swap, g.nu, g.nv, q, i, j);
+}
+
+// The plan of a mesh with n_mat distinct sigma_e (0: not known) up to sig_max
+// and lds bytes of LDS per workgroup.
+DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool refl, size_t lds);
+size_t dg_hand_words(const DgPlan& p);
+size_t dg_sweep_lds_bytes(const DgPlan& p, int n_mat, bool refl);
 // Start of a step's source iteration: phi_c = 0, iteration state reset, the
 // first iterate's nodal source, reflected traces of the first sweep zeroed.
 hipError_t launch_si_start(const DgArgs& a, int si_max, hipStream_t s);
@@ -574,14 +576,14 @@ hipError_t launch_cg_solve_one_block(const CgArgs& a, double tol, int max_iter, 
 bool cg_one_block(long long n);
 hipError_t launch_cg_iteration(const CgArgs& a, double tol, int si_max, hipStream_t s);
 hipError_t launch_cg_to_nodal(const CgArgs& a, double* phi_c, const int* halt, hipStream_t s);
-hipError_t launch_dg_sweep(const DgArgs& a, bool table, hipStream_t s);
-// One reduction of a source iteration: the direction sum of the planes (each
-// layout's directions in order, then the two sums added) replaces phi_c in
+hipError_t launch_dg_sweep(const DgArgs& a, hipStream_t s);
+// One reduction of a source iteration: the direction sum of the planes (the
+// groups of a quadrant in order, then the four quadrants) replaces phi_c in
 // place, the next iterate's source is formed, and the residual decides
 // st->si.done (n_part blocks, dg_reduce_partials).
 hipError_t launch_dg_reduce(const DgArgs& a, double* partials, int n_part, double si_tol,
                             int si_max, hipStream_t s);
-int dg_reduce_partials(long long n_nodes);
+int dg_reduce_partials(int nx, int ny);
 
 // util.hip
 hipError_t launch_fill_u64(unsigned long long* p, long long n, unsigned long long v,
