@@ -127,7 +127,6 @@ struct Sizes {
   long long n_faces;    // boundary faces emitting an inflow (0 without one)
   long long n_src_cap;  // source bank: at most n_p (1 + 1/16) + n_cells particles per pass
   int n_dir;
-  int n_copies;  // private tally copies
   bool fp32;
   int n_mat;  // distinct sigma_e
   DgPlan dg;  // the collided solve's sweep
@@ -315,15 +314,6 @@ static Sizes sizes_of(const slh_problem* p) {
   z.cap = p->census_cap > 0 ? p->census_cap : std::max<long long>(p->n_particles, 1);
   z.n_cand = z.cap + z.n_src_cap;
   z.n_dir = p->sn_order * p->sn_order;
-  // private tally copies: 16 per XCD on meshes of 64K cells or more (the
-  // adds of a pass spread over more copies wait less on each other: on a
-  // 1024^2 mesh 128 copies take each pass from 44 to 40 ms, where 32, 64 and
-  // 256 copies do not), else 8 per XCD; halved while a tally array would
-  // exceed 1 GB, down to one copy per XCD, then below
-  z.n_copies = z.n_cells >= 65536 ? 128 : 64;
-  while (z.n_copies > 1 &&
-         (size_t)z.n_copies * kTallyStride * 8 * (size_t)z.n_cells > ((size_t)1 << 30))
-    z.n_copies /= 2;
   z.fp32 = p->precision == SLH_FP32_TRACK;
   z.diffusion = p->closure == SLH_CLOSE_DIFFUSION;
   z.dsa = !z.diffusion && p->si_accel == SLH_ACCEL_DSA;
@@ -354,7 +344,7 @@ static Sizes sizes_of(const slh_problem* p) {
   b += nc * 32 * 2 + (size_t)tree_leaves(z.n_cells + z.n_faces) * 16 * 2;  // sources, count trees
   b += (size_t)kMajGroups * kMajBins * 8;    // majorant histograms
   b += (size_t)z.n_faces * 8;                // inflow of the boundary faces
-  b += nc * 8 * kTallyStride * 3 * (size_t)z.n_copies;  // tallies
+  b += nc * 8 * kTallyStride * 3 * (size_t)kTallyCopies;  // tallies
   b += nc * 8 * 3 + nc * 32;                 // phi_pre/post/R, phi_c
   if (z.diffusion || z.dsa)
     b += nc * 8 * 9 + 4 * 1024 * 8;          // CG: diag, cE, cN, x, r, z, p x2, q; partials
@@ -656,9 +646,9 @@ static slh_status setup(slh_solver* s) {
   ALLOC(s->ctreeR, double, 2 * s->tree_L);
   ALLOC(s->maj_hist, unsigned long long, kMajGroups * kMajBins);
   if (z.n_faces) ALLOC(s->inflow, double, z.n_faces);
-  ALLOC(s->Tpre, unsigned long long, (size_t)z.n_copies * kTallyStride * nc);
-  ALLOC(s->Tpost, unsigned long long, (size_t)z.n_copies * kTallyStride * nc);
-  ALLOC(s->TR, unsigned long long, (size_t)z.n_copies * kTallyStride * nc);
+  ALLOC(s->Tpre, unsigned long long, (size_t)kTallyCopies * kTallyStride * nc);
+  ALLOC(s->Tpost, unsigned long long, (size_t)kTallyCopies * kTallyStride * nc);
+  ALLOC(s->TR, unsigned long long, (size_t)kTallyCopies * kTallyStride * nc);
   ALLOC(s->phi_pre, double, nc);
   ALLOC(s->phi_post, double, nc);
   ALLOC(s->phi_R, double, nc);
@@ -897,8 +887,6 @@ static PassArgs pass_args(slh_solver* s, int kind) {
   a.out_src_base = s->z.cap;
   a.Ta = kind == 1 ? s->Tpre : s->TR;
   a.Tb = kind == 1 ? s->Tpost : s->TR;
-  a.n_copies = s->z.n_copies;
-  a.xcd_local = s->z.n_copies % kNumXcd == 0 ? 1 : 0;
   a.copy_stride = (long long)kTallyStride * s->z.n_cells;
   a.st = s->st;
   return a;
@@ -1025,7 +1013,7 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
   const double inv_adt = 1.0 / s->adt;
   const double cdt = p.steady ? s->horizon : p.c * p.dt;  // longest path of a history
   const long long cstride = (long long)kTallyStride * nc;
-  const long long n_tally = (long long)z.n_copies * kTallyStride * nc;
+  const long long n_tally = (long long)kTallyCopies * kTallyStride * nc;
   // source iterations launched in this step's batch (each predicated on the
   // device's stopping test), none without a collided solve
   const int n_it = s->skip_remap ? 0 : s->batch_run;
@@ -1043,7 +1031,7 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
       HIP_TRY(launch_mc_pass(pass_args(s, 1), z.fp32, s->grid1, st));
       return SLH_OK;
     case kMid: {
-      HIP_TRY(launch_tally_to_flux(s->Tpre, s->phi_pre, s->Tpost, s->phi_post, nc, z.n_copies,
+      HIP_TRY(launch_tally_to_flux(s->Tpre, s->phi_pre, s->Tpost, s->phi_post, nc, kTallyCopies,
                                    cstride, s->st, inv_adt, st));
       hipLaunchKernelGGL(k_snapshot, dim3(1), dim3(64), 0, st, s->st, s->bal_store + 0, 1, 0);
       if (use_cg(s)) {
@@ -1080,7 +1068,7 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
     default: {  // kEnd: the remap census is the state at t_{n+1} (capped)
       // without a remap leg the solution is the pure-MC flux of pass 1
       HIP_TRY(launch_tally_to_flux(s->skip_remap ? s->Tpre : s->TR, s->phi_R, nullptr, nullptr,
-                                   nc, z.n_copies, cstride, s->st, inv_adt, st));
+                                   nc, kTallyCopies, cstride, s->st, inv_adt, st));
       hipLaunchKernelGGL(k_snapshot, dim3(1), dim3(64), 0, st, s->st, s->bal_store + 1, 2,
                          n_it > 0 ? 1 : 0);
       void* nb = s->bank_mem[1 - s->cur];

@@ -427,20 +427,24 @@ struct PassArgs {
   SrcRec<float>* src32;
   uint8_t* alive;
   long long out_src_base;  // slot of source particle s is out_src_base + s
-  // tallies: n_copies private copies of one fixed-point word per cell (word
-  // stride kTallyStride), copy c at offset c * copy_stride.  xcd_local: the
-  // copies are split evenly over the eight XCDs, a workgroup adds only into
-  // its own XCD's copies, and the adds are workgroup-scope atomics, which
-  // the XCD's L2 resolves (device-scope atomics go past the L2)
+  // tallies: kTallyCopies private copies of one fixed-point word per cell
+  // (word stride kTallyStride), copy c at offset c * copy_stride, split evenly
+  // over the eight XCDs: a workgroup adds only into its own XCD's copies, and
+  // the adds are workgroup-scope atomics, which the XCD's L2 resolves
+  // (device-scope atomics go past the L2)
   unsigned long long* Ta;
   unsigned long long* Tb;
-  int n_copies;
-  int xcd_local;
   long long copy_stride;
   DevState* st;
 };
 
 constexpr int kNumXcd = 8;  // XCDs of the device (hardware XCC ids 0..7)
+
+// Private tally copies: four per XCD.  The waves' caches leave few adds to
+// them: on a 1024^2 mesh one per XCD to sixteen take the same, but on small
+// ones the cells' lines are busy: 140^2, 2e6 histories, passes of 188, 166,
+// 155, 154, 157 us with 1, 2, 4, 8, 16 copies per XCD.
+constexpr int kTallyCopies = 4 * kNumXcd;
 
 // ---------------------------------------------------------------------------
 // Launch wrappers (defined in the .hip files)
