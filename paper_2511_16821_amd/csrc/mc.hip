@@ -109,6 +109,23 @@ template <> struct Real<float> {
 enum { EV_CENSUS = 0, EV_COLLIDE = 1, EV_XFACE = 2, EV_YFACE = 3 };
 enum { END_NONE = 0, END_CENSUS, END_LEAK, END_CUTOFF };
 
+// States of a lane: without a history, tracking one, its history at a
+// collision, its history at its end.  A segment is cheap and every iteration
+// has one for each running lane; a collision (three points, a sine and cosine,
+// a logarithm) and the change from a finished history to the next (balance,
+// census record, bank record, first optical depth) cost as much as several
+// segments, and in any one iteration only a few lanes are there.  So lanes
+// wait until a quarter of the wave's live lanes have a collision, or kRefillAt
+// lanes are free, or none runs.  (The order of a wave's work does not show in
+// the results.)  1024^2, N_s = 3, 2e8 histories: passes of 27.1 and 21.4 ms
+// served at once, 21.9 / 19.9 with 12 free and 8 colliding lanes, 20.5 / 18.6
+// as here, 22.3 / 18.7 with 32 and 24; 30x50 steady, where a wave has 16
+// histories: 0.38 ms at once, 0.43 with twelve colliding lanes, 0.34 with a
+// quarter of the live ones.
+enum { LN_IDLE = 0, LN_RUN, LN_COL, LN_END };
+constexpr int kRefillAt = 24;
+constexpr int kCollideShare = 4;
+
 __device__ __forceinline__ double maxabs4(const double* q) {
   return fmax(fmax(fabs(q[0]), fabs(q[1])), fmax(fabs(q[2]), fabs(q[3])));
 }
@@ -188,8 +205,10 @@ constexpr long long kWorkChunk = 1024;
 // a wave start on neighbouring work items (cell order) and stay near each
 // other, so many adds of a busy region meet in the cache instead of queueing
 // at the same L2 lines; integer sums make the result the same as with one
-// atomic per add.  512 slots per wave (24 KB per block) keep three blocks per
-// compute unit.
+// atomic per add.  FP64: 512 slots per wave (24 KB per block),
+// three blocks per compute unit, which the registers allow; FP32: 256, four
+// blocks (256^2, 2e7 histories: passes of 0.87 and 0.65 ms against 0.97 and
+// 0.68 with three).
 //
 // The hash is multiplicative and the copy is the wave's: the cells that a wave
 // visits are a disc of the mesh, whose rows fell on the same slots by the low
@@ -198,13 +217,9 @@ constexpr long long kWorkChunk = 1024;
 // a pass: six in ten went past the cache; the passes take 30.2 and 21.1 ms
 // against 33.6 and 29.9, and 28.7 and 20.3 without any tally).  Flushing every
 // 16, 32, 64, 128 iterations: 30.5, 30.2, 30.2, 30.4 ms.
-constexpr int kTcBits = 9;
-constexpr int kTcSlots = 1 << kTcBits;
+template <typename R> constexpr int kTcBits = sizeof(R) == 4 ? 8 : 9;
+template <typename R> constexpr int kPassWaves = sizeof(R) == 4 ? 4 : 3;  // per SIMD
 constexpr int kTcFlush = 32;
-
-__device__ __forceinline__ int tc_slot(unsigned w) {
-  return (int)((w * 0x9E3779B1u) >> (32 - kTcBits));
-}
 
 // Copies of a tracking block's balance in LDS (odd stride: the copies start
 // in different banks).
@@ -350,8 +365,10 @@ __global__ __launch_bounds__(256) void k_emit(PassArgs a) {
 }
 
 template <typename R, int KIND>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_mc_pass(PassArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<R>))) void k_mc_pass(
+    PassArgs a) {
   if (a.st->halt) return;
+  constexpr int kTcSlots = 1 << kTcBits<R>;
   // Block balance in kBalCopies LDS copies picked by lane: with a per-lane
   // address the adds are plain LDS atomics, where one shared address would
   // make the compiler serialise them over the active lanes in a scalar loop.
@@ -387,7 +404,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   StageRec<R>* const bout = Real<R>::out(a);
   const int n_lim = a.n_lim;
 
-  bool have = false;
+  int ls = LN_IDLE;     // the lane's state
+  int end = END_NONE;   // how its history ended (LN_END)
   long long q_next = 0, q_end = 0;  // the wave's current chunk of work indices (uniform)
   bool q_done = false;              // no chunk is left for this wave
   const long long n_wv = (long long)gridDim.x * (blockDim.x / 64);
@@ -449,10 +467,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   };
 
   for (;;) {
-    // idle lanes take the next indices of the wave's chunk, in lane order; a
-    // used-up chunk is replaced by the wave's next one
+    const unsigned long long m_run = __ballot(ls == LN_RUN);
+    const bool more = !q_done || q_next < q_end;  // work is left for this wave
+    const unsigned long long m_free = __ballot(ls == LN_END || (more && ls == LN_IDLE));
     bool fresh = false;
-    if (__any(!have)) {
+    if (m_free && (!m_run || __popcll(m_free) >= kRefillAt)) {
+      if (ls == LN_END) {
+        if (KIND == 2 && end == END_CENSUS && a.keep_census) {
+          const long long slot = from_census ? g : a.out_src_base + (g - n_in);
+          Real<R>::stage(bout + slot, px, py, ox, oy, w, hid, iy * a.nx + ix);
+          a.alive[slot] = 1;
+          lane_alive++;
+        }
+        // fold the history's balance into the block (fixed point, exact)
+        const double wend = (double)w;
+        if (!isfinite(wend) || !isfinite(acc_abs) || !isfinite(acc_sca)) lane_bad++;
+        bal_add(my_bal, from_census ? B_CENSUS_IN_W : B_SOURCE_W, w0, inv_W);
+        bal_add(my_bal, B_ABSORBED, acc_abs, inv_W);
+        if (acc_sca != 0.0) bal_add(my_bal, B_SCATTERED, acc_sca, inv_W);
+        bal_add(my_bal, end == END_CENSUS ? B_CENSUS : (end == END_LEAK ? B_LEAKED : B_CUTOFF),
+                wend, inv_W);
+        ls = LN_IDLE;
+      }
+      // idle lanes take the next indices of the wave's chunk, in lane order; a
+      // used-up chunk is replaced by the wave's next one
       if (q_next >= q_end && !q_done) {
         unsigned long long base = 0ull;
         if (q_dyn) {
@@ -468,18 +506,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         q_end = base + chunk < n_tot ? (long long)(base + chunk) : (long long)n_tot;
         q_done = base + chunk >= n_tot;
       }
-      const unsigned long long need = __ballot(!have);
+      const unsigned long long need = __ballot(ls == LN_IDLE);
       const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
           (uint32_t)(need >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
       const long long avail = q_end - q_next;
-      if (!have && (long long)rank < avail) {
+      if (ls == LN_IDLE && (long long)rank < avail) {
         g = q_next + rank;
         fresh = true;
       }
       q_next += (long long)__popcll(need) < avail ? (long long)__popcll(need) : avail;
     }
     if (fresh) {
-      have = true;
+      ls = LN_RUN;
       lane_hist++;
       seg_p = 0;
       acc_abs = 0.0;
@@ -537,16 +575,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         dcur = 1;
       }
     }
-    if (!__any(have)) {
+    const unsigned long long m_col = __ballot(ls == LN_COL);
+    if (m_col && (!m_run || kCollideShare * __popcll(m_col) >= __popcll(m_col | m_run))) {
+      if (ls == LN_COL) {
+        // isotropic re-emission, scatter counter n <- n + 1
+        const R ua = PointU<R>::u(point_u32n(s_sobol, a.points, stream, dcur, pidx));
+        const R ub = PointU<R>::u(point_u32n(s_sobol, a.points, stream, dcur + 1u, pidx));
+        dcur += 2;
+        const R sn = (R)2 * sqrt(ua * ((R)1 - ua));
+        R sp, cp;
+        Real<R>::scpi((R)2 * ub, &sp, &cp);
+        ox = sn * cp;
+        oy = sn * sp;
+        iox = ox != (R)0 ? (R)1 / ox : (R)0;
+        ioy = oy != (R)0 ? (R)1 / oy : (R)0;
+        n++;
+        if (n < n_lim) {
+          tau = -log(PointU<R>::u(point_u32n(s_sobol, a.points, stream, dcur, pidx)));
+          dcur++;
+        }
+        ls = LN_RUN;
+      }
+    }
+    if (!__any(ls == LN_RUN)) {  // no lane runs, collides or ends, and no work is left
       if (p_word) to_tally(p_word, p_val);  // the last pending add
       tc_flush();
       break;
     }
-    // this iteration's tally word and value (none for an idle lane)
+    // this iteration's tally word and value (none for a lane that does not run)
     unsigned t_word = 0u;
     unsigned long long t_val = 0ull;
-    if (have) {
-
+    if (ls == LN_RUN) {
       // ---- one segment ----
       const int cell = iy * a.nx + ix;
       const R ss = m_cur.x, sa = m_cur.y, stt = sa + ss;
@@ -583,7 +642,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       trel += l / c;
       seg_p++;
 
-      int end = END_NONE;
+      end = END_NONE;
       if (ev == EV_CENSUS) {
         px += ox * l;
         py += oy * l;
@@ -591,22 +650,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       } else if (ev == EV_COLLIDE) {
         px += ox * l;
         py += oy * l;
-        // isotropic re-emission, scatter counter n <- n + 1
-        const R ua = PointU<R>::u(point_u32n(s_sobol, a.points, stream, dcur, pidx));
-        const R ub = PointU<R>::u(point_u32n(s_sobol, a.points, stream, dcur + 1u, pidx));
-        dcur += 2;
-        const R sn = (R)2 * sqrt(ua * ((R)1 - ua));
-        R sp, cp;
-        Real<R>::scpi((R)2 * ub, &sp, &cp);
-        ox = sn * cp;
-        oy = sn * sp;
-        iox = ox != (R)0 ? (R)1 / ox : (R)0;
-        ioy = oy != (R)0 ? (R)1 / oy : (R)0;
-        n++;
-        if (n < n_lim) {
-          tau = -log(PointU<R>::u(point_u32n(s_sobol, a.points, stream, dcur, pidx)));
-          dcur++;
-        }
+        ls = LN_COL;
       } else if (ev == EV_XFACE) {
         // a reflective side mirrors the direction; the history stays in its cell
         py += oy * l;
@@ -637,23 +681,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       // segment does not include the atomic's round trip
       if (end == END_NONE && ev >= EV_XFACE) m_cur = Real<R>::mat(a, iy * a.nx + ix);
 
-      if (end != END_NONE) {
-        if (KIND == 2 && end == END_CENSUS && a.keep_census) {
-          const long long slot = from_census ? g : a.out_src_base + (g - n_in);
-          Real<R>::stage(bout + slot, px, py, ox, oy, w, hid, iy * a.nx + ix);
-          a.alive[slot] = 1;
-          lane_alive++;
-        }
-        // fold the history's balance into the block (fixed point, exact)
-        const double wend = (double)w;
-        if (!isfinite(wend) || !isfinite(acc_abs) || !isfinite(acc_sca)) lane_bad++;
-        bal_add(my_bal, from_census ? B_CENSUS_IN_W : B_SOURCE_W, w0, inv_W);
-        bal_add(my_bal, B_ABSORBED, acc_abs, inv_W);
-        if (acc_sca != 0.0) bal_add(my_bal, B_SCATTERED, acc_sca, inv_W);
-        bal_add(my_bal, end == END_CENSUS ? B_CENSUS : (end == END_LEAK ? B_LEAKED : B_CUTOFF),
-                wend, inv_W);
-        have = false;
-      }
+      if (end != END_NONE) ls = LN_END;
     }
     // A lane's consecutive adds to one word (segments that end in a
     // collision or at the census stay in their cell) are summed in registers;
@@ -672,7 +700,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
     }
     if (f_word) {
-      const int slot = tc_slot(f_word);
+      const int slot = (int)((f_word * 0x9E3779B1u) >> (32 - kTcBits<R>));
       unsigned tg = tc_tag[slot];
       if (tg == 0u) {
         const unsigned old = atomicCAS(&tc_tag[slot], 0u, f_word);

@@ -52,8 +52,9 @@ constexpr int kSobolDims = 32;
 // shifted Halton set below; dims beyond a set's table and the pseudo-random
 // mode 1 hash (stream, dim, index).  The XOR runs over nibble
 // tables: N[d][p][n] is the XOR of V[d][4p + k] over the set bits k of the
-// 4-bit value n, so a word is the XOR of its index's eight nibble entries
-// (eight lookups instead of a loop over the set bits).  N has kSobolDims x
+// 4-bit value n, so a word is the XOR of its index's nibble entries
+// (a lookup per nibble up to the highest set one: indices count the particles
+// of an emitter, two or three nibbles).  N has kSobolDims x
 // 8 x 16 words, built from V (kSobolDims x 32 words).
 constexpr int kSobolNibbleWords = kSobolDims * 8 * 16;
 
@@ -75,8 +76,7 @@ __device__ __forceinline__ uint32_t sobol_word_nib(const uint32_t* N, uint32_t d
                                                    uint32_t index) {
   const uint32_t* t = N + dim * 128u;
   uint32_t x = 0;
-#pragma unroll
-  for (int pos = 0; pos < 8; ++pos) x ^= t[pos * 16 + ((index >> (4 * pos)) & 15u)];
+  for (; index; index >>= 4, t += 16) x ^= t[index & 15u];  // (the entries of 0 are 0)
   return x;
 }
 
