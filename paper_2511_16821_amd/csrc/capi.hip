@@ -514,7 +514,7 @@ struct slh_solver {
   int* mat_off = nullptr;         // DG table: offset of each cell's material in it
   double* sig_e_mat = nullptr;    // and sigma_e of the materials
   unsigned long long* hand = nullptr;  // traces between a sweep's workgroups
-  double* dg_src = nullptr;       // source of a sweep ([quadrant][mode][slot])
+  double* dg_src = nullptr;       // source of a sweep ([quadrant][slot][mode])
   int n_part = 1;
   void* bank_mem[2] = {nullptr, nullptr};
   void* stage_mem = nullptr;

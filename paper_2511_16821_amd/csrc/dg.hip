@@ -137,8 +137,8 @@ __global__ void k_si_start(DgArgs g, double* __restrict__ bnd0, long long n_bnd,
     for (int q = 0; q < 4; ++q) {
       double2* S = reinterpret_cast<double2*>(g.src) + (long long)q * 2 * n;
       const int pos = dg_slot(g, q, ci, cj);
-      S[pos] = m1;
-      S[n + pos] = m2;
+      S[2 * pos] = m1;
+      S[2 * pos + 1] = m2;
     }
   }
   for (long long k = i0; k < n_bnd; k += str) bnd0[k] = 0.0;
@@ -332,11 +332,11 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
   for (int k = threadIdx.x; k < (SPLIT ? n_waves : g.n_strips); k += blockDim.x) prog[k] = 0;
   __syncthreads();
 
-  const unsigned half = 16u * (unsigned)n;  // bytes of one mode of a source or plane (n < 2^23)
-  const double2* const src = reinterpret_cast<const double2*>(g.src) + (size_t)q * 2 * n;
-  double2* const out = reinterpret_cast<double2*>(g.psi) + (size_t)(q * g.n_grp + grp) * 2 * n;
-  const __amdgpu_buffer_rsrc_t src1 = buffer_of(src, half), src2 = buffer_of(src + n, half);
-  const __amdgpu_buffer_rsrc_t out1 = buffer_of(out, half), out2 = buffer_of(out + n, half);
+  const unsigned bytes = 32u * (unsigned)n;  // of a source or plane (n < 2^23)
+  const __amdgpu_buffer_rsrc_t src =
+      buffer_of(reinterpret_cast<const double2*>(g.src) + (size_t)q * 2 * n, bytes);
+  const __amdgpu_buffer_rsrc_t out = buffer_of(
+      reinterpret_cast<double2*>(g.psi) + (size_t)(q * g.n_grp + grp) * 2 * n, bytes);
   const __amdgpu_buffer_rsrc_t ids =
       TABLE ? buffer_of(g.mat_off + (size_t)q * n, 4u * n) : buffer_of(g.sig_e, 8u * n);
   constexpr double kap = kV1i;  // v1 = -1 + i kap
@@ -382,13 +382,13 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
     int rk[AHEAD];                 // byte offsets of the materials' table rows
     double re[AHEAD];              // sigma_e
     int ro[AHEAD];                 // byte offset of the step's slot row
-    const int row_bytes = 16 * rows, o_begin = 16 * 64 * s * nu, o_end = o_begin + nu * row_bytes;
+    const int row_bytes = 32 * rows, o_begin = 32 * 64 * s * nu, o_end = o_begin + nu * row_bytes;
     int f_t = 0, f_off = o_begin;  // next step to fetch
     auto fetch = [&](int k) __attribute__((always_inline)) {
-      r1[k] = buffer_load2(src1, 16 * lr, f_off);
-      r2[k] = buffer_load2(src2, 16 * lr, f_off);
+      r1[k] = buffer_load2(src, 32 * lr, f_off);
+      r2[k] = buffer_load2(src, 32 * lr + 16, f_off);
       if (TABLE) {
-        rk[k] = (int)__builtin_amdgcn_raw_buffer_load_b32(ids, 4 * lr, f_off >> 2, 0);
+        rk[k] = (int)__builtin_amdgcn_raw_buffer_load_b32(ids, 4 * lr, f_off >> 3, 0);
       } else {
         const int u = f_t - lane;
         const int c = cell0 + (u < 0 ? 0 : (u < nu ? u : nu - 1)) * cell_u;
@@ -554,9 +554,9 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
             acc2.y += w[d] * X2i;
           }
         }
-        const int lane_off = act ? 16 * lane : kNoCell;
-        buffer_store2<SPLIT>(out1, lane_off, ro[k], acc1.x, acc1.y);
-        buffer_store2<SPLIT>(out2, lane_off, ro[k], acc2.x, acc2.y);
+        const int lane_off = act ? 32 * lane : kNoCell;
+        buffer_store2<SPLIT>(out, lane_off, ro[k], acc1.x, acc1.y);
+        buffer_store2<SPLIT>(out, lane_off + 16, ro[k], acc2.x, acc2.y);
 #pragma unroll
         for (int d = 0; d < PER; ++d) leave_at[d] = make_double2(uyr[d], uyi[d]);
         leave_at += leave_by;
@@ -731,11 +731,13 @@ size_t dg_hand_words(const DgPlan& p) {
 // diffusion correction the combine keeps phi_new - phi_old in dnode instead
 // and leaves the source and the residual to k_dsa_apply.  The last block of a
 // grid to leave its partials takes the iteration's decision.
-constexpr int kRedWaves = 4;  // a wave per quadrant
+constexpr int kTile = 8;                  // cells of a tile's side
+constexpr int kRedCells = kTile * kTile;  // one wave per quadrant
+constexpr int kRedWaves = 4;
 constexpr int kRedBlock = 64 * kRedWaves;
 
 int dg_reduce_partials(int nx, int ny) {
-  const long long tiles = (long long)((nx + 7) / 8) * ((ny + 7) / 8);
+  const long long tiles = (long long)((nx + kTile - 1) / kTile) * ((ny + kTile - 1) / kTile);
   return (int)(tiles < 1024 ? tiles : 1024);
 }
 
@@ -825,11 +827,10 @@ __device__ __forceinline__ void add_norms(double4 v, double4 d, double r, double
 // quadrant's planes at the lane's cell, the four nodal sums meet in LDS, and
 // after the cells' update (wave 0) it forms the quadrant's next source.  The
 // cells of a slot row lie on a diagonal of the mesh, so a wave takes its tile
-// along the diagonals of its quadrant: eight lanes then read, and write, one
-// cache line (cells in row-major order took a line for every lane: 75 us a
-// reduction against 18 us, 140x140, S_12).
-constexpr int kTile = 8;
-constexpr int kRedCells = kTile * kTile;
+// along the diagonals of its quadrant: eight lanes then read, and write, two
+// whole cache lines (140x140, S_12: 29 us a reduction; cells in row-major order,
+// a line for every lane, 75 us; the two modes in arrays of their own, one line
+// for eight lanes, 40 us; tiles of 16 x 16, 33 us).
 constexpr int kNodeRow = kRedCells + 1;  // LDS stride of a node: [node][cell]
 
 // Tiles of the mesh, and tile cell of lane l in quadrant q: column (d - e) mod
@@ -841,7 +842,7 @@ struct TileCell {
 };
 __device__ __forceinline__ TileCell tile_cell(const DgArgs& g, int tile, int q, int lane) {
   const int tx = (g.nx + kTile - 1) / kTile;
-  const int e = lane & 7, d = lane >> 3, f = (d - e) & 7;
+  const int e = lane % kTile, d = lane / kTile, f = (d - e) & (kTile - 1);
   const int x = g.swap ? e : f, y = g.swap ? f : e;
   const int i = (q & 1) ? kTile - 1 - x : x, j = (q & 2) ? kTile - 1 - y : y;
   const int ci = tile % tx * kTile + i, cj = tile / tx * kTile + j;
@@ -869,8 +870,8 @@ __device__ __forceinline__ void put_source(const DgArgs& g, int q, const TileCel
            s_src[quad_node(q, g.swap, 1, 0) * kNodeRow + t.at],
            s_src[quad_node(q, g.swap, 1, 1) * kNodeRow + t.at], m1, m2);
   double2* const S = reinterpret_cast<double2*>(g.src) + (size_t)q * 2 * n;
-  S[t.slot] = m1;
-  S[n + t.slot] = m2;
+  S[2 * t.slot] = m1;
+  S[2 * t.slot + 1] = m2;
 }
 
 // Nodal source of a cell into LDS (wave 0).
@@ -902,6 +903,17 @@ __global__ __launch_bounds__(kRedBlock) void k_dg_combine(DgArgs g, double* part
   double dsum = 0.0, nsum = 0.0;
   for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const TileCell t = tile_cell(g, tile, q, lane);
+    // wave 0: the cell's data for the update, in flight with the planes
+    double4 o = make_double4(0.0, 0.0, 0.0, 0.0);
+    double ssc = 0.0, pp = 0.0, pre = 0.0;
+    if (q == 0) {
+      o = reinterpret_cast<const double4*>(g.phi_c)[t.cell];
+      if (!g.dnode) {
+        ssc = g.sig_s[t.cell];
+        pp = g.phi_post[t.cell];
+        if (g.phi_pre) pre = g.phi_pre[t.cell];
+      }
+    }
     double2 m1 = make_double2(0.0, 0.0), m2 = m1;
     auto add = [&](int u, double2 t1, double2 t2) __attribute__((always_inline)) {
       const double w = g.per == 1 ? dir[3 * u + 2] : 1.0;
@@ -915,8 +927,8 @@ __global__ __launch_bounds__(kRedBlock) void k_dg_combine(DgArgs g, double* part
       double2 t1[8], t2[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        t1[e] = plane[(size_t)(u + e) * 2 * n + t.slot];
-        t2[e] = plane[(size_t)(u + e) * 2 * n + n + t.slot];
+        t1[e] = plane[((size_t)(u + e) * n + t.slot) * 2];
+        t2[e] = plane[((size_t)(u + e) * n + t.slot) * 2 + 1];
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e) add(u + e, t1[e], t2[e]);
@@ -926,8 +938,8 @@ __global__ __launch_bounds__(kRedBlock) void k_dg_combine(DgArgs g, double* part
 #pragma unroll
       for (int e = 0; e < 7; ++e) {
         const int v = u + e < g.n_grp ? u + e : g.n_grp - 1;
-        t1[e] = plane[(size_t)v * 2 * n + t.slot];
-        t2[e] = plane[(size_t)v * 2 * n + n + t.slot];
+        t1[e] = plane[((size_t)v * n + t.slot) * 2];
+        t2[e] = plane[((size_t)v * n + t.slot) * 2 + 1];
       }
 #pragma unroll
       for (int e = 0; e < 7; ++e)
@@ -943,19 +955,17 @@ __global__ __launch_bounds__(kRedBlock) void k_dg_combine(DgArgs g, double* part
       double f[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const int o = k * kNodeRow + t.at;
-        f[k] = (s_phi[0][o] + s_phi[3][o]) + (s_phi[1][o] + s_phi[2][o]);
+        const int at = k * kNodeRow + t.at;
+        f[k] = (s_phi[0][at] + s_phi[3][at]) + (s_phi[1][at] + s_phi[2][at]);
       }
       const double4 v = make_double4(f[0], f[1], f[2], f[3]);
-      const double4 o = reinterpret_cast<const double4*>(g.phi_c)[t.cell];
       const double4 d = make_double4(v.x - o.x, v.y - o.y, v.z - o.z, v.w - o.w);
       reinterpret_cast<double4*>(g.phi_c)[t.cell] = v;
       if (g.dnode) {  // the correction, the source and the residual come later
         reinterpret_cast<double4*>(g.dnode)[t.cell] = d;
       } else {
-        const double pp = g.phi_post[t.cell];
-        nodal_source(s_src, t.at, g.sig_s[t.cell] * inv4pi, v, pp);
-        add_norms(v, d, g.phi_pre ? g.phi_pre[t.cell] + pp : 0.0, dsum, nsum);
+        nodal_source(s_src, t.at, ssc * inv4pi, v, pp);
+        add_norms(v, d, g.phi_pre ? pre + pp : 0.0, dsum, nsum);
       }
     }
     __syncthreads();

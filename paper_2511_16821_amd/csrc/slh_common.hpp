@@ -481,10 +481,10 @@ struct DgArgs : DgPlan {
                          // over phi_c alone, else over phi_c + phi_pre + phi_post
   double* phi_c;         // nodal [cell][4] (row-major): the collided iterate, updated in place
   double* src;           // sigma_s/(4 pi)(phi_c + phi_post) as coefficients of the
-                         // element's modes: [quadrant][mode][slot], complex
+                         // element's modes: [quadrant][slot][mode], complex
   double* psi;           // psi_m of each direction (one per group) or sums of w_m
                          // psi_m over the directions of a group, as coefficients:
-                         // [quadrant][group][mode][slot], complex
+                         // [quadrant][group][slot][mode], complex
   double* dnode;         // nodal phi^{k+1/2} - phi^k (row-major) for the diffusion
                          // correction (diffusion synthetic acceleration), or null
   // with a table: byte offset of each cell's material in it (32 bytes each),
