@@ -363,8 +363,8 @@ static Sizes sizes_of(const slh_problem* p) {
   b += (size_t)z.n_cand * ((z.fp32 ? 32 : 64) + 1 + 4);  // staging, alive, kept cells
   b += (size_t)census_tiles(z.n_cand) * 16;          // tile counts and their scan
   b += std::max(scan_tmp_elems(census_tiles(z.n_cand)),
-                scan_tmp_elems((long long)radix_hist_elems(z.cap))) * 8;
-  b += (size_t)z.cap * 4 * 6 + radix_hist_elems(z.cap) * 16 + nc * 4;  // census ordering
+                scan_tmp_elems((long long)radix_hist_elems(z.cap, z.n_cells))) * 8;
+  b += (size_t)z.cap * 4 * 6 + radix_hist_elems(z.cap, z.n_cells) * 8 + nc * 4;  // census ordering
   b += sizeof(DevState) + 32 * 32 * 4 + 64 * 8 + kCensusBlocks * 8;
   b += 64 * 1024;  // alignment of the ~30 device buffers
   z.bytes = b;
@@ -525,7 +525,7 @@ struct slh_solver {
   // census ordering: (cell, slot) pairs and their sort buffers, the radix
   // histograms, cohort starts per cell, and each bank's cohort ranks
   uint32_t *skey[2] = {nullptr, nullptr}, *sval[2] = {nullptr, nullptr};
-  long long *rhist = nullptr, *rincl = nullptr;
+  uint32_t *rhist = nullptr, *rincl = nullptr;
   uint32_t* cstart = nullptr;
   uint32_t* crank[2] = {nullptr, nullptr};
   uint32_t* sobol = nullptr;
@@ -614,6 +614,21 @@ struct slh_solver {
   }
 };
 
+// The boundary faces of the inflow as emitters after the cells: face f's
+// majorant is (pi L_f) tdt pow2_ceil(|G_f|), the partial current pi G of an
+// isotropic inflow over the face and the step (tdt = 1 in steady state).
+static Emitters emitters(const slh_solver* s) {
+  Emitters e;
+  e.inflow = s->inflow;
+  e.nx = s->prob.nx;
+  e.ny = s->prob.ny;
+  e.n_faces = s->z.n_faces;
+  const double tdt = s->prob.steady ? 1.0 : s->prob.dt;
+  e.cx = (M_PI * s->hy) * tdt;
+  e.cy = (M_PI * s->hx) * tdt;
+  return e;
+}
+
 static slh_status setup(slh_solver* s) {
   const slh_problem& p = s->prob;
   const Sizes& z = s->z;
@@ -700,14 +715,14 @@ static slh_status setup(slh_solver* s) {
   ALLOC(s->tcount, long long, census_tiles(z.n_cand));
   ALLOC(s->tincl, long long, census_tiles(z.n_cand));
   ALLOC(s->scan_i, long long, std::max(scan_tmp_elems(census_tiles(z.n_cand)),
-                                      scan_tmp_elems((long long)radix_hist_elems(z.cap))));
+                                      scan_tmp_elems((long long)radix_hist_elems(z.cap, z.n_cells))));
   for (int k = 0; k < 2; ++k) {
     ALLOC(s->skey[k], uint32_t, z.cap);
     ALLOC(s->sval[k], uint32_t, z.cap);
     ALLOC(s->crank[k], uint32_t, z.cap);
   }
-  ALLOC(s->rhist, long long, radix_hist_elems(z.cap));
-  ALLOC(s->rincl, long long, radix_hist_elems(z.cap));
+  ALLOC(s->rhist, uint32_t, radix_hist_elems(z.cap, z.n_cells));
+  ALLOC(s->rincl, uint32_t, radix_hist_elems(z.cap, z.n_cells));
   ALLOC(s->cstart, uint32_t, nc);
   ALLOC(s->sobol, uint32_t, 32 * 32);
   ALLOC(s->st, DevState, 1);
@@ -807,6 +822,8 @@ static slh_status setup(slh_solver* s) {
   HIP_TRY(launch_fill_f64(s->ctree1, 2 * s->tree_L, 0.0, st));
   HIP_TRY(launch_fill_f64(s->ctreeR, 2 * s->tree_L, 0.0, st));
   hipLaunchKernelGGL(k_state_init, dim3(1), dim3(1), 0, st, s->st);
+  // the first pass's source is the same in every step: so are its sum and w_q
+  HIP_TRY(launch_majorant_sum(s->qn1, nc, emitters(s), s->adt, z.n_p, 1, s->maj_hist, s->st, st));
   HIP_TRY(launch_fill_f64(s->phi_c, 4 * nc, 0.0, st));
   if (s->hand) HIP_TRY(launch_fill_u64(s->hand, (long long)dg_hand_words(z.dg), 0ull, st));
   HIP_TRY(launch_fill_f64(s->phi_pre, nc, 0.0, st));
@@ -816,21 +833,6 @@ static slh_status setup(slh_solver* s) {
   HIP_TRY(launch_fill_u8(s->alive, z.n_cand, 0, st));
   HIP_TRY(hipStreamSynchronize(st));  // host vectors above go out of scope
   return SLH_OK;
-}
-
-// The boundary faces of the inflow as emitters after the cells: face f's
-// majorant is (pi L_f) tdt pow2_ceil(|G_f|), the partial current pi G of an
-// isotropic inflow over the face and the step (tdt = 1 in steady state).
-static Emitters emitters(const slh_solver* s) {
-  Emitters e;
-  e.inflow = s->inflow;
-  e.nx = s->prob.nx;
-  e.ny = s->prob.ny;
-  e.n_faces = s->z.n_faces;
-  const double tdt = s->prob.steady ? 1.0 : s->prob.dt;
-  e.cx = (M_PI * s->hy) * tdt;
-  e.cy = (M_PI * s->hx) * tdt;
-  return e;
 }
 
 static PassArgs pass_args(slh_solver* s, int kind) {
@@ -1019,9 +1021,8 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
   const int n_it = s->skip_remap ? 0 : s->batch_run;
   switch (part) {
     case kA: {
-      HIP_TRY(launch_emission_plan(s->qn1, nc, emitters(s), s->adt, z.n_p, p.seed, p.points, 1,
-                                   s->maj_hist,
-                                   s->ctree1, s->st, st));
+      HIP_TRY(launch_emission_counts(s->qn1, nc, emitters(s), s->adt, p.seed, p.points, 1,
+                                     s->ctree1, s->st, st));
       HIP_TRY(launch_pass_prep(s->st, s->ctree1, 1, z.n_src_cap, cdt, s->Tpre, n_tally, s->Tpost,
                                n_tally, nullptr, 0, st));
       HIP_TRY(launch_emit(pass_args(s, 1), z.fp32, st));
@@ -1054,9 +1055,10 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
       if (use_cg(s)) HIP_TRY(launch_cg_to_nodal(cg_args(s), s->phi_c, &s->st->halt, st));
       HIP_TRY(launch_remap_source(nc, s->q, s->sig_s, s->phi_pre, s->phi_post, s->phi_c,
                                   s->qnR, &s->st->halt, st));
-      HIP_TRY(launch_emission_plan(s->qnR, nc, emitters(s), s->adt, z.n_p, p.seed, p.points, 2,
-                                   s->maj_hist,
-                                   s->ctreeR, s->st, st));
+      HIP_TRY(launch_majorant_sum(s->qnR, nc, emitters(s), s->adt, z.n_p, 2, s->maj_hist, s->st,
+                                  st));
+      HIP_TRY(launch_emission_counts(s->qnR, nc, emitters(s), s->adt, p.seed, p.points, 2,
+                                     s->ctreeR, s->st, st));
       HIP_TRY(launch_pass_prep(s->st, s->ctreeR, 2, z.n_src_cap, cdt, s->TR, n_tally, nullptr, 0,
                                s->alive, z.n_cand, st));
       HIP_TRY(launch_emit(pass_args(s, 2), z.fp32, st));
@@ -1088,7 +1090,7 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
       HIP_TRY(launch_census_keys(s->kcell, s->alive, s->tcount, s->tincl, z.n_cand, z.cap,
                                  s->skey[0], s->sval[0], s->st, st));
       HIP_TRY(radix_sort_pairs(s->skey[0], s->sval[0], s->skey[1], s->sval[1], last, z.cap, nc,
-                               s->rhist, s->rincl, s->scan_i, s->st, st));
+                               s->rhist, s->rincl, (uint32_t*)s->scan_i, s->st, st));
       if (z.fp32)
         HIP_TRY(launch_census_gather<float>((const StageRec<float>*)s->stage_mem, s->sval[odd],
                                             last, z.cap, (StageRec<float>*)nb, s->st, s->cmax,
@@ -1098,8 +1100,9 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
                                              s->sval[odd], last, z.cap, (StageRec<double>*)nb,
                                              s->st, s->cmax, st));
       HIP_TRY(launch_census_finish(s->st, s->tincl, tiles, z.cap, s->cmax, st));
-      HIP_TRY(launch_cohort_ranks(s->skey[odd], &s->st->n_in, z.cap, s->cstart,
-                                  s->crank[1 - s->cur], s->st, st));
+      if (p.census_qmc)  // (a history's own stream takes no rank)
+        HIP_TRY(launch_cohort_ranks(s->skey[odd], &s->st->n_in, z.cap, s->cstart,
+                                    s->crank[1 - s->cur], s->st, st));
       return SLH_OK;
     }
   }

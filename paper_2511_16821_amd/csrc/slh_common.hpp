@@ -611,30 +611,34 @@ hipError_t launch_remap_source(long long n, const double* q, const double* sig_s
                                const double* phi_c, double* qn, const int* halt,
                                hipStream_t s);
 long long tree_leaves(long long n_cells);
-// Emission plan of a pass (the counts of the stratified emission): histogram
-// of the cell majorants M_i = adt pow2_ceil(max corner |q_i|) by exponent,
-// their exact sum rounded once to FP64 (st->sumM[kind - 1]), the weight
-// quantum w_q (st->wq[kind - 1]), the counts
-// n_i = floor(M_i / w_q) + [u_i < frac(M_i / w_q)] with u_i point 0 of the
-// cell's count stream, and the count tree over them (root: particles).
-// hist: kMajBins words, zero on entry and left zero (the last bin counts
-// cells whose majorant is not finite).
+// Emission plan of a pass (the counts of the stratified emission).
+// launch_majorant_sum: histogram of the cell majorants M_i = adt pow2_ceil(max
+// corner |q_i|) by exponent, their exact sum rounded once to FP64
+// (st->sumM[kind - 1]) and the weight quantum w_q (st->wq[kind - 1]); for the
+// first pass, whose source is the problem's, once for all steps.
+// launch_emission_counts: the step's counts n_i = floor(M_i / w_q) + [u_i <
+// frac(M_i / w_q)] with u_i point 0 of the cell's count stream, and the count
+// tree over them (root: particles).
+// hist: kMajGroups kMajBins words (cells, x faces, y faces), zero on entry and
+// left zero (the last bin of a group counts majorants that are not finite).
 constexpr int kMajBins = 2112;
-hipError_t launch_emission_plan(const double* qn, long long n_cells, const Emitters& em,
-                                double adt, long long n_src, uint64_t seed, int points, int kind,
-                                unsigned long long* hist, double* ctree, DevState* st,
-                                hipStream_t s);
-// hist: kMajHistWords words (cells, x faces, y faces)
+hipError_t launch_majorant_sum(const double* qn, long long n_cells, const Emitters& em,
+                               double adt, long long n_src, int kind, unsigned long long* hist,
+                               DevState* st, hipStream_t s);
+hipError_t launch_emission_counts(const double* qn, long long n_cells, const Emitters& em,
+                                  double adt, uint64_t seed, int points, int kind, double* ctree,
+                                  DevState* st, hipStream_t s);
 constexpr int kMajGroups = 3;
 size_t scan_tmp_elems(long long n);
 hipError_t scan_inclusive_i64(const long long* in, long long* out, long long n,
                               long long* tmp, const int* halt, hipStream_t s);
+hipError_t scan_inclusive_u32(const uint32_t* in, uint32_t* out, long long n, uint32_t* tmp,
+                              const int* halt, hipStream_t s);
 hipError_t launch_thin_params(DevState* st, long long cap, long long margin, hipStream_t s);
-// Census candidates are processed in tiles of kKeepTile slots.
+// Census candidates are processed in tiles of slots.
 // launch_census_keep: each candidate's keep decision (alive and, with the cap
 // active, its key test), stored in place of its alive byte, and the kept
 // count of each tile (tcount, census_tiles(n) entries).
-constexpr int kKeepTile = 4096;
 long long census_tiles(long long n);
 // It also copies each kept candidate's cell into cell (n entries; 0 for the
 // others), read by the ordering keys in place of the records.
@@ -651,12 +655,13 @@ hipError_t launch_census_keep(uint8_t* alive, const StageRec<R>* stage, long lon
 hipError_t launch_census_keys(const int32_t* cell, const uint8_t* keep, const long long* tcount,
                               const long long* tincl, long long n, long long cap, uint32_t* keys,
                               uint32_t* vals, const DevState* st, hipStream_t s);
-long long radix_tiles(long long n);
 int radix_passes(long long n_keys_max);
-size_t radix_hist_elems(long long cap);
+// 32-bit histogram entries of a sort of up to cap pairs with keys below
+// n_keys_max (counts and positions stay below 2^32)
+size_t radix_hist_elems(long long cap, long long n_keys_max);
 hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
                             const long long* incl_last, long long cap, long long key_bound,
-                            long long* hist, long long* hincl, long long* scan_tmp,
+                            uint32_t* hist, uint32_t* hincl, uint32_t* scan_tmp,
                             const DevState* st, hipStream_t s);
 template <typename R>
 hipError_t launch_census_gather(const StageRec<R>* src, const uint32_t* vals,

@@ -207,49 +207,8 @@ __device__ __forceinline__ int maj_bin(double p) {
   return b < 0 ? 0 : (b >= kMajBad ? kMajBad : b);
 }
 
-// Block histogram in LDS, then one global add per non-empty bin and block.
-__global__ __launch_bounds__(256) void k_maj_hist(const double* __restrict__ qn, long long n,
-                                                  unsigned long long* __restrict__ hist,
-                                                  const int* halt) {
-  if (*halt) return;
-  __shared__ unsigned int s_h[kMajBins];
-  for (int k = threadIdx.x; k < kMajBins; k += blockDim.x) s_h[k] = 0u;
-  __syncthreads();
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const double p = cell_majorant_pow2(reinterpret_cast<const double4*>(qn)[i]);
-    if (p > 0.0) atomicAdd(&s_h[maj_bin(p)], 1u);
-  }
-  __syncthreads();
-  for (int k = threadIdx.x; k < kMajBins; k += blockDim.x)
-    if (s_h[k]) atomicAdd(&hist[k], (unsigned long long)s_h[k]);
-}
-
-// The faces of an inflow: one global add per face to the x-face (group 1)
-// or y-face (group 2) histogram.
-__global__ void k_face_hist(Emitters em, unsigned long long* __restrict__ hist, const int* halt) {
-  if (*halt) return;
-  for (long long f = (long long)blockIdx.x * blockDim.x + threadIdx.x; f < em.n_faces;
-       f += (long long)gridDim.x * blockDim.x) {
-    int k;
-    const int side = face_side((int)f, em.nx, em.ny, &k);
-    const double p = pow2_ceil(fabs(em.inflow[f]));
-    if (p > 0.0) atomicAdd(&hist[(side < 2 ? 1 : 2) * kMajBins + maj_bin(p)], 1ull);
-  }
-}
-
 constexpr int kSumLimbs = 36;  // 2304 bits above 2^-1074
-
-// Bits [r, r + 64) of the 128-bit value (hi, lo), zero outside it.
-__device__ __forceinline__ unsigned long long bits128(unsigned long long lo, unsigned long long hi,
-                                                      int r) {
-  if (r <= -64 || r >= 128) return 0ull;
-  if (r < 0) return lo << (-r);
-  if (r == 0) return lo;
-  if (r < 64) return (lo >> r) | (hi << (64 - r));
-  if (r == 64) return hi;
-  return hi >> (r - 64);
-}
+constexpr int kSumWords = 2 * kSumLimbs;
 
 // bits [b, b + n) of the accumulator (n <= 64, b >= 0)
 __device__ __forceinline__ unsigned long long limbs_bits(const unsigned long long* acc, int b,
@@ -260,124 +219,143 @@ __device__ __forceinline__ unsigned long long limbs_bits(const unsigned long lon
   return n == 64 ? v : (v & ((1ull << n) - 1ull));
 }
 
-// The exact sum of the histogram, rounded once; w_q; and the histogram
-// cleared for the next plan.  The block copies and clears the histogram and
-// lists its non-empty bins (in any order: the sum below is exact integer
-// arithmetic); then one wave sums them.  Lane k < kSumLimbs owns 64-bit limb
-// k of the sum (bit 0 = 2^-1074): every listed bin's term c_b mant_b 2^pos_b
-// adds its bits that fall in the limb, and the limb counts its own
-// overflows; lane 0 then propagates the carries and rounds.
-constexpr int kMajSumThreads = 256;
-__global__ __launch_bounds__(kMajSumThreads) void k_maj_sum(unsigned long long* __restrict__ hist,
-                                                            double adt, double cx, double cy,
-                                                            long long n_src, int kind,
-                                                            DevState* st) {
+// The exact sum of a plan's majorants, rounded once, and w_q.  Every
+// emitter's power-of-two majorant goes to its block's histogram in LDS (cells;
+// then the faces of an inflow, an x-face and a y-face histogram), and each
+// non-empty bin of a block to the global one.  The last block of the grid to
+// have done so copies and clears the histogram (it is zero between plans) and
+// adds up its bins: a bin's term c_b mant_b 2^pos_b, one thread each, goes in
+// pieces of 32 bits to the 64-bit words of an accumulator in LDS (bit 0 =
+// 2^-1074; at most 6336 pieces to a word: no overflow); then the carries are
+// propagated and the sum is rounded.  (As a launch of its own in which one wave
+// walked the bins, each lane owning a limb, the sum took 13 us on a 20x20
+// mesh, 42 us on 140x140 and 120 us where the remap source of a thick medium
+// spreads over 200 bins.)
+constexpr int kMajThreads = 256;
+__global__ __launch_bounds__(kMajThreads) void k_maj_sum(const double* __restrict__ qn,
+                                                         long long n, Emitters em,
+                                                         unsigned long long* __restrict__ hist,
+                                                         double adt, long long n_src, int kind,
+                                                         DevState* st) {
   if (st->halt) return;
-  __shared__ unsigned long long s_h[kMajGroups * kMajBins];
-  __shared__ unsigned short s_list[kMajGroups * kMajBins];
-  __shared__ unsigned long long s_limb[kSumLimbs], s_carry[kSumLimbs];
-  __shared__ int s_n, s_bad, s_ovf;
-  const int lane = threadIdx.x;
-  if (lane == 0) {
-    s_n = 0;
+  __shared__ unsigned int s_h[kMajGroups * kMajBins];
+  __shared__ unsigned long long s_word[kSumWords];
+  __shared__ unsigned long long s_limb[kSumLimbs];
+  __shared__ int s_last, s_bad, s_top, s_low;
+  const int t = threadIdx.x;
+  const int n_bins = em.n_faces > 0 ? kMajGroups * kMajBins : kMajBins;
+  for (int k = t; k < n_bins; k += kMajThreads) s_h[k] = 0u;
+  if (t < kSumWords) s_word[t] = 0ull;
+  if (t == 0) {
     s_bad = 0;
-    s_ovf = 0;
+    s_top = -1;
+    s_low = kSumWords;
   }
   __syncthreads();
-  constexpr int kN = kMajGroups * kMajBins;
-  constexpr int kPer = (kN + kMajSumThreads - 1) / kMajSumThreads;
-  unsigned long long v[kPer];  // every load in flight before the first use
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int k = lane + j * kMajSumThreads;
-    v[j] = k < kN ? hist[k] : 0ull;
-  }
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int k = lane + j * kMajSumThreads;
-    if (k >= kN) continue;
-    hist[k] = 0ull;
-    s_h[k] = v[j];
-    if (v[j]) {
-      if (k % kMajBins == kMajBad) s_bad = 1;
-      else s_list[atomicAdd(&s_n, 1)] = (unsigned short)k;
+  for (long long i = (long long)blockIdx.x * kMajThreads + t; i < n + em.n_faces;
+       i += (long long)gridDim.x * kMajThreads) {
+    if (i < n) {
+      const double p = cell_majorant_pow2(reinterpret_cast<const double4*>(qn)[i]);
+      if (p > 0.0) atomicAdd(&s_h[maj_bin(p)], 1u);
+    } else {
+      int k;
+      const int side = face_side((int)(i - n), em.nx, em.ny, &k);
+      const double p = pow2_ceil(fabs(em.inflow[i - n]));
+      if (p > 0.0) atomicAdd(&s_h[(side < 2 ? 1 : 2) * kMajBins + maj_bin(p)], 1u);
     }
   }
   __syncthreads();
-  if (s_bad) {
-    // a majorant overflowed: no emission (flagged by the pass set-up)
-    if (lane == 0) {
-      st->sumM[kind - 1] = __builtin_huge_val();
-      st->wq[kind - 1] = 0.0;
-    }
-    return;
+  for (int k = t; k < n_bins; k += kMajThreads)
+    if (s_h[k]) atomicAdd(&hist[k], (unsigned long long)s_h[k]);
+  // this wave's adds have reached memory before the block counts itself
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (t == 0) {
+    const unsigned before = __hip_atomic_fetch_add(&st->red_blocks, 1u, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    s_last = before == gridDim.x - 1;
   }
-  const int n_list = s_n;
-  unsigned long long acc = 0ull, carry = 0ull;
-  bool overflow = false;
-  // every emitter group (cells, x faces, y faces): the value of each of its
-  // majorants in bin b is its constant times 2^(b - 1074)
-  for (int i = 0; lane < 64 && i < n_list && !overflow; ++i) {
-    const int gb = s_list[i];
+  __syncthreads();
+  if (!s_last) return;
+  if (t == 0) st->red_blocks = 0u;
+  for (int gb = t; gb < n_bins; gb += kMajThreads) {
+    const unsigned long long c =
+        __hip_atomic_load(&hist[gb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!c) continue;
+    hist[gb] = 0ull;
     const int g = gb / kMajBins, b = gb - g * kMajBins;
-    const unsigned long long c = s_h[gb];  // the same in every lane
-    const double V = (g == 0 ? adt : g == 1 ? cx : cy) * ldexp(1.0, b - 1074);
+    if (b == kMajBad) {
+      s_bad = 1;
+      continue;
+    }
+    // the value of the group's majorants in bin b: its constant times 2^(b - 1074)
+    const double V = (g == 0 ? adt : g == 1 ? em.cx : em.cy) * ldexp(1.0, b - 1074);
     if (!(V > 0.0)) continue;
     if (!isfinite(V)) {
-      overflow = true;
-      break;
+      s_bad = 1;
+      continue;
     }
-    int e;
-    const double m = frexp(V, &e);  // V = m 2^e, m in [1/2, 1)
+    int ex;
+    const double m = frexp(V, &ex);  // V = m 2^ex, m in [1/2, 1)
     unsigned long long mant = (unsigned long long)ldexp(m, 53);
-    int pos = e - 53 + 1074;        // V = mant 2^(pos - 1074)
-    if (pos < 0) {                  // subnormal V: its low bits are zero
+    int pos = ex - 53 + 1074;        // V = mant 2^(pos - 1074)
+    if (pos < 0) {                   // subnormal V: its low bits are zero
       mant >>= -pos;
       pos = 0;
     }
+    // c mant 2^(pos mod 32) in four words of 32 bits (c < 2^31, so below 2^116)
+    const int w0 = pos >> 5, sh = pos & 31;
     const unsigned long long lo = c * mant, hi = __umul64hi(c, mant);
-    const unsigned long long add = bits128(lo, hi, 64 * lane - pos);
-    acc += add;
-    carry += acc < add ? 1ull : 0ull;
-  }
-  if (lane == 0 && overflow) s_ovf = 1;  // the same in every lane of the wave
-  if (lane < kSumLimbs) {
-    s_limb[lane] = acc;
-    s_carry[lane] = carry;
+    const unsigned long long a0 = lo << sh;
+    const unsigned long long a1 = (hi << sh) | (sh ? lo >> (64 - sh) : 0ull);
+    const unsigned long long part[4] = {a0 & 0xffffffffull, a0 >> 32, a1 & 0xffffffffull,
+                                        a1 >> 32};
+    for (int k = 0; k < 4; ++k)
+      if (part[k]) atomicAdd(&s_word[w0 + k], part[k]);
+    atomicMin(&s_low, w0);
+    atomicMax(&s_top, w0 + 3);
   }
   __syncthreads();
-  if (lane != 0) return;
-  if (s_ovf) {
+  if (t != 0) {
+    return;
+  }
+  if (s_bad) {
+    // a majorant overflowed: no emission (flagged by the pass set-up)
     st->sumM[kind - 1] = __builtin_huge_val();
     st->wq[kind - 1] = 0.0;
     return;
   }
-  unsigned long long cin = 0ull;
-  for (int k = 0; k < kSumLimbs; ++k) {  // carries of limb k go to limb k + 1
-    const unsigned long long v = s_limb[k] + cin;
-    cin = (v < cin ? 1ull : 0ull) + s_carry[k];
-    s_limb[k] = v;
-  }
-  const unsigned long long* L = s_limb;
-  int top = -1;
-  for (int k = kSumLimbs - 1; k >= 0 && top < 0; --k)
-    if (L[k]) top = 64 * k + 63 - __clzll((long long)L[k]);
   double sum = 0.0;
-  if (top >= 0 && top < 53) {
-    sum = ldexp((double)L[0], -1074);  // fewer than 53 bits: exact
-  } else if (top >= 53) {
-    unsigned long long mant = limbs_bits(L, top - 52, 53);
-    const unsigned long long rnd = limbs_bits(L, top - 53, 1);
-    bool sticky = false;
-    const int below = top - 53;  // bits [0, below) decide a tie
-    for (int k = 0; k < (below >> 6) && !sticky; ++k) sticky = L[k] != 0ull;
-    if (!sticky && (below & 63)) sticky = limbs_bits(L, below & ~63, below & 63) != 0ull;
-    int ex = top - 52 - 1074;
-    if (rnd && (sticky || (mant & 1ull))) {
-      mant += 1ull;
-      if (mant == (1ull << 53)) { mant >>= 1; ex += 1; }
+  if (s_top >= 0) {
+    // carries, from the lowest word with a term to two above the highest
+    const int end = s_top + 2 < kSumWords - 1 ? s_top + 2 : kSumWords - 1;
+    unsigned long long carry = 0ull;
+    int top = -1;
+    for (int k = 0; k < kSumLimbs; ++k) s_limb[k] = 0ull;
+    for (int k = s_low; k <= end; ++k) {
+      const unsigned long long v = s_word[k] + carry;
+      carry = v >> 32;
+      const unsigned long long w = v & 0xffffffffull;
+      s_limb[k >> 1] |= w << (32 * (k & 1));
+      if (w) top = 32 * k + 63 - __clzll((long long)w);
     }
-    sum = ldexp((double)mant, ex);
+    const unsigned long long* L = s_limb;
+    if (top < 53) {
+      sum = ldexp((double)L[0], -1074);  // fewer than 53 bits: exact
+    } else {
+      unsigned long long mant = limbs_bits(L, top - 52, 53);
+      const unsigned long long rnd = limbs_bits(L, top - 53, 1);
+      bool sticky = false;
+      const int below = top - 53;  // bits [0, below) decide a tie
+      for (int k = s_low >> 1; k < (below >> 6) && !sticky; ++k) sticky = L[k] != 0ull;
+      if (!sticky && (below & 63)) sticky = limbs_bits(L, below & ~63, below & 63) != 0ull;
+      int ex = top - 52 - 1074;
+      if (rnd && (sticky || (mant & 1ull))) {
+        mant += 1ull;
+        if (mant == (1ull << 53)) { mant >>= 1; ex += 1; }
+      }
+      sum = ldexp((double)mant, ex);
+    }
   }
   st->sumM[kind - 1] = sum;
   st->wq[kind - 1] = (sum > 0.0 && isfinite(sum) && n_src > 0) ? quantum5(sum / (double)n_src)
@@ -387,15 +365,10 @@ __global__ __launch_bounds__(kMajSumThreads) void k_maj_sum(unsigned long long* 
 constexpr int kTreeChunk = 1024;
 
 // Level of width W (nodes W..2W-1): block b sums nodes [W + b C, W + (b+1) C)
-// with C = min(W, 1024) up through log2(C) levels.  Leaves are integers, so
-// every sum is exact.
-__global__ __launch_bounds__(512) void k_tree_up(double* t, long long W, const int* halt) {
-  if (*halt) return;
-  __shared__ double buf[2][kTreeChunk];
-  const long long C = W < kTreeChunk ? W : kTreeChunk;
-  const long long base = W + (long long)blockIdx.x * C;
-  for (int j = threadIdx.x; j < C; j += blockDim.x) buf[0][j] = t[base + j];
-  __syncthreads();
+// with C = min(W, 1024) up through log2(C) levels; buf[0] holds the block's
+// nodes.  Leaves are integers, so every sum is exact.
+__device__ __forceinline__ void tree_up(double* t, long long W, int C,
+                                        double (*buf)[kTreeChunk]) {
   long long width = W, cnt = C;
   long long first = (long long)blockIdx.x * C;  // offset of this block within the level
   int cur = 0;
@@ -413,24 +386,30 @@ __global__ __launch_bounds__(512) void k_tree_up(double* t, long long W, const i
   }
 }
 
-// All levels above the leaves, in launches of ten levels.
-static void tree_up_all(double* tree, long long L, const int* halt, hipStream_t s) {
-  long long W = L;
-  while (W > 1) {
-    const long long C = W < kTreeChunk ? W : kTreeChunk;
-    hipLaunchKernelGGL(k_tree_up, dim3((unsigned)(W / C)), dim3(512), 0, s, tree, W, halt);
-    W /= C;
-  }
+__global__ __launch_bounds__(512) void k_tree_up(double* t, long long W, const int* halt) {
+  if (*halt) return;
+  __shared__ double buf[2][kTreeChunk];
+  const int C = W < kTreeChunk ? (int)W : kTreeChunk;
+  for (int j = threadIdx.x; j < C; j += blockDim.x)
+    buf[0][j] = t[W + (long long)blockIdx.x * C + j];
+  __syncthreads();
+  tree_up(t, W, C, buf);
 }
 
-__global__ void k_count_leaves(const double* __restrict__ qn, long long n, Emitters em,
-                               long long L, double adt, uint64_t seed, int points, int kind,
-                               const DevState* __restrict__ st, double* __restrict__ ct) {
+// The counts of up to 1024 emitters per block (the leaves of the count tree)
+// and the levels above them.
+__global__ __launch_bounds__(512) void k_count_leaves(const double* __restrict__ qn, long long n,
+                                                      Emitters em, long long L, double adt,
+                                                      uint64_t seed, int points, int kind,
+                                                      const DevState* __restrict__ st,
+                                                      double* __restrict__ ct) {
   if (st->halt) return;
+  __shared__ double buf[2][kTreeChunk];
+  const int C = L < kTreeChunk ? (int)L : kTreeChunk;
   const double wq = st->wq[kind - 1];
   const uint64_t step = st->step;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < L;
-       i += (long long)gridDim.x * blockDim.x) {
+  for (int j = threadIdx.x; j < C; j += blockDim.x) {
+    const long long i = (long long)blockIdx.x * C + j;
     double c = 0.0;
     if (i < n + em.n_faces && wq > 0.0) {
       double Mi;
@@ -450,27 +429,35 @@ __global__ void k_count_leaves(const double* __restrict__ qn, long long n, Emitt
       }
     }
     ct[L + i] = c;
+    buf[0][j] = c;
   }
+  __syncthreads();
+  tree_up(ct, L, C, buf);
 }
 
-hipError_t launch_emission_plan(const double* qn, long long n_cells, const Emitters& em,
-                                double adt, long long n_src, uint64_t seed, int points, int kind,
-                                unsigned long long* hist, double* ctree, DevState* st,
-                                hipStream_t s) {
+hipError_t launch_majorant_sum(const double* qn, long long n_cells, const Emitters& em,
+                               double adt, long long n_src, int kind, unsigned long long* hist,
+                               DevState* st, hipStream_t s) {
+  const long long b = (n_cells + em.n_faces + 255) / 256;
+  const int grid = (int)(b < 1024 ? (b < 1 ? 1 : b) : 1024);
+  hipLaunchKernelGGL(k_maj_sum, dim3(grid), dim3(kMajThreads), 0, s, qn, n_cells, em, hist, adt,
+                     n_src, kind, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_emission_counts(const double* qn, long long n_cells, const Emitters& em,
+                                  double adt, uint64_t seed, int points, int kind, double* ctree,
+                                  DevState* st, hipStream_t s) {
   const long long L = tree_leaves(n_cells + em.n_faces);
-  long long b = (n_cells + 255) / 256;
-  int grid = (int)(b < 1024 ? (b < 1 ? 1 : b) : 1024);
-  const int* halt = &st->halt;
-  hipLaunchKernelGGL(k_maj_hist, dim3(grid), dim3(256), 0, s, qn, n_cells, hist, halt);
-  if (em.n_faces > 0)
-    hipLaunchKernelGGL(k_face_hist, dim3((unsigned)((em.n_faces + 255) / 256)), dim3(256), 0, s,
-                       em, hist, halt);
-  hipLaunchKernelGGL(k_maj_sum, dim3(1), dim3(kMajSumThreads), 0, s, hist, adt, em.cx, em.cy, n_src, kind, st);
-  b = (L + 255) / 256;
-  grid = (int)(b < 4096 ? (b < 1 ? 1 : b) : 4096);
-  hipLaunchKernelGGL(k_count_leaves, dim3(grid), dim3(256), 0, s, qn, n_cells, em, L, adt, seed,
-                     points, kind, (const DevState*)st, ctree);
-  tree_up_all(ctree, L, halt, s);  // integer-valued sums below 2^53: exact
+  long long W = L, C = L < kTreeChunk ? L : kTreeChunk;
+  hipLaunchKernelGGL(k_count_leaves, dim3((unsigned)(L / C)), dim3(512), 0, s, qn, n_cells, em, L,
+                     adt, seed, points, kind, (const DevState*)st, ctree);
+  // the levels above (integer-valued sums below 2^53: exact)
+  for (W /= C; W > 1; W /= C) {
+    C = W < kTreeChunk ? W : kTreeChunk;
+    hipLaunchKernelGGL(k_tree_up, dim3((unsigned)(W / C)), dim3(512), 0, s, ctree, W,
+                       (const int*)&st->halt);
+  }
   return hipGetLastError();
 }
 
@@ -554,6 +541,10 @@ hipError_t scan_inclusive_i64(const long long* in, long long* out, long long n,
                               long long* tmp, const int* halt, hipStream_t s) {
   return scan_rec<long long>(in, out, n, tmp, halt, s);
 }
+hipError_t scan_inclusive_u32(const uint32_t* in, uint32_t* out, long long n, uint32_t* tmp,
+                              const int* halt, hipStream_t s) {
+  return scan_rec<uint32_t>(in, out, n, tmp, halt, s);
+}
 
 // ---------------------------------------------------------------------------
 // Census population control.  When more than `cap` particles reach t_{n+1},
@@ -594,9 +585,16 @@ hipError_t launch_thin_params(DevState* st, long long cap, long long margin, hip
   return hipGetLastError();
 }
 
-long long census_tiles(long long n) { return (n + kKeepTile - 1) / kKeepTile; }
+// Rounds of 256 candidates per tile: sixteen, or two where the candidates would
+// fill few blocks (20x20, 2e4 candidates: keep decisions 17 -> 5 us).
+static int keep_rounds(long long n) { return n > (1ll << 18) ? 16 : 2; }
 
-// One tile of kKeepTile candidates per block, read in rounds of 256 (slot
+long long census_tiles(long long n) {
+  const long long tile = 256ll * keep_rounds(n);
+  return (n + tile - 1) / tile;
+}
+
+// One tile of candidates per block, read in rounds of 256 (slot
 // base + r 256 + t in round r, thread t): each candidate's keep decision in
 // place of its alive byte, the tile's kept count, and the cell of each kept
 // candidate in a plain array (history id and cell share a 32-byte sector of
@@ -608,7 +606,7 @@ __global__ __launch_bounds__(256) void k_census_keep(uint8_t* __restrict__ alive
                                                      long long n, uint64_t seed,
                                                      const DevState* st,
                                                      long long* __restrict__ tcount,
-                                                     int32_t* __restrict__ cell) {
+                                                     int32_t* __restrict__ cell, int rounds) {
   if (st->halt) return;
   __shared__ int s_c[4];
   // the thinning keys' stream: (step, pass 2, population 2)
@@ -616,9 +614,9 @@ __global__ __launch_bounds__(256) void k_census_keep(uint8_t* __restrict__ alive
   const int act = st->thin_active;
   const unsigned long long mant = st->thin_mant;
   const int rs = st->thin_rshift;
-  const long long base = (long long)blockIdx.x * kKeepTile;
+  const long long base = (long long)blockIdx.x * 256 * rounds;
   int cnt = 0;
-  for (int r = 0; r < kKeepTile / 256; ++r) {
+  for (int r = 0; r < rounds; ++r) {
     const long long i = base + r * 256 + threadIdx.x;
     if (i >= n) break;
     int f = alive[i] ? 1 : 0;
@@ -647,7 +645,7 @@ hipError_t launch_census_keep(uint8_t* alive, const StageRec<R>* stage, long lon
                               int32_t* cell, hipStream_t s) {
   const long long tiles = census_tiles(n > 0 ? n : 1);
   hipLaunchKernelGGL(k_census_keep<R>, dim3((unsigned)tiles), dim3(256), 0, s, alive, stage, n,
-                     seed, st, tcount, cell);
+                     seed, st, tcount, cell, keep_rounds(n));
   return hipGetLastError();
 }
 template hipError_t launch_census_keep<double>(uint8_t*, const StageRec<double>*, long long,
@@ -682,14 +680,14 @@ __global__ __launch_bounds__(256) void k_census_keys(const int32_t* __restrict__
                                                      long long n, long long cap,
                                                      uint32_t* __restrict__ keys,
                                                      uint32_t* __restrict__ vals,
-                                                     const DevState* st) {
+                                                     const DevState* st, int rounds) {
   if (st->halt) return;
   __shared__ int s_w[4];
   long long before = tincl[blockIdx.x] - tcount[blockIdx.x];  // kept in earlier tiles
   if (before >= cap || tcount[blockIdx.x] == 0) return;       // the same for the whole block
-  const long long base = (long long)blockIdx.x * kKeepTile;
+  const long long base = (long long)blockIdx.x * 256 * rounds;
   const int w = threadIdx.x >> 6;
-  for (int r = 0; r < kKeepTile / 256; ++r) {
+  for (int r = 0; r < rounds; ++r) {
     const long long i = base + r * 256 + threadIdx.x;
     const bool f = i < n && keep[i] != 0;
     const unsigned long long m = __ballot(f);
@@ -717,7 +715,7 @@ hipError_t launch_census_keys(const int32_t* cell, const uint8_t* keep, const lo
                               uint32_t* vals, const DevState* st, hipStream_t s) {
   const long long tiles = census_tiles(n > 0 ? n : 1);
   hipLaunchKernelGGL(k_census_keys, dim3((unsigned)tiles), dim3(256), 0, s, cell, keep, tcount,
-                     tincl, n, cap, keys, vals, st);
+                     tincl, n, cap, keys, vals, st, keep_rounds(n));
   return hipGetLastError();
 }
 
@@ -726,8 +724,10 @@ hipError_t launch_census_keys(const int32_t* cell, const uint8_t* keep, const lo
 // of 10 bits; 140^2: two of 8).  A tile of 256 rounds x 256 pairs per block,
 // with as many rounds as give 16 pairs per digit value on average (16 rounds
 // up to 8-bit digits, 64 for 10-bit), so that the scatter of a tile still
-// writes runs of whole sectors; the pairs are read in rounds (pair base +
-// r 256 + t in round r, thread t), in index order.
+// writes runs of whole sectors, but no more than leave 32 tiles: a round is a
+// chain of barriers (20x20, 1e4 pairs: 33 us in one tile of 32 rounds, 5 us in
+// twenty of two).  The pairs are read in rounds (pair base + r 256 + t in round
+// r, thread t), in index order.
 //   upsweep:   the tile's digit histogram -> hist[digit][tile]
 //   scan:      inclusive scan of hist (digit-major): the pairs of digit d of
 //              tile b start at incl[d][b] - hist[d][b]
@@ -753,29 +753,26 @@ static int sort_digit_bits(long long n_keys_max) {
   return (sort_key_bits(n_keys_max) + p - 1) / p;
 }
 
-static int sort_rounds(int digit_bits) { return digit_bits <= 8 ? 16 : 16 << (digit_bits - 8); }
-
-static long long sort_tiles(long long n, int digit_bits) {
-  const long long tile = 256ll * sort_rounds(digit_bits);
-  return (n + tile - 1) / tile;
+static int sort_rounds(long long cap, int digit_bits) {
+  const long long most = digit_bits <= 8 ? 16 : 16 << (digit_bits - 8);
+  return (int)std::max<long long>(2, std::min(most, cap / (32 * 256)));
 }
 
-long long radix_tiles(long long n) { return sort_tiles(n, 8); }
+static long long sort_tiles(long long cap, int digit_bits) {
+  const long long tile = 256ll * sort_rounds(cap, digit_bits);
+  return ((cap > 0 ? cap : 1) + tile - 1) / tile;
+}
 
-// Histogram entries for any digit width: digits x tiles is largest for the
-// widest digits (1024 x ceil(cap / 16384) >= 256 x ceil(cap / 4096)).
-size_t radix_hist_elems(long long cap) {
-  size_t m = 0;
-  for (int b = 8; b <= kSortMaxBits; ++b)
-    m = std::max(m, ((size_t)1 << b) * (size_t)sort_tiles(cap > 0 ? cap : 1, b));
-  return m;
+size_t radix_hist_elems(long long cap, long long n_keys_max) {
+  const int bits = sort_digit_bits(n_keys_max);
+  return ((size_t)1 << bits) * (size_t)sort_tiles(cap, bits);
 }
 
 __global__ __launch_bounds__(256) void k_radix_up(const uint32_t* __restrict__ keys,
                                                   const long long* incl_last, long long cap,
                                                   int shift, int bits, int rounds,
                                                   long long n_tiles,
-                                                  long long* __restrict__ hist,
+                                                  uint32_t* __restrict__ hist,
                                                   const DevState* st) {
   if (st->halt) return;
   __shared__ uint32_t h[kSortMaxDigits];
@@ -791,7 +788,7 @@ __global__ __launch_bounds__(256) void k_radix_up(const uint32_t* __restrict__ k
   }
   __syncthreads();
   for (int d = threadIdx.x; d < n_dig; d += 256)
-    hist[(long long)d * n_tiles + blockIdx.x] = (long long)h[d];
+    hist[(long long)d * n_tiles + blockIdx.x] = h[d];
 }
 
 __global__ __launch_bounds__(256) void k_radix_down(const uint32_t* __restrict__ kin,
@@ -801,11 +798,11 @@ __global__ __launch_bounds__(256) void k_radix_down(const uint32_t* __restrict__
                                                     const long long* incl_last, long long cap,
                                                     int shift, int bits, int rounds,
                                                     long long n_tiles,
-                                                    const long long* __restrict__ hist,
-                                                    const long long* __restrict__ hincl,
+                                                    const uint32_t* __restrict__ hist,
+                                                    const uint32_t* __restrict__ hincl,
                                                     const DevState* st) {
   if (st->halt) return;
-  __shared__ long long s_start[kSortMaxDigits];  // first output index of each digit of this tile
+  __shared__ uint32_t s_start[kSortMaxDigits];  // first output index of each digit of this tile
   __shared__ uint32_t s_run[kSortMaxDigits];     // pairs of each digit in the earlier rounds
   __shared__ uint32_t s_wave[4][kSortMaxDigits]; // pairs of each digit in each wave of the round
   const int t = threadIdx.x, w = t >> 6;
@@ -841,7 +838,7 @@ __global__ __launch_bounds__(256) void k_radix_down(const uint32_t* __restrict__
     if (ok) {
       uint32_t before = s_run[d];
       for (int v = 0; v < w; ++v) before += s_wave[v][d];
-      const long long o = s_start[d] + before + below;
+      const uint32_t o = s_start[d] + before + below;
       kout[o] = key;
       vout[o] = val;
     }
@@ -861,12 +858,12 @@ __global__ __launch_bounds__(256) void k_radix_down(const uint32_t* __restrict__
 // (k1, v1) after an odd number (radix_passes(key_bound)).
 hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
                             const long long* incl_last, long long cap, long long key_bound,
-                            long long* hist, long long* hincl, long long* scan_tmp,
+                            uint32_t* hist, uint32_t* hincl, uint32_t* scan_tmp,
                             const DevState* st, hipStream_t s) {
   const int passes = radix_passes(key_bound);
   const int bits = sort_digit_bits(key_bound);
-  const int rounds = sort_rounds(bits);
-  const long long tiles = sort_tiles(cap > 0 ? cap : 1, bits);
+  const int rounds = sort_rounds(cap, bits);
+  const long long tiles = sort_tiles(cap, bits);
   for (int p = 0; p < passes; ++p) {
     uint32_t* ki = (p & 1) ? k1 : k0;
     uint32_t* vi = (p & 1) ? v1 : v0;
@@ -874,11 +871,11 @@ hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* 
     uint32_t* vo = (p & 1) ? v0 : v1;
     hipLaunchKernelGGL(k_radix_up, dim3((unsigned)tiles), dim3(256), 0, s, (const uint32_t*)ki,
                        incl_last, cap, bits * p, bits, rounds, tiles, hist, st);
-    hipError_t e = scan_inclusive_i64(hist, hincl, (1ll << bits) * tiles, scan_tmp, &st->halt, s);
+    hipError_t e = scan_inclusive_u32(hist, hincl, (1ll << bits) * tiles, scan_tmp, &st->halt, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_radix_down, dim3((unsigned)tiles), dim3(256), 0, s, (const uint32_t*)ki,
                        (const uint32_t*)vi, ko, vo, incl_last, cap, bits * p, bits, rounds, tiles,
-                       (const long long*)hist, (const long long*)hincl, st);
+                       (const uint32_t*)hist, (const uint32_t*)hincl, st);
   }
   return hipGetLastError();
 }
