@@ -365,7 +365,7 @@ static Sizes sizes_of(const slh_problem* p) {
   b += std::max(scan_tmp_elems(census_tiles(z.n_cand)),
                 scan_tmp_elems((long long)radix_hist_elems(z.cap, z.n_cells))) * 8;
   b += (size_t)z.cap * 4 * 6 + radix_hist_elems(z.cap, z.n_cells) * 8 + nc * 4;  // census ordering
-  b += sizeof(DevState) + 32 * 32 * 4 + 64 * 8 + kCensusBlocks * 8;
+  b += sizeof(DevState) + 4 * kSobolNibbleWords + 64 * 8 + kCensusBlocks * 8;
   b += 64 * 1024;  // alignment of the ~30 device buffers
   z.bytes = b;
   return z;
@@ -724,7 +724,7 @@ static slh_status setup(slh_solver* s) {
   ALLOC(s->rhist, uint32_t, radix_hist_elems(z.cap, z.n_cells));
   ALLOC(s->rincl, uint32_t, radix_hist_elems(z.cap, z.n_cells));
   ALLOC(s->cstart, uint32_t, nc);
-  ALLOC(s->sobol, uint32_t, 32 * 32);
+  ALLOC(s->sobol, uint32_t, kSobolNibbleWords);
   ALLOC(s->st, DevState, 1);
   ALLOC(s->bal_store, BalStore, 2);
 #undef ALLOC
@@ -814,7 +814,8 @@ static slh_status setup(slh_solver* s) {
   if (z.diffusion || z.dsa)
     HIP_TRY(launch_diff_coef(p.nx, p.ny, s->mat64, time_term(&p), s->hx, s->hy,
                              z.dsa ? 0 : p.boundary, s->cg_diag, s->cg_e, s->cg_n, st));
-  HIP_TRY(hipMemcpyAsync(s->sobol, sobol_table_host(), 4 * 32 * 32, hipMemcpyHostToDevice, st));
+  HIP_TRY(hipMemcpyAsync(s->sobol, sobol_table_host(), 4 * kSobolNibbleWords,
+                         hipMemcpyHostToDevice, st));
   HIP_TRY(launch_fill_u64(s->maj_hist, kMajGroups * kMajBins, 0ull, st));  // left zero by every plan
   if (z.n_faces)
     HIP_TRY(hipMemcpyAsync(s->inflow, s->h_inflow.data(), 8 * z.n_faces, hipMemcpyHostToDevice,
@@ -1865,8 +1866,8 @@ extern "C" slh_status slh_qmc_points(uint64_t seed, uint64_t step, uint32_t pass
   static uint32_t* table = nullptr;  // per process, device 0 context
   if (!table) {
     uint32_t* t = nullptr;
-    HIP_TRY(hipMalloc(&t, 4 * 32 * 32));
-    HIP_TRY(hipMemcpy(t, sobol_table_host(), 4 * 32 * 32, hipMemcpyHostToDevice));
+    HIP_TRY(hipMalloc(&t, 4 * kSobolNibbleWords));
+    HIP_TRY(hipMemcpy(t, sobol_table_host(), 4 * kSobolNibbleWords, hipMemcpyHostToDevice));
     table = t;
   }
   const uint64_t stream = stream_seed(seed, step, pass, population, cohort);

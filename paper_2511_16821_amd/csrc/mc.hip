@@ -30,7 +30,21 @@
 
 namespace slh {
 
-const uint32_t* sobol_table_host() { return slh_sobol_v; }
+const uint32_t* sobol_table_host() {
+  struct Table {
+    alignas(16) uint32_t w[kSobolNibbleWords];
+    Table() {
+      for (int e = 0; e < kSobolNibbleWords; ++e) {
+        const int d = e >> 7, pos = (e >> 4) & 7;
+        w[e] = 0u;
+        for (int k = 0; k < 4; ++k)
+          if (e >> k & 1) w[e] ^= slh_sobol_v[d * 32 + 4 * pos + k];
+      }
+    }
+  };
+  static const Table t;  // initialised once, whichever thread comes first
+  return t.w;
+}
 
 template <typename R> struct Real;
 template <> struct Real<double> {
@@ -269,14 +283,24 @@ __device__ __forceinline__ float wave_uniform(float v) {
 // and last particles then show it, and the emitter's stream and
 // per-dimension scramble seeds are computed once for the run.  A run that
 // spans emitters descends the tree for each of its inner particles.
+//
+// The records of a wave's particles leave through LDS: a lane's record is four
+// 16-byte words, and lanes of a run apart would write one word to each of 64
+// sectors in every store; transposed, four neighbouring lanes write one whole
+// 64-byte record (1e7 particles on 256^2: FP64 0.32 -> 0.26 ms, FP32 0.33 ->
+// 0.24, with the six dimensions' tables loaded instead of built).
 constexpr long long kEmitRun = 8;
+constexpr int kEmitDims = 6;   // dimensions that a source particle's emission draws
+constexpr int kEmitWaves = 4;  // waves per block
+constexpr int kEmitRow = 5;    // LDS words of 16 bytes per record (padded against conflicts)
 
 template <typename R, int KIND>
 __global__ __launch_bounds__(256) void k_emit(PassArgs a) {
   if (a.st->halt) return;
-  __shared__ uint32_t s_sobol[kSobolNibbleWords];
+  __shared__ __align__(16) uint32_t s_sobol[kEmitDims * 128];
   __shared__ double s_top[kTreeTop];
-  sobol_nibbles_fill(a.sobol, s_sobol, threadIdx.x, blockDim.x);
+  __shared__ uint4 s_rec[kEmitWaves][64 * kEmitRow];
+  sobol_nibbles_load(a.sobol, s_sobol, kEmitDims, threadIdx.x, blockDim.x);
   {
     const long long ntop = 2 * a.tree_L < kTreeTop ? 2 * a.tree_L : kTreeTop;
     for (int k = threadIdx.x; k < kTreeTop; k += blockDim.x)
@@ -290,10 +314,18 @@ __global__ __launch_bounds__(256) void k_emit(PassArgs a) {
   SrcRec<R>* const b = Real<R>::src(a);
   const long long T = (long long)gridDim.x * blockDim.x;
   const long long run = n_emit / T < 1 ? 1 : (n_emit / T > kEmitRun ? kEmitRun : n_emit / T);
-  for (long long r0 = ((long long)blockIdx.x * blockDim.x + threadIdx.x) * run; r0 < n_emit;
-       r0 += run * T) {
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  SrcRec<R>* const row = reinterpret_cast<SrcRec<R>*>(s_rec[wv] + lane * kEmitRow);
+  uint4* const out = reinterpret_cast<uint4*>(b);
+  static_assert(sizeof(SrcRec<R>) == 4 * sizeof(uint4), "a record is four words");
+  // the wave's particles [w0, w0 + 64 run), the lane's run from r0
+  for (long long w0 = ((long long)blockIdx.x * kEmitWaves + wv) * 64 * run; w0 < n_emit;
+       w0 += run * T) {
+    const long long r0 = w0 + lane * run;
     const long long r1 = (r0 + run < n_emit ? r0 + run : n_emit) - 1;
-    long long sj[2] = {r0, r1};
+    // (a lane past the last particle looks up the last one)
+    long long sj[2] = {r0 < n_emit ? r0 : n_emit - 1, r1};
     CellPick pk[2];
     count_pick_n<2>(a.ctree, s_top, a.tree_L, sj, pk);
     const bool one = pk[0].cell == pk[1].cell;
@@ -301,65 +333,80 @@ __global__ __launch_bounds__(256) void k_emit(PassArgs a) {
     uint64_t stream = 0;
     uint32_t sd[6];
 #pragma unroll 1
-    for (long long s = r0; s <= r1; ++s) {
-      CellPick pc;
-      if (one) pc = CellPick{pk[0].cell, pk[0].l + (uint32_t)(s - r0)};
-      else if (s == r0) pc = pk[0];
-      else if (s == r1) pc = pk[1];
-      else count_pick_n<1>(a.ctree, s_top, a.tree_L, &s, &pc);
-      const long long ci = pc.cell;  // the emitter: a cell, or a boundary face after them
-      const uint32_t l = pc.l;
-      if (ci != cur) {
-        cur = ci;
-        stream = stream_seed(a.seed, step, (uint32_t)KIND, 0u, (uint64_t)ci);
+    for (int k = 0; k < (int)run; ++k) {
+      const long long s = r0 + k;
+      if (s <= r1) {
+        CellPick pc;
+        if (one) pc = CellPick{pk[0].cell, pk[0].l + (uint32_t)(s - r0)};
+        else if (s == r0) pc = pk[0];
+        else if (s == r1) pc = pk[1];
+        else count_pick_n<1>(a.ctree, s_top, a.tree_L, &s, &pc);
+        const long long ci = pc.cell;  // the emitter: a cell, or a boundary face after them
+        const uint32_t l = pc.l;
+        if (ci != cur) {
+          cur = ci;
+          stream = stream_seed(a.seed, step, (uint32_t)KIND, 0u, (uint64_t)ci);
 #pragma unroll
-        for (int d = 0; d < 6; ++d) sd[d] = point_seed(stream, (uint32_t)d);
-      }
-      const R u1 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[0], 0u, l));
-      const R u2 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[1], 1u, l));
-      const R u3 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[2], 2u, l));
-      const R u4 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[3], 3u, l));
-      const R tau = a.n_lim > 0
-                        ? -log(PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[5], 5u, l)))
-                        : (R)0;
-      if (ci < a.n_cells) {
-        const R u5 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[4], 4u, l));
-        const R sn = (R)2 * sqrt(u4 * ((R)1 - u4));
-        R sp, cp;
-        Real<R>::scpi((R)2 * u5, &sp, &cp);
-        const double* q = a.qn + 4 * ci;
-        const double wscale = wq / pow2_ceil(maxabs4(q));  // exact: a power-of-two ratio
-        const R w = (R)(bilinear(q, (double)u1, (double)u2) * wscale);
-        Real<R>::put_src(b + s, hx * u1, hy * u2, sn * cp, sn * sp, w, u3 * dt_birth, tau,
-                         (int)ci, l);
-      } else {
-        // entering through boundary face f (the inflow G): uniform along the
-        // face (dim 0) and in time (dim 1), the cosine law about the inward
-        // normal, mu = sqrt(u) (dim 2), the in-plane tangential component
-        // sqrt(1 - mu^2) cos(2 pi u) (dim 3); weight w_q G_f / pow2_ceil(|G_f|)
-        int k;
-        const int f = (int)(ci - a.n_cells);
-        const int side = face_side(f, a.nx, a.ny, &k);
-        const R mu = sqrt(u3);
-        R sp, cp;
-        Real<R>::scpi((R)2 * u4, &sp, &cp);
-        const R tg = sqrt((R)1 - u3) * cp;
-        const double G = a.em.inflow[f];
-        const R w = (R)(G * (wq / pow2_ceil(fabs(G))));
-        R px, py, ox, oy;
-        if (side < 2) {
-          px = side == 0 ? (R)0 : hx;
-          py = hy * u1;
-          ox = side == 0 ? mu : -mu;
-          oy = tg;
-        } else {
-          px = hx * u1;
-          py = side == 2 ? (R)0 : hy;
-          oy = side == 2 ? mu : -mu;
-          ox = tg;
+          for (int d = 0; d < 6; ++d) sd[d] = point_seed(stream, (uint32_t)d);
         }
-        Real<R>::put_src(b + s, px, py, ox, oy, w, u2 * dt_birth, tau, (int)ci, l);
+        const R u1 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[0], 0u, l));
+        const R u2 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[1], 1u, l));
+        const R u3 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[2], 2u, l));
+        const R u4 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[3], 3u, l));
+        const R tau = a.n_lim > 0
+                          ? -log(PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[5], 5u, l)))
+                          : (R)0;
+        if (ci < a.n_cells) {
+          const R u5 = PointU<R>::u(point_u32s(s_sobol, a.points, stream, sd[4], 4u, l));
+          const R sn = (R)2 * sqrt(u4 * ((R)1 - u4));
+          R sp, cp;
+          Real<R>::scpi((R)2 * u5, &sp, &cp);
+          const double* q = a.qn + 4 * ci;
+          const double wscale = wq / pow2_ceil(maxabs4(q));  // exact: a power-of-two ratio
+          const R w = (R)(bilinear(q, (double)u1, (double)u2) * wscale);
+          Real<R>::put_src(row, hx * u1, hy * u2, sn * cp, sn * sp, w, u3 * dt_birth, tau,
+                           (int)ci, l);
+        } else {
+          // entering through boundary face f (the inflow G): uniform along the
+          // face (dim 0) and in time (dim 1), the cosine law about the inward
+          // normal, mu = sqrt(u) (dim 2), the in-plane tangential component
+          // sqrt(1 - mu^2) cos(2 pi u) (dim 3); weight w_q G_f / pow2_ceil(|G_f|)
+          int along;
+          const int f = (int)(ci - a.n_cells);
+          const int side = face_side(f, a.nx, a.ny, &along);
+          const R mu = sqrt(u3);
+          R sp, cp;
+          Real<R>::scpi((R)2 * u4, &sp, &cp);
+          const R tg = sqrt((R)1 - u3) * cp;
+          const double G = a.em.inflow[f];
+          const R w = (R)(G * (wq / pow2_ceil(fabs(G))));
+          R px, py, ox, oy;
+          if (side < 2) {
+            px = side == 0 ? (R)0 : hx;
+            py = hy * u1;
+            ox = side == 0 ? mu : -mu;
+            oy = tg;
+          } else {
+            px = hx * u1;
+            py = side == 2 ? (R)0 : hy;
+            oy = side == 2 ? mu : -mu;
+            ox = tg;
+          }
+          Real<R>::put_src(row, px, py, ox, oy, w, u2 * dt_birth, tau, (int)ci, l);
+        }
       }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int of = (64 * j + lane) >> 2, part = lane & 3;  // whose record, which word
+        const long long d = w0 + of * run + k;
+        if (d < n_emit) out[4 * d + part] = s_rec[wv][of * kEmitRow + part];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
   }
 }
@@ -376,7 +423,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<
   // and census-in weights (exact in fixed point).
   __shared__ unsigned long long s_bal[kBalCopies * kBalStride];
   __shared__ unsigned long long s_cnt[4];
-  __shared__ uint32_t s_sobol[kSobolNibbleWords];
+  __shared__ __align__(16) uint32_t s_sobol[kSobolNibbleWords];
   __shared__ unsigned s_tc_tag[4 * kTcSlots];  // four waves per block
   __shared__ unsigned long long s_tc_sum[4 * kTcSlots];
   for (int k = threadIdx.x; k < 4 * kTcSlots; k += blockDim.x) {
@@ -385,7 +432,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<
   }
   for (int k = threadIdx.x; k < kBalCopies * kBalStride; k += blockDim.x) s_bal[k] = 0ull;
   if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0ull;
-  sobol_nibbles_fill(a.sobol, s_sobol, threadIdx.x, blockDim.x);
+  sobol_nibbles_load(a.sobol, s_sobol, kSobolDims, threadIdx.x, blockDim.x);
   __syncthreads();
 
   DevState* st = a.st;
@@ -779,10 +826,13 @@ int mc_pass_grid(bool fp32, int kind, long long max_work) {
 
 hipError_t launch_emit(const PassArgs& a, bool fp32, hipStream_t s) {
   if (a.n_src <= 0) return hipSuccess;
-  // at most 2048 blocks (each block first stages 24 KB of tables in LDS, six
-  // blocks fit a compute unit); a thread takes its particles in runs
-  long long b = (a.n_src + 255) / 256;
-  const int grid = (int)(b < 2048 ? b : 2048);
+  // Runs of eight on at most 2048 blocks; fewer particles first give up the
+  // blocks above 1024 and then the length of their runs (1e6 particles: 38 us
+  // on 1024 blocks in runs of four, 51 on 2048 in runs of one or two, 58 on
+  // 512 in runs of eight; 1e7: 0.26 ms on 2048, 0.29 on 1280)
+  const long long b = (a.n_src + 255) / 256;
+  const long long few = b < 1024 ? b : 1024, runs = b / kEmitRun;
+  const int grid = (int)(runs < few ? few : (runs < 2048 ? runs : 2048));
   if (a.kind == 1) {
     if (fp32) hipLaunchKernelGGL((k_emit<float, 1>), dim3(grid), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_emit<double, 1>), dim3(grid), dim3(256), 0, s, a);
@@ -809,8 +859,8 @@ __global__ __launch_bounds__(256) void k_qmc_points(uint64_t stream, uint32_t di
                                                     uint32_t nd, uint32_t idx0, uint32_t n,
                                                     int mode, const uint32_t* sobol,
                                                     uint32_t* out) {
-  __shared__ uint32_t s_nib[kSobolNibbleWords];
-  sobol_nibbles_fill(sobol, s_nib, threadIdx.x, blockDim.x);
+  __shared__ __align__(16) uint32_t s_nib[kSobolNibbleWords];
+  sobol_nibbles_load(sobol, s_nib, kSobolDims, threadIdx.x, blockDim.x);
   __syncthreads();
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (long long)n * nd) return;

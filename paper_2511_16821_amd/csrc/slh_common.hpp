@@ -55,21 +55,16 @@ constexpr int kSobolDims = 32;
 // 4-bit value n, so a word is the XOR of its index's nibble entries
 // (a lookup per nibble up to the highest set one: indices count the particles
 // of an emitter, two or three nibbles).  N has kSobolDims x
-// 8 x 16 words, built from V (kSobolDims x 32 words).
+// 8 x 16 words, built once from V (sobol_table_host).
 constexpr int kSobolNibbleWords = kSobolDims * 8 * 16;
 
-__device__ __forceinline__ void sobol_nibbles_fill(const uint32_t* __restrict__ V, uint32_t* N,
-                                                   int tid, int nthreads) {
-  for (int e = tid; e < kSobolNibbleWords; e += nthreads) {
-    const int d = e >> 7, pos = (e >> 4) & 7, n = e & 15;
-    const uint32_t* v = V + d * 32 + 4 * pos;
-    uint32_t x = 0;
-    if (n & 1) x ^= v[0];
-    if (n & 2) x ^= v[1];
-    if (n & 4) x ^= v[2];
-    if (n & 8) x ^= v[3];
-    N[e] = x;
-  }
+// The first n_dims dimensions of the table into a block's LDS, in 16-byte
+// words (256 threads: four each for all of it; built in every block from the
+// direction numbers it took a block 64 loads a thread).
+__device__ __forceinline__ void sobol_nibbles_load(const uint32_t* __restrict__ table, uint32_t* N,
+                                                   int n_dims, int tid, int nthreads) {
+  for (int e = tid; e < n_dims * 32; e += nthreads)
+    reinterpret_cast<uint4*>(N)[e] = reinterpret_cast<const uint4*>(table)[e];
 }
 
 __device__ __forceinline__ uint32_t sobol_word_nib(const uint32_t* N, uint32_t dim,
@@ -412,7 +407,7 @@ struct PassArgs {
   const int* ns_cell;    // per-cell limits (unlimited as INT_MAX), or null
   int bc;                // reflective sides: 1 x_lo, 2 x_hi, 4 y_lo, 8 y_hi
   int points;            // 0 Sobol'-Owen, 1 pseudo-random
-  const uint32_t* sobol; // direction numbers
+  const uint32_t* sobol; // nibble tables of the Sobol' words
   double w_cut_rel;
   unsigned int max_segments;
   // census: input bank and output slots (census index, or out_src_base +
@@ -456,7 +451,7 @@ hipError_t launch_mc_pass(const PassArgs& a, bool fp32, int grid, hipStream_t s)
 hipError_t launch_qmc_points(uint64_t stream, uint32_t dim0, uint32_t nd, uint32_t idx0,
                              uint32_t n, int mode, const uint32_t* sobol, uint32_t* out,
                              hipStream_t s);
-const uint32_t* sobol_table_host();
+const uint32_t* sobol_table_host();  // nibble tables, kSobolNibbleWords words
 
 // How the collided solve sweeps a mesh: the u axis a wave walks along and the
 // v axis its lanes lie on (swap 0: u = x, v = y; 1: the other way round),
