@@ -962,6 +962,7 @@ static CgArgs cg_args(slh_solver* s) {
   c.part_b = s->cg_part + 2 * s->cg_npart;
   // the closing stage's solve is the step's iteration; the correction is a
   // solve inside each source iteration, skipped once that iteration is done
+  c.red = s->st->red;
   c.cs = s->z.diffusion ? &s->st->si : &s->st->dsa;
   c.gate = s->z.diffusion ? nullptr : &s->st->si.done;
   return c;

@@ -770,9 +770,7 @@ __device__ __forceinline__ void residual(double dsum, double nsum, double* parti
       __hip_atomic_store(&partials[2 * blockIdx.x + 1], nsum, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      const unsigned before = __hip_atomic_fetch_add(&st->red_blocks, 1u, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-      s_last = before == gridDim.x - 1;
+      if (lane == 0) s_last = count_block(st->red);
     }
   }
   __syncthreads();
@@ -796,7 +794,6 @@ __device__ __forceinline__ void residual(double dsum, double nsum, double* parti
       nrm2 += s_n[k];
     }
     const double dn = sqrt(dn2), nrm = sqrt(nrm2);
-    st->red_blocks = 0u;
     st->si.dn2_prev = st->si.iter > 0 ? st->si.dn2 : 0.0;
     st->si.dn2 = dn2;
     st->si.nrm2 = nrm2;

@@ -6,16 +6,17 @@
 // (no tau/(c dt) in steady state), harmonic-mean face coefficients, Marshak
 // vacuum sides and zero-current reflective sides.  The symmetric positive
 // definite system is solved by Jacobi-preconditioned conjugate gradients
-// from phi = 0, each iteration three kernels:
+// from phi = 0, each iteration two kernels:
 //   k_cg_spmv:     p_k = z + beta p_{k-1} (every cell also forms its four
 //                  neighbours' p_k, so the update needs no separate pass),
 //                  q = A p_k, block partials of p_k . q;
 //   k_cg_update:   alpha = rz / (p_k . q) (each block sums the partials in
 //                  the same fixed order), x += alpha p_k, r -= alpha q,
-//                  z = r / diag, block partials of r . z and r . r;
-//   k_cg_residual: one block: beta, the stopping test ||r|| <= tol ||b||,
-//                  the iteration count, in the source-iteration state, so the
-//                  host loop and the graph batching of the S_N path apply.
+//                  z = r / diag, block partials of r . z and r . r; the last
+//                  block to leave its partials: beta, the stopping test ||r||
+//                  <= tol ||b||, the iteration count, in the source-iteration
+//                  state, so the graph batching of the S_N path applies (a
+//                  launch of its own took 3-4 us of every iteration).
 // Reductions use fixed association orders: results do not depend on
 // scheduling.  The two p buffers alternate by iteration parity.  Meshes of
 // up to 4096 cells run the whole solve in one workgroup instead
@@ -93,71 +94,85 @@ hipError_t launch_diff_coef(int nx, int ny, const double2* mat, double tt, doubl
   return hipGetLastError();
 }
 
-// Block sum of two values per thread into out[2 blockIdx.x + {0,1}].
-__device__ __forceinline__ void block_sum2(double a, double b, double* out) {
-  __shared__ double s_a[kCgBlock], s_b[kCgBlock];
-  s_a[threadIdx.x] = a;
-  s_b[threadIdx.x] = b;
+// Sum of a block's values in the association order of a tree that halves the
+// block from 128 threads to 1; in thread 0.  The two widest levels read LDS
+// behind one barrier, the others stay in the first wave (a barrier per level
+// cost 1-2 us of every launch).
+__device__ __forceinline__ double block_tree(double v, double* s) {
+  const int t = threadIdx.x;
+  s[t] = v;
   __syncthreads();
-  for (int off = kCgBlock / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      s_a[threadIdx.x] += s_a[threadIdx.x + off];
-      s_b[threadIdx.x] += s_b[threadIdx.x + off];
-    }
-    __syncthreads();
+  if (t < 64) {
+    v = (s[t] + s[t + 128]) + (s[t + 64] + s[t + 192]);
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
   }
+  return v;
+}
+
+// Leaves the block's sums of two values per thread in part[2 block + {0, 1}]
+// and says whether the block is the grid's last to do so.  The partials cross
+// the XCDs as agent-scope stores and loads; the stores have reached memory
+// when the block counts itself.
+__device__ __forceinline__ bool leave_partials(double a, double b, double* part, int block,
+                                               RedCounter* red) {
+  __shared__ double s_a[kCgBlock], s_b[kCgBlock];
+  __shared__ int s_last;
+  a = block_tree(a, s_a);
+  b = block_tree(b, s_b);
   if (threadIdx.x == 0) {
-    out[2 * blockIdx.x] = s_a[0];
-    out[2 * blockIdx.x + 1] = s_b[0];
+    __hip_atomic_store(&part[2 * block], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&part[2 * block + 1], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    s_last = count_block(red);
   }
+  __syncthreads();
+  return s_last != 0;
 }
 
 // Fixed-order sum of the first (w = 0) or second (w = 1) value of n_part
-// block partials; every thread of the block gets the result.
+// block partials of an earlier kernel; every thread of the block gets it.
 __device__ __forceinline__ double sum_partials(const double* part, int n_part, int w) {
   __shared__ double s[kCgBlock];
+  __shared__ double s_sum;
   double v = 0.0;
   for (int b = threadIdx.x; b < n_part; b += kCgBlock) v += part[2 * b + w];
-  s[threadIdx.x] = v;
+  v = block_tree(v, s);
+  if (threadIdx.x == 0) s_sum = v;
   __syncthreads();
-  for (int off = kCgBlock / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
-    __syncthreads();
-  }
-  const double r = s[0];
-  __syncthreads();
-  return r;
+  return s_sum;
 }
 
-// Start: b = sigma_s phi_post, x = 0, r = b, z = r / diag, p_{-1} = 0
-// (buffer 1), partials of r . z and b . b.
-__global__ __launch_bounds__(kCgBlock) void k_cg_start(
-    long long n, const double* __restrict__ sig_s, const double* __restrict__ phi_post,
-    const double* __restrict__ diag, double* __restrict__ x, double* __restrict__ r,
-    double* __restrict__ z, double* __restrict__ p1, double* __restrict__ part,
-    const int* halt) {
-  if (*halt) return;
-  double rz = 0.0, bb = 0.0;
-  for (long long k = (long long)blockIdx.x * kCgBlock + threadIdx.x; k < n;
-       k += (long long)gridDim.x * kCgBlock) {
-    const double b = sig_s[k] * phi_post[k];
-    const double zk = b / diag[k];
-    x[k] = 0.0;
-    r[k] = b;
-    z[k] = zk;
-    p1[k] = 0.0;
-    rz += b * zk;
-    bb += b * b;
+// The same sums of both values of this kernel's partials, in thread 0.
+__device__ __forceinline__ void sum_left(const double* part, int n_part, double& a, double& b) {
+  __shared__ double s_a[kCgBlock], s_b[kCgBlock];
+  a = b = 0.0;
+  for (int k = threadIdx.x; k < n_part; k += kCgBlock) {
+    a += __hip_atomic_load(&part[2 * k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    b += __hip_atomic_load(&part[2 * k + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  block_sum2(rz, bb, part);
+  a = block_tree(a, s_a);
+  b = block_tree(b, s_b);
 }
 
-__global__ __launch_bounds__(kCgBlock) void k_cg_start_state(const double* part, int n_part,
-                                                             IterState* cs, const int* gate,
-                                                             int max_iter, const int* halt) {
-  if ((gate && *gate) || (halt && *halt)) return;
-  const double rz = sum_partials(part, n_part, 0);
-  const double bb = sum_partials(part, n_part, 1);
+// Both kernels of an iteration are bound by memory on large meshes (1024^2: 56
+// and 64 MB in 12 and 17 us, 17 and 20 us before) and by launch and reduction
+// latency on small ones (140^2: 4.6 and 6.0 us; with the decision of 3.7 us as
+// a launch of its own and a barrier per level 17 us an iteration, now 10.6).
+// Blocks take runs of the mesh XCD by XCD, so that a row's neighbours are read
+// by the same L2; partials are indexed by the run, which keeps the order of the
+// sums.  The update loads kCgAhead cells (all of a thread's on 1024^2) before it
+// waits for the first.
+constexpr int kCgAhead = 4;
+__device__ __forceinline__ int cg_block() {
+  return gridDim.x % 8u ? (int)blockIdx.x
+                        : (int)((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+}
+
+// State of a new solve from the partials of r . z and b . b (one block).
+__device__ __forceinline__ void start_state(const double* part, int n_part, IterState* cs,
+                                            int max_iter) {
+  double rz, bb;
+  sum_left(part, n_part, rz, bb);
   if (threadIdx.x == 0) {
     cs->iter = 0;
     cs->bad = 0;
@@ -175,14 +190,38 @@ __global__ __launch_bounds__(kCgBlock) void k_cg_start_state(const double* part,
   }
 }
 
+// Start: b = sigma_s phi_post, x = 0, r = b, z = r / diag, p_{-1} = 0
+// (buffer 1), r . z and b . b, and the state of the solve.
+__global__ __launch_bounds__(kCgBlock) void k_cg_start(
+    long long n, const double* __restrict__ sig_s, const double* __restrict__ phi_post,
+    const double* __restrict__ diag, double* __restrict__ x, double* __restrict__ r,
+    double* __restrict__ z, double* __restrict__ p1, double* part, RedCounter* red,
+    IterState* cs, int max_iter, const int* halt) {
+  if (*halt) return;
+  double rz = 0.0, bb = 0.0;
+  for (long long k = (long long)blockIdx.x * kCgBlock + threadIdx.x; k < n;
+       k += (long long)gridDim.x * kCgBlock) {
+    const double b = sig_s[k] * phi_post[k];
+    const double zk = b / diag[k];
+    x[k] = 0.0;
+    r[k] = b;
+    z[k] = zk;
+    p1[k] = 0.0;
+    rz += b * zk;
+    bb += b * b;
+  }
+  if (leave_partials(rz, bb, part, blockIdx.x, red))
+    start_state(part, gridDim.x, cs, max_iter);
+}
+
 // Start of the diffusion correction of a source iteration: b = sigma_s times
 // the cell average of phi^{k+1/2} - phi^k (dnode, four nodes per cell), x = 0,
-// r = b, z = r / diag, p_{-1} = 0, partials of r . z and b . b.
+// r = b, z = r / diag, p_{-1} = 0, r . z and b . b, and the state of the solve.
 __global__ __launch_bounds__(kCgBlock) void k_dsa_start(
     long long n, const double* __restrict__ sig_s, const double* __restrict__ dnode,
     const double* __restrict__ diag, double* __restrict__ x, double* __restrict__ r,
-    double* __restrict__ z, double* __restrict__ p1, double* __restrict__ part,
-    const int* gate) {
+    double* __restrict__ z, double* __restrict__ p1, double* part, RedCounter* red,
+    IterState* cs, int max_iter, const int* gate) {
   if (*gate) return;
   double rz = 0.0, bb = 0.0;
   for (long long k = (long long)blockIdx.x * kCgBlock + threadIdx.x; k < n;
@@ -197,7 +236,8 @@ __global__ __launch_bounds__(kCgBlock) void k_dsa_start(
     rz += b * zk;
     bb += b * b;
   }
-  block_sum2(rz, bb, part);
+  if (leave_partials(rz, bb, part, blockIdx.x, red))
+    start_state(part, gridDim.x, cs, max_iter);
 }
 
 __global__ __launch_bounds__(kCgBlock) void k_cg_spmv(
@@ -211,52 +251,80 @@ __global__ __launch_bounds__(kCgBlock) void k_cg_spmv(
   double* __restrict__ pk = P + (long long)(it & 1) * n;
   const double* __restrict__ pm = P + (long long)((it + 1) & 1) * n;
   double pq = 0.0;
-  for (long long k = (long long)blockIdx.x * kCgBlock + threadIdx.x; k < n;
-       k += (long long)gridDim.x * kCgBlock) {
-    const int i = (int)(k % nx), j = (int)(k / nx);
+  // at most 1024 blocks (cg_partials): the stride and the first cells are 32-bit
+  const int block = cg_block();
+  const unsigned stride = gridDim.x * kCgBlock, first = block * kCgBlock + threadIdx.x;
+  int i = (int)(first % (unsigned)nx), j = (int)(first / (unsigned)nx);
+  const int di = (int)(stride % (unsigned)nx), dj = (int)(stride / (unsigned)nx);
+  for (long long k = first; k < n; k += stride) {
+    // a side without a neighbour reads the cell itself and counts zero, so that
+    // the loads need no branches between them
+    const bool hE = i + 1 < nx, hW = i > 0, hN = j + 1 < ny, hS = j > 0;
+    const long long kE = hE ? k + 1 : k, kW = hW ? k - 1 : k;
+    const long long kN = hN ? k + nx : k, kS = hS ? k - nx : k;
+    const double c0 = cE[k], c1 = cE[kW], c2 = cN[k], c3 = cN[kS];
     const double pc = z[k] + beta * pm[k];
+    const double pE = z[kE] + beta * pm[kE], pW = z[kW] + beta * pm[kW];
+    const double pN = z[kN] + beta * pm[kN], pS = z[kS] + beta * pm[kS];
     double a = 0.0;
-    if (i + 1 < nx) a += cE[k] * (z[k + 1] + beta * pm[k + 1]);
-    if (i > 0) a += cE[k - 1] * (z[k - 1] + beta * pm[k - 1]);
-    if (j + 1 < ny) a += cN[k] * (z[k + nx] + beta * pm[k + nx]);
-    if (j > 0) a += cN[k - nx] * (z[k - nx] + beta * pm[k - nx]);
+    a += (hE ? c0 : 0.0) * (hE ? pE : 0.0);
+    a += (hW ? c1 : 0.0) * (hW ? pW : 0.0);
+    a += (hN ? c2 : 0.0) * (hN ? pN : 0.0);
+    a += (hS ? c3 : 0.0) * (hS ? pS : 0.0);
     const double qk = diag[k] * pc - a;
     pk[k] = pc;
     q[k] = qk;
     pq += pc * qk;
+    i += di;
+    j += dj;
+    if (i >= nx) {
+      i -= nx;
+      ++j;
+    }
   }
-  block_sum2(pq, 0.0, part);
+  __shared__ double s_pq[kCgBlock];
+  pq = block_tree(pq, s_pq);
+  if (threadIdx.x == 0) part[2 * block] = pq;
 }
 
 __global__ __launch_bounds__(kCgBlock) void k_cg_update(
     long long n, const double* __restrict__ diag, const double* __restrict__ P,
     const double* __restrict__ q, double* __restrict__ x, double* __restrict__ r,
-    double* __restrict__ z, const double* __restrict__ part_pq, int n_part,
-    double* __restrict__ part, const IterState* cs, const int* gate) {
+    double* __restrict__ z, const double* __restrict__ part_pq, int n_part, double* part,
+    RedCounter* red, IterState* cs, const int* gate, double tol, int max_iter) {
   if ((gate && *gate) || cs->done) return;
   const double pq = sum_partials(part_pq, n_part, 0);
   const double alpha = cs->rz / pq;
   const double* __restrict__ pk = P + (long long)(cs->iter & 1) * n;
   double rz = 0.0, rr = 0.0;
-  for (long long k = (long long)blockIdx.x * kCgBlock + threadIdx.x; k < n;
-       k += (long long)gridDim.x * kCgBlock) {
-    x[k] += alpha * pk[k];
-    const double rk = r[k] - alpha * q[k];
-    const double zk = rk / diag[k];
-    r[k] = rk;
-    z[k] = zk;
-    rz += rk * zk;
-    rr += rk * rk;
+  const int block = cg_block();
+  const long long stride = (long long)gridDim.x * kCgBlock;
+  for (long long k0 = (long long)block * kCgBlock + threadIdx.x; k0 < n; k0 += kCgAhead * stride) {
+    double xk[kCgAhead], rk[kCgAhead], p[kCgAhead], qk[kCgAhead], d[kCgAhead];
+#pragma unroll
+    for (int m = 0; m < kCgAhead; ++m) {
+      const long long k = k0 + m * stride < n ? k0 + m * stride : k0;
+      xk[m] = x[k];
+      rk[m] = r[k];
+      p[m] = pk[k];
+      qk[m] = q[k];
+      d[m] = diag[k];
+    }
+#pragma unroll
+    for (int m = 0; m < kCgAhead; ++m) {
+      const long long k = k0 + m * stride;
+      if (k >= n) break;
+      x[k] = xk[m] + alpha * p[m];
+      const double rm = rk[m] - alpha * qk[m];
+      const double zm = rm / d[m];
+      r[k] = rm;
+      z[k] = zm;
+      rz += rm * zm;
+      rr += rm * rm;
+    }
   }
-  block_sum2(rz, rr, part);
-}
-
-__global__ __launch_bounds__(kCgBlock) void k_cg_residual(const double* part, int n_part,
-                                                          IterState* cs, const int* gate,
-                                                          double tol, int max_iter) {
-  if ((gate && *gate) || cs->done) return;
-  const double rz = sum_partials(part, n_part, 0);
-  const double rr = sum_partials(part, n_part, 1);
+  if (!leave_partials(rz, rr, part, block, red)) return;
+  sum_left(part, n_part, rz, rr);
   if (threadIdx.x == 0) {
     const double bb = cs->bb;
     cs->iter += 1;
@@ -385,9 +453,8 @@ hipError_t launch_cg_start(const CgArgs& a, const double* sig_s, const double* p
                            int max_iter, const int* halt, hipStream_t s) {
   const long long n = (long long)a.nx * a.ny;
   hipLaunchKernelGGL(k_cg_start, dim3(a.n_part), dim3(kCgBlock), 0, s, n, sig_s, phi_post,
-                     (const double*)a.diag, a.x, a.r, a.z, a.P + n, a.part_a, halt);
-  hipLaunchKernelGGL(k_cg_start_state, dim3(1), dim3(kCgBlock), 0, s, (const double*)a.part_a,
-                     a.n_part, a.cs, a.gate, max_iter, halt);
+                     (const double*)a.diag, a.x, a.r, a.z, a.P + n, a.part_a, a.red, a.cs,
+                     max_iter, halt);
   return hipGetLastError();
 }
 
@@ -395,9 +462,8 @@ hipError_t launch_dsa_start(const CgArgs& a, const double* sig_s, const double* 
                             int max_iter, hipStream_t s) {
   const long long n = (long long)a.nx * a.ny;
   hipLaunchKernelGGL(k_dsa_start, dim3(a.n_part), dim3(kCgBlock), 0, s, n, sig_s, dnode,
-                     (const double*)a.diag, a.x, a.r, a.z, a.P + n, a.part_a, a.gate);
-  hipLaunchKernelGGL(k_cg_start_state, dim3(1), dim3(kCgBlock), 0, s, (const double*)a.part_a,
-                     a.n_part, a.cs, a.gate, max_iter, (const int*)nullptr);
+                     (const double*)a.diag, a.x, a.r, a.z, a.P + n, a.part_a, a.red, a.cs,
+                     max_iter, a.gate);
   return hipGetLastError();
 }
 
@@ -418,10 +484,8 @@ hipError_t launch_cg_iteration(const CgArgs& a, double tol, int max_iter, hipStr
                      (const double*)a.z, a.P, a.q, a.part_a, (const IterState*)a.cs, a.gate);
   hipLaunchKernelGGL(k_cg_update, dim3(a.n_part), dim3(kCgBlock), 0, s, n,
                      (const double*)a.diag, (const double*)a.P, (const double*)a.q, a.x, a.r,
-                     a.z, (const double*)a.part_a, a.n_part, a.part_b, (const IterState*)a.cs,
-                     a.gate);
-  hipLaunchKernelGGL(k_cg_residual, dim3(1), dim3(kCgBlock), 0, s, (const double*)a.part_b,
-                     a.n_part, a.cs, a.gate, tol, max_iter);
+                     a.z, (const double*)a.part_a, a.n_part, a.part_b, a.red, a.cs,
+                     a.gate, tol, max_iter);
   return hipGetLastError();
 }
 

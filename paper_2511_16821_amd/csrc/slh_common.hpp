@@ -288,6 +288,13 @@ struct IterState {
   double bb;    // CG: b . b
 };
 
+// Counters of the blocks that have left their partials, eight and their root,
+// each in a line of its own.
+constexpr int kRedGroups = 8;
+struct alignas(128) RedCounter {
+  unsigned int n;
+};
+
 struct DevState {
   long long n_in;            // census-in bank size
   double maxabs_w;           // max |w| over the census-in bank
@@ -314,12 +321,11 @@ struct DevState {
   // ended with a non-finite weight or tally, 4 the plan exceeded the source
   // bank (clamped to it)
   int numeric;
-  unsigned int red_blocks;      // blocks of the running reduction that left their partials
   unsigned int ticket[8];       // tasks taken of the running sweep, per class of blocks
   unsigned int sweep_tag;       // tag of the next sweep's traces between workgroups
-  unsigned int pad2;
   unsigned long long bal[2 * B_NFIELDS];
   unsigned long long step;      // time step being computed (point streams, history ids)
+  RedCounter red[kRedGroups + 1];  // of the running reduction (count_block)
   // source iteration of the collided solve (or the conjugate gradients of
   // the diffusion closing stage), kept on the device so that a batch of
   // iterations needs no host round trip: once si.done is set the remaining
@@ -351,6 +357,30 @@ struct DevState {
   int acc_numeric;
   int pad3;
 };
+
+// Counts a block that has left its partials (one thread per block, its stores
+// waited for) and says whether it is the grid's last.  The blocks of one launch
+// all count themselves or none does; the last clears the counters.  A counter
+// takes 10-12 ns per block (the XCDs meet in memory), which held the last block
+// of a 1024-block conjugate-gradient update for half of its 25 us: large grids
+// count in eight groups first (1024 blocks: 25.1 -> 16.9 us; a DG reduction of
+// 256 or 324 blocks: no difference).
+constexpr unsigned kRedOneCounter = 512;
+__device__ __forceinline__ bool count_block(RedCounter* red) {
+  const auto add = [](unsigned* p) {
+    return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  unsigned of = gridDim.x;
+  if (of >= kRedOneCounter) {
+    const unsigned g = blockIdx.x % kRedGroups;
+    if (add(&red[g].n) != (of - g + kRedGroups - 1) / kRedGroups - 1) return false;
+    red[g].n = 0u;
+    of = kRedGroups;
+  }
+  if (add(&red[kRedGroups].n) != of - 1) return false;
+  red[kRedGroups].n = 0u;
+  return true;
+}
 
 // Emitters of a pass beyond the cells: the boundary faces of a prescribed
 // inflow G (n_faces = 2 (nx + ny) values, or none): the x_lo faces (index
@@ -552,6 +582,7 @@ struct CgArgs {
   double *x, *r, *z, *P, *q;
   double *part_a, *part_b;
   int n_part;           // cg_partials(nx * ny)
+  RedCounter* red;      // st->red
   IterState* cs;        // the solve's state: st->si for the closing stage,
                         // st->dsa for the correction of a source iteration
   const int* gate;      // if not null and set (the source iteration is done),

@@ -270,14 +270,9 @@ __global__ __launch_bounds__(kMajThreads) void k_maj_sum(const double* __restric
   // this wave's adds have reached memory before the block counts itself
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (t == 0) {
-    const unsigned before = __hip_atomic_fetch_add(&st->red_blocks, 1u, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-    s_last = before == gridDim.x - 1;
-  }
+  if (t == 0) s_last = count_block(st->red);
   __syncthreads();
   if (!s_last) return;
-  if (t == 0) st->red_blocks = 0u;
   for (int gb = t; gb < n_bins; gb += kMajThreads) {
     const unsigned long long c =
         __hip_atomic_load(&hist[gb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
