@@ -587,6 +587,137 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
   }
 }
 
+// A mesh of one row (nv = 1): its cells form a chain only through the u traces,
+// and a cell maps its inflow trace to its outflow trace by ux' = A ux + B with
+//   A = a (v1 c1 + conj(v1 c2)),
+//   B = v1 c1 (S1 + b uy) + conj(v1 c2 (S2 + b uy)),
+// since conj(X2) is linear in ux.  Such maps compose associatively, so a
+// workgroup per direction finds the inflow traces of all cells by a prefix scan
+// of the maps, a thread taking `per` successive cells (one up to 1024), where
+// the strips' walk takes a step per cell (80 cells between reflective sides,
+// S_4: 19 -> 4.4 us a sweep, the steady solve 5.0 -> 2.5 ms; what is left is
+// launch and memory latency).
+constexpr int kRowWaves = 16;
+
+struct TraceMap {
+  double ar, ai, br, bi;
+};
+// the map `second` after the map `first`
+__device__ __forceinline__ TraceMap after(const TraceMap& first, const TraceMap& second) {
+  TraceMap t;
+  t.ar = second.ar * first.ar - second.ai * first.ai;
+  t.ai = second.ar * first.ai + second.ai * first.ar;
+  t.br = fma(second.ar, first.br, fma(-second.ai, first.bi, second.br));
+  t.bi = fma(second.ar, first.bi, fma(second.ai, first.br, second.bi));
+  return t;
+}
+__device__ __forceinline__ TraceMap shuffle_up(const TraceMap& m, int off) {
+  return {__shfl_up(m.ar, off), __shfl_up(m.ai, off), __shfl_up(m.br, off),
+          __shfl_up(m.bi, off)};
+}
+__device__ __forceinline__ double2 apply(const TraceMap& m, double2 x) {
+  return make_double2(fma(m.ar, x.x, fma(-m.ai, x.y, m.br)), fma(m.ar, x.y, fma(m.ai, x.x, m.bi)));
+}
+
+template <bool REFL>
+__global__ __launch_bounds__(64 * kRowWaves) void k_dg_sweep_row(DgArgs g) {
+  if (g.st->si.done) return;
+  __shared__ TraceMap s_map[kRowWaves];  // of each wave's cells
+  constexpr double kap = kV1i;           // v1 = -1 + i kap
+  const int nu = g.nu, q = (int)blockIdx.x / g.n_grp;
+  const int m = q * g.n_quad + ((int)blockIdx.x - q * g.n_grp);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double x = fabs(g.dir[3 * m]) / g.hx, y = fabs(g.dir[3 * m + 1]) / g.hy;
+  const double a = g.swap ? y : x, b = g.swap ? x : y;
+  // reflective sides as in k_dg_sweep
+  const bool back = (q & (g.swap ? 2 : 1)) != 0, vnegative = (q & (g.swap ? 1 : 2)) != 0;
+  const int ubc = g.swap ? g.bc >> 2 : g.bc, vbc = g.swap ? g.bc : g.bc >> 2;
+  const bool u_in = REFL && (ubc & (back ? 2 : 1)), u_out = REFL && (ubc & (back ? 1 : 2));
+  const bool v_in = REFL && (vbc & (vnegative ? 2 : 1));
+  const bool v_out = REFL && (vbc & (vnegative ? 1 : 2));
+  const int it = REFL ? g.st->si.iter : 0;
+  const size_t n_tr = (size_t)nu + 1;  // traces of a direction: the u face's, then the v faces'
+  const double2* b_u = nullptr;
+  const double2* b_v = nullptr;
+  double2* b_out = nullptr;
+  if (REFL) {
+    const double2* const b_in =
+        reinterpret_cast<const double2*>(g.bnd) + (size_t)((it + 1) & 1) * g.n_dir * n_tr;
+    b_u = b_in + (g.swap ? g.refl_y : g.refl_x)[m] * n_tr;
+    b_v = b_in + (g.swap ? g.refl_x : g.refl_y)[m] * n_tr + 1;
+    b_out = reinterpret_cast<double2*>(g.bnd) + ((size_t)(it & 1) * g.n_dir + m) * n_tr;
+  }
+  const double2* const src = reinterpret_cast<const double2*>(g.src) + (size_t)q * 2 * nu;
+  double2* const out =
+      reinterpret_cast<double2*>(g.psi) + (size_t)blockIdx.x * 2 * nu;
+
+  struct Cell {
+    double2 c1, c2, t1, t2;  // t = S + b uy
+  };
+  auto load = [&](int u) {
+    double se;
+    if (g.mat_off)
+      se = g.sig_e_mat[g.mat_off[(size_t)q * nu + u] >> 5];
+    else
+      se = g.sig_e[back ? nu - 1 - u : u];
+    Cell c;
+    c.t1 = src[2 * u];
+    c.t2 = src[2 * u + 1];
+    if (v_in) {
+      const double2 uy = b_v[u];
+      c.t1.x = fma(b, uy.x, c.t1.x);
+      c.t1.y = fma(b, uy.y, c.t1.y);
+      c.t2.x = fma(b, uy.x, c.t2.x);
+      c.t2.y = fma(b, uy.y, c.t2.y);
+    }
+    mode_inverse(a, b, se, c.c1, c.c2);
+    return c;
+  };
+  auto times = [](double2 p, double2 r) {
+    return make_double2(p.x * r.x - p.y * r.y, p.x * r.y + p.y * r.x);
+  };
+  // v1 X1 + conj(v1 X2)
+  auto trace = [&](double2 X1, double2 X2) {
+    return make_double2(fma(-kap, X1.y + X2.y, -(X1.x + X2.x)),
+                        fma(kap, X1.x - X2.x, -(X1.y - X2.y)));
+  };
+
+  const int per = (nu + (int)blockDim.x - 1) / (int)blockDim.x;
+  const int u0 = (int)threadIdx.x * per, u1 = u0 + per < nu ? u0 + per : nu;
+  const double2 ux0 = u_in ? b_u[0] : make_double2(0.0, 0.0);
+  TraceMap map = {1.0, 0.0, 0.0, 0.0};  // of the thread's cells
+  Cell mine;                            // its first cell
+  for (int u = u0; u < u1; ++u) {
+    const Cell c = load(u);
+    if (u == u0) mine = c;
+    const double2 A = trace(c.c1, c.c2), B = trace(times(c.c1, c.t1), times(c.c2, c.t2));
+    map = after(map, {a * A.x, a * A.y, B.x, B.y});
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const TraceMap before = shuffle_up(map, off), both = after(before, map);
+    if (lane >= off) map = both;
+  }
+  if (lane == 63) s_map[wave] = map;
+  __syncthreads();
+  double2 ux = ux0;  // into the wave's first cell, then into the thread's
+  for (int k = 0; k < wave; ++k) ux = apply(s_map[k], ux);
+  const TraceMap before = shuffle_up(map, 1);
+  if (lane > 0) ux = apply(before, ux);
+  for (int u = u0; u < u1; ++u) {
+    const Cell c = u == u0 ? mine : load(u);
+    const double2 X1 = times(c.c1, make_double2(fma(a, ux.x, c.t1.x), fma(a, ux.y, c.t1.y)));
+    const double2 X2 = times(c.c2, make_double2(fma(a, ux.x, c.t2.x), fma(-a, ux.y, c.t2.y)));
+    ux = trace(X1, X2);
+    out[2 * u] = X1;  // the reduction applies the weight
+    out[2 * u + 1] = X2;
+    if (v_out)
+      b_out[1 + u] = make_double2(fma(-kap, X1.y - X2.y, -(X1.x + X2.x)),
+                                  fma(kap, X1.x - X2.x, -(X1.y + X2.y)));
+    if (u_out && u == nu - 1) b_out[0] = ux;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Plan of the sweep
 // ---------------------------------------------------------------------------
@@ -609,7 +740,7 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool 
   auto cost = [](int nu, int nv) {
     return (long long)((nv + 63) / 64) * (nu + (nv < 64 ? nv : 64) - 1);
   };
-  p.swap = cost(ny, nx) < cost(nx, ny) ? 1 : 0;
+  p.swap = cost(ny, nx) < cost(nx, ny) || nx == 1 ? 1 : 0;  // one column: as one row
   p.nu = p.swap ? ny : nx;
   p.nv = p.swap ? nx : ny;
   p.n_strips = (p.nv + 63) / 64;
@@ -707,7 +838,13 @@ hipError_t launch_dg_sweep(const DgArgs& a, hipStream_t s) {
       a.n_blk * a.n_waves < (split ? a.n_strips : 1) || (split && a.n_blk > 1 && !a.hand) ||
       (!split && a.n_blk != 1) || a.nx * a.ny >= 1 << 23)
     return hipErrorInvalidValue;
-  if (table) {
+  if (a.nv == 1 && a.per == 1) {
+    const int waves = std::min(kRowWaves, (a.nu + 63) / 64);
+    if (refl)
+      hipLaunchKernelGGL((k_dg_sweep_row<true>), dim3(4 * a.n_grp), dim3(64 * waves), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_dg_sweep_row<false>), dim3(4 * a.n_grp), dim3(64 * waves), 0, s, a);
+  } else if (table) {
     if (refl) sweep_launch<true, true>(a, lds, s);
     else sweep_launch<true, false>(a, lds, s);
   } else {

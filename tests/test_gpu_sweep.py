@@ -68,3 +68,14 @@ def test_four_directions_per_wave(S, oracle, nx, ny, sn, boundary, per_cell):
     short step and a loose tolerance leave the oracle two or three sweeps."""
     _check(S, oracle, _problem(nx, ny, per_cell, dt=1e-3, sn_order=sn, boundary=boundary,
                                si_tol=1e-4), 1)
+
+
+@pytest.mark.parametrize("per_cell", [False, True])
+@pytest.mark.parametrize("n,boundary", [
+    (2, 15), (64, 0), (65, 13), (128, 7), (1024, 0), (1025, 15), (2500, 14)])
+@pytest.mark.parametrize("along_x", [True, False])
+def test_one_row(S, oracle, n, boundary, along_x, per_cell):
+    """One row or one column of cells: a wave's, a workgroup's, and more cells
+    than a workgroup has threads (two and three for a thread)."""
+    nx, ny = (n, 1) if along_x else (1, n)
+    _check(S, oracle, _problem(nx, ny, per_cell, dt=0.1, sn_order=4, boundary=boundary), 2)
