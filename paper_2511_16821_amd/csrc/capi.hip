@@ -1002,6 +1002,10 @@ static slh_status enqueue_si(slh_solver* s, hipStream_t st, int n_it) {
     }
   } else {
     const DgArgs d = dg_args(s);
+    if (n_it > 0 && dg_row_solve(d, lds_limit())) {
+      HIP_TRY(launch_dg_row_solve(d, n_it, s->si_tol, s->si_max, st));
+      return SLH_OK;
+    }
     for (int it = 0; it < n_it; ++it) {
       HIP_TRY(launch_dg_sweep(d, st));
       HIP_TRY(launch_dg_reduce(d, s->dg_part, s->n_part, s->si_tol, s->si_max, st));

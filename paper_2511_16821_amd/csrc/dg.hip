@@ -619,6 +619,15 @@ __device__ __forceinline__ double2 apply(const TraceMap& m, double2 x) {
   return make_double2(fma(m.ar, x.x, fma(-m.ai, x.y, m.br)), fma(m.ar, x.y, fma(m.ai, x.x, m.bi)));
 }
 
+__device__ __forceinline__ double2 times(double2 p, double2 r) {
+  return make_double2(p.x * r.x - p.y * r.y, p.x * r.y + p.y * r.x);
+}
+// v1 X1 + conj(v1 X2)
+__device__ __forceinline__ double2 trace_of(double2 X1, double2 X2) {
+  return make_double2(fma(-kV1i, X1.y + X2.y, -(X1.x + X2.x)),
+                      fma(kV1i, X1.x - X2.x, -(X1.y - X2.y)));
+}
+
 template <bool REFL>
 __global__ __launch_bounds__(64 * kRowWaves) void k_dg_sweep_row(DgArgs g) {
   if (g.st->si.done) return;
@@ -673,14 +682,6 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_dg_sweep_row(DgArgs g) {
     mode_inverse(a, b, se, c.c1, c.c2);
     return c;
   };
-  auto times = [](double2 p, double2 r) {
-    return make_double2(p.x * r.x - p.y * r.y, p.x * r.y + p.y * r.x);
-  };
-  // v1 X1 + conj(v1 X2)
-  auto trace = [&](double2 X1, double2 X2) {
-    return make_double2(fma(-kap, X1.y + X2.y, -(X1.x + X2.x)),
-                        fma(kap, X1.x - X2.x, -(X1.y - X2.y)));
-  };
 
   const int per = (nu + (int)blockDim.x - 1) / (int)blockDim.x;
   const int u0 = (int)threadIdx.x * per, u1 = u0 + per < nu ? u0 + per : nu;
@@ -690,7 +691,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_dg_sweep_row(DgArgs g) {
   for (int u = u0; u < u1; ++u) {
     const Cell c = load(u);
     if (u == u0) mine = c;
-    const double2 A = trace(c.c1, c.c2), B = trace(times(c.c1, c.t1), times(c.c2, c.t2));
+    const double2 A = trace_of(c.c1, c.c2), B = trace_of(times(c.c1, c.t1), times(c.c2, c.t2));
     map = after(map, {a * A.x, a * A.y, B.x, B.y});
   }
 #pragma unroll
@@ -708,7 +709,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_dg_sweep_row(DgArgs g) {
     const Cell c = u == u0 ? mine : load(u);
     const double2 X1 = times(c.c1, make_double2(fma(a, ux.x, c.t1.x), fma(a, ux.y, c.t1.y)));
     const double2 X2 = times(c.c2, make_double2(fma(a, ux.x, c.t2.x), fma(-a, ux.y, c.t2.y)));
-    ux = trace(X1, X2);
+    ux = trace_of(X1, X2);
     out[2 * u] = X1;  // the reduction applies the weight
     out[2 * u + 1] = X2;
     if (v_out)
@@ -1147,6 +1148,245 @@ hipError_t launch_dg_reduce(const DgArgs& a, double* partials, int n_part, doubl
                             int si_max, hipStream_t s) {
   hipLaunchKernelGGL(k_dg_combine, dim3(n_part), dim3(kRedBlock), 0, s, a, partials, si_tol,
                      si_max);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Source iterations of a short row in one workgroup
+// ---------------------------------------------------------------------------
+// Meshes of one row and up to 128 cells: the whole batch of source iterations
+// in one workgroup, the iterations separated by barriers instead of launches
+// (k_dg_sweep_row and k_dg_combine take 11 us an iteration, nearly all of it
+// launches and memory latency).  Sixteen lanes sweep a direction, K cells each,
+// by a scan of the cells' trace maps along the direction's travel; the four
+// rows of a wave are the four quadrants, wave w takes their direction w (so at
+// most eight per quadrant).  The fluxes meet in LDS, where a thread per node
+// sums them to the next iterate and its source; then every thread takes the
+// same decision from the waves' partial norms.  What bounds an iteration is the
+// issue of the busiest SIMD's two waves: S_4 with reflective sides takes 2.5 us on
+// 16 cells, 6 us on 80 and 10 us on 128 (one launch each for sweep and reduction:
+// 10, 11 and 11.5 us).  More cells or directions keep the separate kernels; c1
+// and c2 would then leave the registers, which cost twice the time.
+constexpr int kRowSolveWaves = 8;
+constexpr int kRowSolveBlock = 64 * kRowSolveWaves;
+constexpr int kRowSolveCells = 128;  // a thread per node
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_or(double otherwise, double v) {
+  const long long o = __double_as_longlong(otherwise), s = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp((int)o, (int)s, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(s >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// The map of the lane `OFF` before in the row of sixteen, else the identity.
+template <int OFF>
+__device__ __forceinline__ TraceMap row_before(const TraceMap& m) {
+  constexpr int kRowShr = 0x110 + OFF;
+  return {dpp_or<kRowShr>(1.0, m.ar), dpp_or<kRowShr>(0.0, m.ai), dpp_or<kRowShr>(0.0, m.br),
+          dpp_or<kRowShr>(0.0, m.bi)};
+}
+
+template <int K>
+__global__ __launch_bounds__(kRowSolveBlock) void k_dg_row_solve(DgArgs g, int n_it, double si_tol,
+                                                                 int si_max) {
+  DevState* const st = g.st;
+  if (st->si.done) return;
+  constexpr int row = 16 * K;  // places of a node's row: cell p at (p % K) * 16 + p / K
+  constexpr double kap = kV1i;
+  extern __shared__ double smem[];
+  double* const s_src = smem;            // nodal source [node][place]
+  double* const s_norm = smem + 4 * row; // partial norms [2][wave]
+  double* const s_phi = s_norm + 2 * kRowSolveWaves;  // sums [wave][quadrant][node][place]
+  const int nu = g.nu, t = threadIdx.x, wave = t >> 6, q = (t >> 4) & 3;
+  const bool back = (q & (g.swap ? 2 : 1)) != 0, vnegative = (q & (g.swap ? 1 : 2)) != 0;
+  const int ubc = g.swap ? g.bc >> 2 : g.bc, vbc = g.swap ? g.bc : g.bc >> 2;
+  const bool refl = g.bc != 0 && g.bnd != nullptr;
+  const bool u_in = refl && (ubc & (back ? 2 : 1)), u_out = refl && (ubc & (back ? 1 : 2));
+  const bool v_in = refl && (vbc & (vnegative ? 2 : 1));
+  const bool v_out = refl && (vbc & (vnegative ? 1 : 2));
+  const size_t n_tr = (size_t)nu + 1;
+  double2* const bnd = reinterpret_cast<double2*>(g.bnd);
+  // the lane's chunk of K cells; lanes and cells in order of travel
+  const int c = back ? 15 - (t & 15) : t & 15;
+  auto cell_of = [&](int k) { return c * K + (back ? K - 1 - k : k); };
+  auto place_of = [&](int k) { return (back ? K - 1 - k : k) * 16 + c; };
+
+  // the sixteen lanes' direction
+  const bool sweeps = wave < g.n_quad;
+  const int m = q * g.n_quad + (sweeps ? wave : 0);
+  const double ox = fabs(g.dir[3 * m]) / g.hx, oy = fabs(g.dir[3 * m + 1]) / g.hy;
+  const double a = g.swap ? oy : ox, b = g.swap ? ox : oy, weight = g.dir[3 * m + 2];
+  const double2* u_from = nullptr;  // its inflow traces in the first buffer
+  const double2* v_from = nullptr;
+  if (refl) {
+    u_from = bnd + (g.swap ? g.refl_y : g.refl_x)[m] * n_tr;
+    v_from = bnd + (g.swap ? g.refl_x : g.refl_y)[m] * n_tr + 1;
+  }
+  const size_t n_bnd = (size_t)g.n_dir * n_tr;  // of a buffer
+  double2 c1[K], c2[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int p = cell_of(k), pc = p < nu ? p : nu - 1;
+    double se;
+    if (g.mat_off)
+      se = g.sig_e_mat[g.mat_off[(size_t)q * nu + (back ? nu - 1 - pc : pc)] >> 5];
+    else
+      se = g.sig_e[pc];
+    mode_inverse(a, b, se, c1[k], c2[k]);
+  }
+
+  // the thread's node
+  const bool node_ok = t < 4 * nu;
+  const int node = t & 3, at = node * row + (t >> 2) % K * 16 + (t >> 2) / K;
+  double phi = 0.0, ssc = 0.0, pp = 0.0, ref = 0.0;
+  if (node_ok) {
+    phi = g.phi_c[t];
+    ssc = g.sig_s[t >> 2] * (0.25 / M_PI);
+    pp = g.phi_post[t >> 2];
+    if (g.phi_pre) ref = g.phi_pre[t >> 2] + pp;
+  }
+  for (int k = t; k < 4 * row; k += kRowSolveBlock) s_src[k] = 0.0;
+  __syncthreads();
+  if (node_ok) s_src[at] = ssc * (phi + pp);
+  __syncthreads();
+
+  const int it0 = st->si.iter;
+  int it = it0, bad = 0, conv = 0, done = 0;
+  double dn2 = st->si.dn2, dn2_prev = 0.0, nrm2 = 0.0;
+  while (it < it0 + n_it && !done) {
+    if (sweeps) {
+      const size_t in = (it + 1) & 1 ? n_bnd : 0;
+      double2* const b_out = bnd + (it & 1 ? n_bnd : 0) + m * n_tr;
+      double2 ux = make_double2(0.0, 0.0);
+      if (u_in) ux = u_from[in];
+      double2 X1[K], X2[K];  // S + b uy, then the cells' modes
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        double s[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          s[j] = s_src[quad_node(q, g.swap, j >> 1, j & 1) * row + place_of(k)];
+        to_modes(s[0], s[1], s[2], s[3], X1[k], X2[k]);
+        if (v_in) {
+          const int p = cell_of(k), pc = p < nu ? p : nu - 1;
+          const double2 uy = v_from[in + (back ? nu - 1 - pc : pc)];
+          X1[k] = make_double2(fma(b, uy.x, X1[k].x), fma(b, uy.y, X1[k].y));
+          X2[k] = make_double2(fma(b, uy.x, X2[k].x), fma(b, uy.y, X2[k].y));
+        }
+      }
+      TraceMap map = {1.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const double2 A = trace_of(c1[k], c2[k]);
+        const double2 B = trace_of(times(c1[k], X1[k]), times(c2[k], X2[k]));
+        const bool ok = cell_of(k) < nu;  // else the identity
+        map = after(map, {ok ? a * A.x : 1.0, ok ? a * A.y : 0.0, ok ? B.x : 0.0,
+                          ok ? B.y : 0.0});
+      }
+      map = after(row_before<1>(map), map);
+      map = after(row_before<2>(map), map);
+      map = after(row_before<4>(map), map);
+      map = after(row_before<8>(map), map);
+      ux = apply(row_before<1>(map), ux);
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const int p = cell_of(k), u = back ? nu - 1 - p : p;
+        X1[k] = times(c1[k], make_double2(fma(a, ux.x, X1[k].x), fma(a, ux.y, X1[k].y)));
+        X2[k] = times(c2[k], make_double2(fma(a, ux.x, X2[k].x), fma(-a, ux.y, X2[k].y)));
+        const bool ok = p < nu;
+        const double2 next = trace_of(X1[k], X2[k]);
+        ux = make_double2(ok ? next.x : ux.x, ok ? next.y : ux.y);
+        if (v_out && ok)
+          b_out[1 + u] = make_double2(fma(-kap, X1[k].y - X2[k].y, -(X1[k].x + X2[k].x)),
+                                      fma(kap, X1[k].x - X2[k].x, -(X1[k].y + X2[k].y)));
+        if (u_out && u == nu - 1) b_out[0] = ux;
+        double f[4];
+        from_modes(X1[k], X2[k], f);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          s_phi[((wave * 4 + q) * 4 + quad_node(q, g.swap, j >> 1, j & 1)) * row + place_of(k)] =
+              weight * f[j];
+      }
+    }
+    __syncthreads();
+    double d2 = 0.0, v2 = 0.0;
+    if (node_ok) {
+      double f[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int w = 0; w < g.n_quad; ++w)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] += s_phi[(w * 4 + k) * 4 * row + at];
+      const double v = (f[0] + f[3]) + (f[1] + f[2]), d = v - phi;
+      phi = v;
+      s_src[at] = ssc * (v + pp);
+      d2 = d * d;
+      v2 = (v + ref) * (v + ref);
+    }
+    d2 = wave_sum(d2);
+    v2 = wave_sum(v2);
+    if ((t & 63) == 0) {
+      s_norm[wave] = d2;
+      s_norm[kRowSolveWaves + wave] = v2;
+    }
+    __syncthreads();
+    dn2_prev = it > 0 ? dn2 : 0.0;
+    dn2 = nrm2 = 0.0;
+    for (int w = 0; w < kRowSolveWaves; ++w) {
+      dn2 += s_norm[w];
+      nrm2 += s_norm[kRowSolveWaves + w];
+    }
+    it += 1;
+    const double dn = sqrt(dn2), nrm = sqrt(nrm2);
+    bad = !isfinite(dn) || !isfinite(nrm);
+    conv = !bad && dn <= si_tol * nrm;
+    done = bad || conv || it >= si_max;
+  }
+  if (node_ok) g.phi_c[t] = phi;
+  if (t == 0) {
+    st->si.dn2_prev = dn2_prev;
+    st->si.dn2 = dn2;
+    st->si.nrm2 = nrm2;
+    st->si.iter = it;
+    st->si.bad = bad;
+    st->si.conv = conv;
+    st->si.done = done;
+  }
+}
+
+static size_t row_solve_lds(const DgArgs& a, int K) {
+  return sizeof(double) * (size_t)(16 * K * 4 * (1 + 4 * a.n_quad) + 2 * kRowSolveWaves);
+}
+
+// Cells per lane of the one-workgroup iteration, 0 where it does not apply.
+static int row_solve_cells(const DgArgs& a) {
+  if (a.nv != 1 || a.per != 1 || a.dnode || a.nu > kRowSolveCells || a.n_quad > kRowSolveWaves)
+    return 0;
+  return (a.nu + 15) / 16;
+}
+
+bool dg_row_solve(const DgArgs& a, size_t lds) {
+  const int K = row_solve_cells(a);
+  return K && row_solve_lds(a, K) <= lds;
+}
+
+template <int K>
+static void row_solve_launch(const DgArgs& a, int n_it, double si_tol, int si_max, hipStream_t s) {
+  hipLaunchKernelGGL((k_dg_row_solve<K>), dim3(1), dim3(kRowSolveBlock), row_solve_lds(a, K), s, a,
+                     n_it, si_tol, si_max);
+}
+
+hipError_t launch_dg_row_solve(const DgArgs& a, int n_it, double si_tol, int si_max,
+                               hipStream_t s) {
+  switch (row_solve_cells(a)) {
+    case 1: row_solve_launch<1>(a, n_it, si_tol, si_max, s); break;
+    case 2: row_solve_launch<2>(a, n_it, si_tol, si_max, s); break;
+    case 3: row_solve_launch<3>(a, n_it, si_tol, si_max, s); break;
+    case 4: row_solve_launch<4>(a, n_it, si_tol, si_max, s); break;
+    case 5: row_solve_launch<5>(a, n_it, si_tol, si_max, s); break;
+    case 6: row_solve_launch<6>(a, n_it, si_tol, si_max, s); break;
+    case 7: row_solve_launch<7>(a, n_it, si_tol, si_max, s); break;
+    case 8: row_solve_launch<8>(a, n_it, si_tol, si_max, s); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

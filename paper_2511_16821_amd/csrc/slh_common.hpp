@@ -607,6 +607,12 @@ bool cg_one_block(long long n);
 hipError_t launch_cg_iteration(const CgArgs& a, double tol, int si_max, hipStream_t s);
 hipError_t launch_cg_to_nodal(const CgArgs& a, double* phi_c, const int* halt, hipStream_t s);
 hipError_t launch_dg_sweep(const DgArgs& a, hipStream_t s);
+// Short one-row meshes: up to n_it source iterations (sweep, reduction and
+// decision) in one workgroup, where dg_row_solve says so (lds: bytes per
+// workgroup).
+bool dg_row_solve(const DgArgs& a, size_t lds);
+hipError_t launch_dg_row_solve(const DgArgs& a, int n_it, double si_tol, int si_max,
+                               hipStream_t s);
 // One reduction of a source iteration: the direction sum of the planes (the
 // groups of a quadrant in order, then the four quadrants) replaces phi_c in
 // place, the next iterate's source is formed, and the residual decides

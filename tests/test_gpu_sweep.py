@@ -79,3 +79,30 @@ def test_one_row(S, oracle, n, boundary, along_x, per_cell):
     than a workgroup has threads (two and three for a thread)."""
     nx, ny = (n, 1) if along_x else (1, n)
     _check(S, oracle, _problem(nx, ny, per_cell, dt=0.1, sn_order=4, boundary=boundary), 2)
+
+
+@pytest.mark.parametrize("nx,ny,sn,kw", [
+    (16, 1, 2, dict(boundary=5)),
+    (1, 33, 4, dict(boundary=15)),
+    (113, 1, 4, dict(boundary=10)),
+    (100, 1, 4, dict(si_batch=3)),              # batches that end before the iteration does
+    (32, 1, 4, dict(boundary=4, si_norm=1)),    # the whole flux as the reference
+    (96, 1, 8, dict(boundary=13)),              # more directions than one workgroup takes
+    (128, 1, 10, dict(boundary=12, si_accel=1)),  # with the diffusion correction
+])
+def test_short_row(S, oracle, nx, ny, sn, kw):
+    """Short rows, whose iterations run in one workgroup, and their limits."""
+    kw = dict(kw)
+    batch = kw.pop("si_batch", 0)
+    p = _problem(nx, ny, True, dt=0.1, sn_order=sn, **kw)
+    log("short row", nx, ny, sn, kw, batch)
+    o = oracle.HybridOracle(p)
+    s = S.Solver(p)
+    if batch:
+        s.set_si_batch(batch)
+    for _ in range(2):
+        r = o.step()
+        s.advance(1)
+        compare_step(S, s, r)
+        assert s.get_stats()["si_iterations"] == r["si_iters"]
+    s.destroy()
