@@ -133,9 +133,10 @@ enum { END_NONE = 0, END_CENSUS, END_LEAK, END_CUTOFF };
 // lanes are free, or none runs.  (The order of a wave's work does not show in
 // the results.)  1024^2, N_s = 3, 2e8 histories: passes of 27.1 and 21.4 ms
 // served at once, 21.9 / 19.9 with 12 free and 8 colliding lanes, 20.5 / 18.6
-// as here, 22.3 / 18.7 with 32 and 24; 30x50 steady, where a wave has 16
-// histories: 0.38 ms at once, 0.43 with twelve colliding lanes, 0.34 with a
-// quarter of the live ones.
+// as here, 22.3 / 18.7 with 32 and 24 (all before the segment's branches went;
+// since then 17.4 / 15.4, 17.9 / 15.9 with 18 free, and a third colliding the
+// same); 30x50 steady, where a wave has 16 histories: 0.38 ms at once, 0.43
+// with twelve colliding lanes, 0.34 with a quarter of the live ones.
 enum { LN_IDLE = 0, LN_RUN, LN_COL, LN_END };
 constexpr int kRefillAt = 24;
 constexpr int kCollideShare = 4;
@@ -644,16 +645,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<
         ls = LN_RUN;
       }
     }
-    if (!__any(ls == LN_RUN)) {  // no lane runs, collides or ends, and no work is left
-      if (p_word) to_tally(p_word, p_val);  // the last pending add
-      tc_flush();
-      break;
-    }
-    // this iteration's tally word and value (none for a lane that does not run)
-    unsigned t_word = 0u;
-    unsigned long long t_val = 0ull;
+    if (!__any(ls == LN_RUN)) break;  // no lane runs, collides or ends, and no work is left
+    // One segment of each running lane.  The passes are bound by the issue of
+    // vector instructions, and a branch here would be taken by some lane of the
+    // wave and, where its sides leave different values, cost a register copy per
+    // value: the event is a set of lane masks, and the new state is selected by
+    // them (290 -> 190 vector instructions a segment; 1024^2, 1e8 particles,
+    // N_s = 3: passes of 20.1 and 18.1 -> 17.4 and 15.4 ms; 256^2 FP32, 1e7: 0.86
+    // and 0.67 -> 0.76 and 0.56).
     if (ls == LN_RUN) {
-      // ---- one segment ----
       const int cell = iy * a.nx + ix;
       const R ss = m_cur.x, sa = m_cur.y, stt = sa + ss;
       const bool pre = n < (a.ns_cell ? a.ns_cell[cell] : n_lim);
@@ -661,106 +661,93 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<
       if (d_cen < (R)0) d_cen = (R)0;
       R d_col = INF;
       if (pre && ss > (R)0) { d_col = tau / ss; if (d_col < (R)0) d_col = (R)0; }
-      R d_x = INF, d_y = INF;
-      if (ox > (R)0) d_x = (hx - px) * iox; else if (ox < (R)0) d_x = -px * iox;
-      if (oy > (R)0) d_y = (hy - py) * ioy; else if (oy < (R)0) d_y = -py * ioy;
+      const bool right = ox > (R)0, up = oy > (R)0;
+      R d_x = ((right ? hx : (R)0) - px) * iox, d_y = ((up ? hy : (R)0) - py) * ioy;
       if (d_x < (R)0) d_x = (R)0;
       if (d_y < (R)0) d_y = (R)0;
+      if (ox == (R)0) d_x = INF;
+      if (oy == (R)0) d_y = INF;
       R l = d_cen;
-      int ev = EV_CENSUS;
-      if (d_col < l) { l = d_col; ev = EV_COLLIDE; }
-      if (d_x < l) { l = d_x; ev = EV_XFACE; }
-      if (d_y < l) { l = d_y; ev = EV_YFACE; }
+      const bool by_col = d_col < l;
+      if (by_col) l = d_col;
+      const bool by_x = d_x < l;
+      if (by_x) l = d_x;
+      const bool cross_y = d_y < l;
+      if (cross_y) l = d_y;
+      const bool cross_x = by_x && !cross_y;
+      const bool collide = by_col && !by_x && !cross_y;
+      const bool census = !by_col && !by_x && !cross_y;
 
       const R sig = pre ? sa : stt;
       const R z = sig * l;
       const R em = expm1(-z);  // e^{-z} - 1
       const R contrib = (sig > (R)0) ? w * (-em) / sig : w * l;
-      // the segment's tally word, added at the end of the iteration
-      t_word = 1u + (KIND == 2 ? (unsigned)cell : 2u * (unsigned)cell + (pre ? 0u : 1u));
-      {
-        const double cd = (double)contrib;
-        t_val = (unsigned long long)fix_round(cd, inv_T);
-        acc_abs += (double)sa * cd;
-        if (!pre) acc_sca += (double)ss * cd;
-      }
+      const unsigned t_word =
+          1u + (KIND == 2 ? (unsigned)cell : 2u * (unsigned)cell + (pre ? 0u : 1u));
+      const double cd = (double)contrib;
+      const unsigned long long t_val = (unsigned long long)fix_round(cd, inv_T);
+      acc_abs += (double)sa * cd;
+      if (!pre) acc_sca += (double)ss * cd;
       w = Real<R>::attenuate(w, z, em);
       if (pre && ss > (R)0) tau -= ss * l;
       trel += l / c;
       seg_p++;
-
-      end = END_NONE;
-      if (ev == EV_CENSUS) {
-        px += ox * l;
-        py += oy * l;
-        end = END_CENSUS;
-      } else if (ev == EV_COLLIDE) {
-        px += ox * l;
-        py += oy * l;
-        ls = LN_COL;
-      } else if (ev == EV_XFACE) {
-        // a reflective side mirrors the direction; the history stays in its cell
-        py += oy * l;
-        if (ox > (R)0) {
-          if (ix == a.nx - 1 && (a.bc & 2)) { px = hx; ox = -ox; iox = -iox; }
-          else { ix++; px = (R)0; }
-        } else {
-          if (ix == 0 && (a.bc & 1)) { px = (R)0; ox = -ox; iox = -iox; }
-          else { ix--; px = hx; }
-        }
-        if (ix < 0 || ix >= a.nx) end = END_LEAK;
-      } else {
-        px += ox * l;
-        if (oy > (R)0) {
-          if (iy == a.ny - 1 && (a.bc & 8)) { py = hy; oy = -oy; ioy = -ioy; }
-          else { iy++; py = (R)0; }
-        } else {
-          if (iy == 0 && (a.bc & 4)) { py = (R)0; oy = -oy; ioy = -ioy; }
-          else { iy--; py = hy; }
-        }
-        if (iy < 0 || iy >= a.ny) end = END_LEAK;
-      }
-      if (end == END_NONE && fabs(w) < w_cut) end = END_CUTOFF;
-      if (end == END_NONE && seg_p >= a.max_segments) { end = END_CUTOFF; lane_killed++; }
       lane_seg++;
+
+      const R nx_p = px + ox * l, ny_p = py + oy * l;
+      // a reflective side mirrors the direction; the history stays in its cell
+      bool mir_x = false, mir_y = false;
+      if (a.bc) {
+        mir_x = cross_x && ix == (right ? a.nx - 1 : 0) && (a.bc & (right ? 2 : 1));
+        mir_y = cross_y && iy == (up ? a.ny - 1 : 0) && (a.bc & (up ? 8 : 4));
+        ox = mir_x ? -ox : ox;
+        iox = mir_x ? -iox : iox;
+        oy = mir_y ? -oy : oy;
+        ioy = mir_y ? -ioy : ioy;
+      }
+      px = cross_x ? (right != mir_x ? (R)0 : hx) : nx_p;
+      py = cross_y ? (up != mir_y ? (R)0 : hy) : ny_p;
+      ix += cross_x && !mir_x ? (right ? 1 : -1) : 0;
+      iy += cross_y && !mir_y ? (up ? 1 : -1) : 0;
+      const bool leak = (unsigned)ix >= (unsigned)a.nx || (unsigned)iy >= (unsigned)a.ny;
+      const bool killed = seg_p >= a.max_segments;
+      const bool over = census || leak, cut = fabs(w) < w_cut;
+      lane_killed += killed && !over && !cut ? 1u : 0u;
+      end = census ? END_CENSUS : (leak ? END_LEAK : END_CUTOFF);
+      ls = over || cut || killed ? LN_END : (collide ? LN_COL : LN_RUN);
       // the next cell's material before the tally atomic: memory operations
       // complete in issue order, so the wait for the material at the next
       // segment does not include the atomic's round trip
-      if (end == END_NONE && ev >= EV_XFACE) m_cur = Real<R>::mat(a, iy * a.nx + ix);
+      if (ls == LN_RUN) m_cur = Real<R>::mat(a, iy * a.nx + ix);
 
-      if (end != END_NONE) ls = LN_END;
-    }
-    // A lane's consecutive adds to one word (segments that end in a
-    // collision or at the census stay in their cell) are summed in registers;
-    // the pending sum goes to the wave's cache when the lane moves to another
-    // word.
-    unsigned f_word = 0u;
-    unsigned long long f_val = 0ull;
-    if (t_word) {
-      if (t_word == p_word) {
-        p_val += t_val;
-      } else {
-        f_word = p_word;
-        f_val = p_val;
-        p_word = t_word;
-        p_val = t_val;
+      // A lane's consecutive adds to one word (segments that end in a
+      // collision or at the census stay in their cell) are summed in registers;
+      // the pending sum goes to the wave's cache when the lane moves to another
+      // word.
+      const bool same = t_word == p_word;
+      const unsigned f_word = same ? 0u : p_word;
+      const unsigned long long f_val = p_val;
+      p_val = (same ? p_val : 0ull) + t_val;
+      p_word = t_word;
+      if (f_word) {
+        const int slot = (int)((f_word * 0x9E3779B1u) >> (32 - kTcBits<R>));
+        unsigned tg = tc_tag[slot];
+        if (tg == 0u) {
+          const unsigned old = atomicCAS(&tc_tag[slot], 0u, f_word);
+          tg = old == 0u ? f_word : old;
+        }
+        if (tg == f_word) atomicAdd(&tc_sum[slot], f_val);
+        else to_tally(f_word, f_val);
       }
-    }
-    if (f_word) {
-      const int slot = (int)((f_word * 0x9E3779B1u) >> (32 - kTcBits<R>));
-      unsigned tg = tc_tag[slot];
-      if (tg == 0u) {
-        const unsigned old = atomicCAS(&tc_tag[slot], 0u, f_word);
-        tg = old == 0u ? f_word : old;
-      }
-      if (tg == f_word) atomicAdd(&tc_sum[slot], f_val);
-      else to_tally(f_word, f_val);
     }
     if (++tc_it == kTcFlush) {
       tc_it = 0;
       tc_flush();
     }
   }
+
+  if (p_word) to_tally(p_word, p_val);  // the last pending add
+  tc_flush();
 
   // wave totals of the integer counters, one atomic per wave
   unsigned long long v0 = lane_seg, v1 = lane_hist, v2 = lane_alive, v3 = lane_killed;
