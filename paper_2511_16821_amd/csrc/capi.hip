@@ -520,7 +520,7 @@ struct slh_solver {
   void* stage_mem = nullptr;
   void* src_mem = nullptr;  // source bank of the current pass
   uint8_t* alive = nullptr;
-  int32_t* kcell = nullptr;  // cell of each kept candidate
+  int32_t* kcell = nullptr;  // cell of each census candidate
   long long *tcount = nullptr, *tincl = nullptr, *scan_i = nullptr;
   // census ordering: (cell, slot) pairs and their sort buffers, the radix
   // histograms, cohort starts per cell, and each bank's cohort ranks
@@ -887,6 +887,7 @@ static PassArgs pass_args(slh_solver* s, int kind) {
     a.src64 = (SrcRec<double>*)s->src_mem;
   }
   a.alive = s->alive;
+  a.cell = s->kcell;
   a.out_src_base = s->z.cap;
   a.Ta = kind == 1 ? s->Tpre : s->TR;
   a.Tb = kind == 1 ? s->Tpost : s->TR;
@@ -1088,10 +1089,10 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
       const int odd = radix_passes(nc) & 1;  // the sorted pairs end in buffer odd
       if (z.fp32)
         HIP_TRY(launch_census_keep(s->alive, (const StageRec<float>*)s->stage_mem, z.n_cand,
-                                   p.seed, s->st, s->tcount, s->kcell, st));
+                                   p.seed, s->st, s->tcount, st));
       else
         HIP_TRY(launch_census_keep(s->alive, (const StageRec<double>*)s->stage_mem, z.n_cand,
-                                   p.seed, s->st, s->tcount, s->kcell, st));
+                                   p.seed, s->st, s->tcount, st));
       HIP_TRY(scan_inclusive_i64(s->tcount, s->tincl, tiles, s->scan_i, &s->st->halt, st));
       HIP_TRY(launch_census_keys(s->kcell, s->alive, s->tcount, s->tincl, z.n_cand, z.cap,
                                  s->skey[0], s->sval[0], s->st, st));

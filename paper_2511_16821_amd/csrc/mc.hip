@@ -446,6 +446,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<
   const double inv_T = wave_uniform(st->inv_T);
   const double inv_W = wave_uniform(st->inv_W);
   const uint64_t step = (uint64_t)wave_uniform((long long)st->step);
+  const uint64_t thin_stream = KIND == 2 ? thin_stream_seed(a.seed, step) : 0ull;
   const R hx = (R)a.hx, hy = (R)a.hy, dt = (R)a.dt, c = (R)a.c;
   const R INF = Real<R>::inf();
   const StageRec<R>* const bin = Real<R>::in(a);
@@ -524,7 +525,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<
         if (KIND == 2 && end == END_CENSUS && a.keep_census) {
           const long long slot = from_census ? g : a.out_src_base + (g - n_in);
           Real<R>::stage(bout + slot, px, py, ox, oy, w, hid, iy * a.nx + ix);
-          a.alive[slot] = 1;
+          a.alive[slot] =
+              (uint8_t)(kAliveBit | (unsigned)(mix64(thin_stream ^ hid) >> kThinShift));
+          a.cell[slot] = iy * a.nx + ix;
           lane_alive++;
         }
         // fold the history's balance into the block (fixed point, exact)

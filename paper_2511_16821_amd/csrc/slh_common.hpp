@@ -34,6 +34,15 @@ __host__ __device__ __forceinline__ uint64_t stream_seed(uint64_t seed, uint64_t
   return mix64(h ^ cohort);
 }
 
+// The thinning keys' stream, (step, pass 2, population 2): a candidate's key
+// is mix64(stream ^ history id).  Its alive byte is kAliveBit and the key's
+// seven leading bits.
+__host__ __device__ __forceinline__ uint64_t thin_stream_seed(uint64_t seed, uint64_t step) {
+  return stream_seed(seed, step, 2u, 2u, 0ull);
+}
+constexpr unsigned kAliveBit = 128u;
+constexpr int kThinShift = 57;
+
 __device__ __forceinline__ uint32_t nested_scramble(uint32_t x, uint32_t s) {
   x = __builtin_bitreverse32(x);
   x += s;
@@ -450,7 +459,8 @@ struct PassArgs {
   StageRec<float>* out32;
   SrcRec<double>* src64;
   SrcRec<float>* src32;
-  uint8_t* alive;
+  uint8_t* alive;          // of each output slot: 0, or kAliveBit and the key's prefix
+  int32_t* cell;           // and its cell
   long long out_src_base;  // slot of source particle s is out_src_base + s
   // tallies: kTallyCopies private copies of one fixed-point word per cell
   // (word stride kTallyStride), copy c at offset c * copy_stride, split evenly
@@ -672,12 +682,10 @@ hipError_t launch_thin_params(DevState* st, long long cap, long long margin, hip
 // active, its key test), stored in place of its alive byte, and the kept
 // count of each tile (tcount, census_tiles(n) entries).
 long long census_tiles(long long n);
-// It also copies each kept candidate's cell into cell (n entries; 0 for the
-// others), read by the ordering keys in place of the records.
 template <typename R>
 hipError_t launch_census_keep(uint8_t* alive, const StageRec<R>* stage, long long n,
                               uint64_t seed, const DevState* st, long long* tcount,
-                              int32_t* cell, hipStream_t s);
+                              hipStream_t s);
 // The census bank at t_{n+1} (kept candidates, first cap in slot order,
 // ordered by cell and within a cell by slot): (cell, slot) pairs of the kept
 // candidates in slot order, then radix_sort_pairs by cell, then the gather of

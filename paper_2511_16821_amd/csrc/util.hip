@@ -589,44 +589,56 @@ long long census_tiles(long long n) {
   return (n + tile - 1) / tile;
 }
 
-// One tile of candidates per block, read in rounds of 256 (slot
-// base + r 256 + t in round r, thread t): each candidate's keep decision in
-// place of its alive byte, the tile's kept count, and the cell of each kept
-// candidate in a plain array (history id and cell share a 32-byte sector of
-// the record, so the copy costs no extra read, and the ordering keys then
-// read 4 bytes a slot instead of the records).
+// One tile of candidates per block, `rounds` successive ones per thread: each
+// candidate's keep decision in place of its alive byte, and the tile's kept
+// count.  The tracking pass left the seven leading bits of each candidate's
+// thinning key with its alive bit, which decide for all candidates but those
+// of the threshold's own prefix, 1 in 128; only these read their record for
+// the history id (2e7 candidates, 256^2: 307 us when every candidate's record
+// was read for its id and cell, below 15 us now; the tracking pass pays 32 us
+// for the bits and the cells).
 template <typename R>
 __global__ __launch_bounds__(256) void k_census_keep(uint8_t* __restrict__ alive,
                                                      const StageRec<R>* __restrict__ stage,
                                                      long long n, uint64_t seed,
                                                      const DevState* st,
-                                                     long long* __restrict__ tcount,
-                                                     int32_t* __restrict__ cell, int rounds) {
+                                                     long long* __restrict__ tcount, int rounds) {
   if (st->halt) return;
   __shared__ int s_c[4];
-  // the thinning keys' stream: (step, pass 2, population 2)
-  const uint64_t thin_stream = stream_seed(seed, st->step, 2u, 2u, 0ull);
+  const uint64_t thin_stream = thin_stream_seed(seed, st->step);
   const int act = st->thin_active;
-  const unsigned long long mant = st->thin_mant;
-  const int rs = st->thin_rshift;
-  const long long base = (long long)blockIdx.x * 256 * rounds;
+  // a key is kept if it is below mant 2^rshift (below 2^64 when thinning)
+  const unsigned long long limit = act ? st->thin_mant << st->thin_rshift : 0ull;
+  const unsigned prefix = (unsigned)(limit >> kThinShift);
+  auto keep = [&](long long i, unsigned b) {
+    if (!b || !act) return b ? 1u : 0u;
+    const unsigned p = b & (kAliveBit - 1u);
+    if (p != prefix) return p < prefix ? 1u : 0u;
+    return mix64(thin_stream ^ stage[i].hid) < limit ? 1u : 0u;
+  };
+  const long long i0 = ((long long)blockIdx.x * 256 + threadIdx.x) * rounds;
   int cnt = 0;
-  for (int r = 0; r < rounds; ++r) {
-    const long long i = base + r * 256 + threadIdx.x;
-    if (i >= n) break;
-    int f = alive[i] ? 1 : 0;
-    int c = 0;
-    if (f) {
-      c = stage[i].cell;
-      if (act) {
-        const unsigned long long key = mix64(thin_stream ^ stage[i].hid);
-        const unsigned long long top = rs >= 64 ? 0ull : (key >> rs);
-        f = top < mant ? 1 : 0;
-        alive[i] = (uint8_t)f;
+  if (rounds == 16 && i0 + 16 <= n) {
+    uint4 v = reinterpret_cast<const uint4*>(alive)[i0 >> 4];
+    unsigned* const w = reinterpret_cast<unsigned*>(&v);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      unsigned o = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned f = keep(i0 + 4 * k + e, w[k] >> 8 * e & 255u);
+        o |= f << 8 * e;
+        cnt += (int)f;
       }
+      w[k] = o;
     }
-    cell[i] = f ? c : 0;
-    cnt += f;
+    reinterpret_cast<uint4*>(alive)[i0 >> 4] = v;
+  } else {
+    for (long long i = i0; i < i0 + rounds && i < n; ++i) {
+      const unsigned f = keep(i, alive[i]);
+      alive[i] = (uint8_t)f;
+      cnt += (int)f;
+    }
   }
   for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
   if (__lane_id() == 0) s_c[threadIdx.x >> 6] = cnt;
@@ -637,18 +649,17 @@ __global__ __launch_bounds__(256) void k_census_keep(uint8_t* __restrict__ alive
 template <typename R>
 hipError_t launch_census_keep(uint8_t* alive, const StageRec<R>* stage, long long n,
                               uint64_t seed, const DevState* st, long long* tcount,
-                              int32_t* cell, hipStream_t s) {
+                              hipStream_t s) {
   const long long tiles = census_tiles(n > 0 ? n : 1);
   hipLaunchKernelGGL(k_census_keep<R>, dim3((unsigned)tiles), dim3(256), 0, s, alive, stage, n,
-                     seed, st, tcount, cell, keep_rounds(n));
+                     seed, st, tcount, keep_rounds(n));
   return hipGetLastError();
 }
 template hipError_t launch_census_keep<double>(uint8_t*, const StageRec<double>*, long long,
-                                               uint64_t, const DevState*, long long*, int32_t*,
+                                               uint64_t, const DevState*, long long*,
                                                hipStream_t);
 template hipError_t launch_census_keep<float>(uint8_t*, const StageRec<float>*, long long,
-                                              uint64_t, const DevState*, long long*, int32_t*,
-                                              hipStream_t);
+                                              uint64_t, const DevState*, long long*, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // The census bank at t_{n+1}: the kept candidates (first cap in slot order)
@@ -667,7 +678,7 @@ __device__ __forceinline__ long long census_count(const long long* incl_last, lo
 // The tile's kept candidates, in slot order, at their places among all kept
 // ones (the kept of earlier tiles first; rounds in order, the waves of a
 // round in order, lanes in order), the first cap of them only; their cells
-// come from the array the keep decisions left.
+// come from the array the tracking pass left.
 __global__ __launch_bounds__(256) void k_census_keys(const int32_t* __restrict__ cell,
                                                      const uint8_t* __restrict__ keep,
                                                      const long long* __restrict__ tcount,
@@ -881,6 +892,12 @@ int census_compact_blocks(long long n) {
   return (int)(b < kCensusBlocks ? (b < 1 ? 1 : b) : kCensusBlocks);
 }
 
+// An FP64 record moves as the 16-byte parts of four neighbouring lanes, so that
+// an access takes whole sectors of the records that it touches and writes a
+// contiguous kilobyte (1e7 records of 64 bytes: 417 us with a record per lane,
+// 325 now, 3.9 TB/s read and written; two or four groups of 64 records in flight
+// the same).  FP32 records, half a sector's pair of parts, are faster with a
+// record per lane (205 against 230 us).
 template <typename R>
 __global__ __launch_bounds__(256) void k_census_gather(const StageRec<R>* __restrict__ src,
                                                        const uint32_t* __restrict__ vals,
@@ -893,13 +910,35 @@ __global__ __launch_bounds__(256) void k_census_gather(const StageRec<R>* __rest
   const R f = (R)st->thin_factor;
   const long long count = census_count(incl_last, cap);
   double mx = 0.0;
-  for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < count;
-       k += (long long)gridDim.x * blockDim.x) {
-    StageRec<R> rec = src[vals[k]];
-    const R w = rec.w * f;
-    rec.w = w;
-    dst[k] = rec;
-    mx = fmax(mx, fabs((double)w));
+  if constexpr (sizeof(R) == 8) {
+    const double2* const in = reinterpret_cast<const double2*>(src);
+    double2* const out = reinterpret_cast<double2*>(dst);
+    const int lane = __lane_id(), part = lane & 3;  // px py | ox oy | w hid | cell
+    for (long long k0 = (long long)blockIdx.x * blockDim.x + (threadIdx.x & ~63u); k0 < count;
+         k0 += (long long)gridDim.x * blockDim.x) {  // the wave's 64 records
+      const uint32_t slot = vals[k0 + lane < count ? k0 + lane : count - 1];
+      double2 v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        v[j] = in[(size_t)__shfl(slot, 16 * j + (lane >> 2)) * 4 + part];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (part == 2) {
+          v[j].x *= f;
+          mx = fmax(mx, fabs(v[j].x));
+        }
+        if (k0 + 16 * j + (lane >> 2) < count) out[k0 * 4 + 64 * j + lane] = v[j];
+      }
+    }
+  } else {
+    for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < count;
+         k += (long long)gridDim.x * blockDim.x) {
+      StageRec<R> rec = src[vals[k]];
+      const R w = rec.w * f;
+      rec.w = w;
+      dst[k] = rec;
+      mx = fmax(mx, fabs((double)w));
+    }
   }
   for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
   if (__lane_id() == 0) s_mx[threadIdx.x >> 6] = mx;
