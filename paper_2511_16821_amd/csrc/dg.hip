@@ -761,15 +761,22 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool 
               dg_sweep_lds_bytes(p, (int)std::min<long long>(n_mat, 1 << 20), refl) <= lds;
     return dg_sweep_lds_bytes(p, p.table ? (int)n_mat : 0, refl) <= lds;
   };
-  // Four directions per wave quarter the planes, which a sweep writes at about
-  // 6 TB/s and the reduction reads at 3.2, but a step takes 0.55 us instead of
-  // 0.16 (times the waves that share a SIMD).  1024^2, S_16: 1.2 + 0.6 ms per
-  // sweep and reduction against 2.45 + 2.65 ms with one direction; 256^2, S_8:
-  // 0.29 + 0.01 ms estimated against 0.09 + 0.045 measured.
+  // Four directions per wave quarter the planes' traffic, but a step takes 0.5
+  // us.  With one direction it takes 0.16, and 0.037 (0.045 above eight) times
+  // the strips of the direction where these keep their compute unit busy: the
+  // eight of 512 rows take 0.29 us a step.  Planes that stay in the 256 MB
+  // last-level cache cost little; past it the reduction reads 3.4 TB/s and the
+  // sweep writes 2 to 4.  Measured sweep and reduction with one and with four
+  // (44 meshes of 192^2 to 1024^2, 1024 x 128 and 655 x 53, S_4 to S_16; this
+  // estimate's choice is within 5% of the better one): 256^2 S_8 0.13 against
+  // 0.26 ms, S_16 0.35 / 0.28; 384^2 S_8 0.32 / 0.41, S_12 0.54 / 0.43; 512^2 S_8
+  // 0.58 / 0.57, S_16 1.30 / 0.66; 1024^2 S_4 1.77 / 1.19, S_16 5.2 / 1.8.
   auto us = [&]() {
-    const double share = p.per == kDgSplit || p.n_waves <= 8 ? 1.0 : p.n_waves / 8.0;
-    return (p.nu + 72.0 * p.n_strips) * (p.per == kDgSplit ? 0.55 : 0.16 * share) +
-           128.0 * p.n_grp * (double)nc * (1.0 / 6e6 + 1.0 / 3.2e6);
+    const bool four = p.per == kDgSplit;
+    const double busy = (p.n_waves <= 8 ? 0.037 : 0.045) * p.n_waves;
+    const double step = four ? 0.5 : (busy > 0.16 ? busy : 0.16);
+    const double mb = 128e-6 * p.n_grp * (double)nc, far = mb > 200.0 ? mb - 200.0 : 0.0;
+    return (p.nu + 72.0 * p.n_strips) * step + (four ? 0.2 : 0.18) * mb + (four ? 0.1 : 0.37) * far;
   };
   if (n_dir >= 4 * kDgSplit && fill(kDgSplit)) {
     const double split_us = us();

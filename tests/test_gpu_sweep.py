@@ -106,3 +106,11 @@ def test_short_row(S, oracle, nx, ny, sn, kw):
         compare_step(S, s, r)
         assert s.get_stats()["si_iterations"] == r["si_iters"]
     s.destroy()
+
+
+@pytest.mark.parametrize("nx,ny,sn,boundary,per_cell", [
+    (256, 250, 16, 9, False),  # four strips: one workgroup per group, no hand-over
+    (770, 768, 4, 0, True)])   # one group of four directions per quadrant
+def test_four_directions_one_block_or_group(S, oracle, nx, ny, sn, boundary, per_cell):
+    _check(S, oracle, _problem(nx, ny, per_cell, dt=1e-3, sn_order=sn, boundary=boundary,
+                               si_tol=1e-4), 1)
