@@ -254,10 +254,10 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   const int n_waves = blockDim.x >> 6;
-  // LDS: table [n_mat + 1][PER] of c1, c2 (SPLIT: 1/|z1|^2, 1/|z2|^2 for c =
-  // conj(z)/|z|^2, half the space, and [n_mat + 1] sigma_e) | row of v-face traces [nu
-  // + kDgPad][PER] and room for idle lanes' traces | reflective sides: traces of the u side [PER][rows] | progress
-  // word of each strip
+  // LDS: row of v-face traces [nu + kDgPad][PER] and room for idle lanes' traces |
+  // reflective sides: traces of the u side [PER][rows] | table [n_mat + 1][PER] of
+  // c1, c2 (SPLIT: 1/|z1|^2, 1/|z2|^2 for c = conj(z)/|z|^2, half the space, and
+  // [n_mat + 1] sigma_e) | progress word of each strip
   const int n_row = TABLE ? g.n_mat + 1 : 0;
   const int n_col = nu + kDgPad;
   const int n_xf = SPLIT ? 64 * n_waves : nv;  // rows of the workgroup
@@ -312,8 +312,10 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
   const int it = REFL ? g.st->si.iter : 0;
   const bool unegative = (q & (g.swap ? 2 : 1)) != 0, vnegative = (q & (g.swap ? 1 : 2)) != 0;
   const int ubc = g.swap ? g.bc >> 2 : g.bc, vbc = g.swap ? g.bc : g.bc >> 2;
-  const bool u_in = REFL && (ubc & (unegative ? 2 : 1)), u_out = REFL && (ubc & (unegative ? 1 : 2));
-  const bool v_in = REFL && (vbc & (vnegative ? 2 : 1)), v_out = REFL && (vbc & (vnegative ? 1 : 2));
+  const bool u_in = REFL && (ubc & (unegative ? 2 : 1));
+  const bool u_out = REFL && (ubc & (unegative ? 1 : 2));
+  const bool v_in = REFL && (vbc & (vnegative ? 2 : 1));
+  const bool v_out = REFL && (vbc & (vnegative ? 1 : 2));
   const int* const ru = g.swap ? g.refl_y : g.refl_x;
   const int* const rv = g.swap ? g.refl_x : g.refl_y;
   const double2* const b_in =
@@ -482,8 +484,8 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
       } else if (s > s0 && t0 < nu) {
         // the strip before has left the traces of these columns
         const int need = t0 + AHEAD < nu ? t0 + AHEAD : nu;
-        while (__hip_atomic_load(&prog[s - s0 - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <
-               need)
+        while (__hip_atomic_load(&prog[s - s0 - 1], __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP) < need)
           __builtin_amdgcn_s_sleep(1);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
       }
@@ -1039,7 +1041,8 @@ __global__ __launch_bounds__(kRedBlock) void k_dg_combine(DgArgs g, double* part
   const int n = g.nx * g.ny;
   const int lane = threadIdx.x & 63;
   const int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const double2* const plane = reinterpret_cast<const double2*>(g.psi) + (size_t)q * g.n_grp * 2 * n;
+  const double2* const plane =
+      reinterpret_cast<const double2*>(g.psi) + (size_t)q * g.n_grp * 2 * n;
   const double* const dir = g.dir + 3 * (size_t)q * g.n_quad;
   const int n_tiles = dg_tiles(g);
   double dsum = 0.0, nsum = 0.0;

@@ -413,8 +413,8 @@ __global__ __launch_bounds__(256) void k_emit(PassArgs a) {
 }
 
 template <typename R, int KIND>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<R>))) void k_mc_pass(
-    PassArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPassWaves<R>)))
+void k_mc_pass(PassArgs a) {
   if (a.st->halt) return;
   constexpr int kTcSlots = 1 << kTcBits<R>;
   // Block balance in kBalCopies LDS copies picked by lane: with a per-lane
