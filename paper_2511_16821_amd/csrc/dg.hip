@@ -977,19 +977,18 @@ __device__ __forceinline__ void add_norms(double4 v, double4 d, double r, double
 // for eight lanes, 40 us; tiles of 16 x 16, 33 us).
 constexpr int kNodeRow = kRedCells + 1;  // LDS stride of a node: [node][cell]
 
-// Tiles of the mesh, and tile cell of lane l in quadrant q: column (d - e) mod
-// 8 of the u axis and row e of the v axis, d and e the lane's octal digits,
-// u and v mirrored as the quadrant is.
+// Tile cell of lane l in quadrant q: column (d - e) mod 8 of the u axis and row e
+// of the v axis, d and e the lane's octal digits, u and v mirrored as the quadrant
+// is.
 struct TileCell {
   int cell, slot, at;  // the cell, its slot, its place in the tile (row-major)
   bool ok;
 };
-__device__ __forceinline__ TileCell tile_cell(const DgArgs& g, int tile, int q, int lane) {
-  const int tx = (g.nx + kTile - 1) / kTile;
+__device__ __forceinline__ TileCell tile_cell(const DgArgs& g, int2 tile, int q, int lane) {
   const int e = lane % kTile, d = lane / kTile, f = (d - e) & (kTile - 1);
   const int x = g.swap ? e : f, y = g.swap ? f : e;
   const int i = (q & 1) ? kTile - 1 - x : x, j = (q & 2) ? kTile - 1 - y : y;
-  const int ci = tile % tx * kTile + i, cj = tile / tx * kTile + j;
+  const int ci = tile.x * kTile + i, cj = tile.y * kTile + j;
   TileCell t;
   t.ok = ci < g.nx && cj < g.ny;
   // a real cell for every lane's loads
@@ -1002,6 +1001,22 @@ __device__ __forceinline__ TileCell tile_cell(const DgArgs& g, int tile, int q, 
 
 __device__ __forceinline__ int dg_tiles(const DgArgs& g) {
   return ((g.nx + kTile - 1) / kTile) * ((g.ny + kTile - 1) / kTile);
+}
+
+// The k-th tile.  A slot row's run of eight cells belongs to two tiles that are
+// neighbours along u, and its cache lines to neighbours along v: where every
+// tile has its block, the blocks of an XCD (k mod 8) take a run of tiles in the
+// order of v, then u (333 x 187, S_8: 30 -> 24 us a reduction, 128^2, S_16: 31 ->
+// 29, 140^2, S_12: 21 -> 20).  On larger meshes the rows' order is the better
+// one: the runs' starts, an eighth of a power of two apart, meet in the same
+// memory channels (1024^2: 0.46 against 0.51 ms; patches of 8 x 8 tiles 0.47).
+__device__ __forceinline__ int2 dg_tile(const DgArgs& g, int k) {
+  const int tx = (g.nx + kTile - 1) / kTile, ty = (g.ny + kTile - 1) / kTile;
+  if (tx * ty > (int)gridDim.x) return make_int2(k % tx, k / tx);
+  const int xcd = k & 7, base = tx * ty >> 3, more = tx * ty & 7;
+  const int p = xcd * base + (xcd < more ? xcd : more) + (k >> 3);
+  const int along = g.swap ? tx : ty, tu = p / along, tv = p - tu * along;
+  return g.swap ? make_int2(tv, tu) : make_int2(tu, tv);
 }
 
 // The quadrant's next source at the lane's cell from the nodal one in LDS.
@@ -1046,8 +1061,8 @@ __global__ __launch_bounds__(kRedBlock) void k_dg_combine(DgArgs g, double* part
   const double* const dir = g.dir + 3 * (size_t)q * g.n_quad;
   const int n_tiles = dg_tiles(g);
   double dsum = 0.0, nsum = 0.0;
-  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const TileCell t = tile_cell(g, tile, q, lane);
+  for (int k = blockIdx.x; k < n_tiles; k += gridDim.x) {
+    const TileCell t = tile_cell(g, dg_tile(g, k), q, lane);
     // wave 0: the cell's data for the update, in flight with the planes
     double4 o = make_double4(0.0, 0.0, 0.0, 0.0);
     double ssc = 0.0, pp = 0.0, pre = 0.0;
@@ -1134,8 +1149,8 @@ __global__ __launch_bounds__(kRedBlock) void k_dsa_apply(DgArgs g,
   const int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int n_tiles = dg_tiles(g);
   double dsum = 0.0, nsum = 0.0;
-  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const TileCell t = tile_cell(g, tile, q, lane);
+  for (int k = blockIdx.x; k < n_tiles; k += gridDim.x) {
+    const TileCell t = tile_cell(g, dg_tile(g, k), q, lane);
     if (q == 0 && t.ok) {
       const double dl = delta[t.cell];
       const double4 o = reinterpret_cast<const double4*>(g.phi_c)[t.cell];
