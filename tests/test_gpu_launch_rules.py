@@ -75,3 +75,26 @@ def test_census_tiles_and_emission_runs(S, oracle, n_particles, cap):
         for f in ("x", "y", "ox", "oy", "w"):
             assert rel_l2(c[f], getattr(b, f)) <= 1e-12, f
     s.destroy()
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (1, 70), (1024, 1), (41, 25), (63, 65), (64, 64)])
+@pytest.mark.parametrize("kw", [dict(closure=1), dict(si_accel=1)])
+def test_conjugate_gradients_in_one_workgroup(S, oracle, nx, ny, kw):
+    """Up to 4096 cells, one to four per thread: the closing stage and the
+    corrections of the source iteration."""
+    from paper_2511_16821_amd import workloads as W
+    rng = np.random.default_rng(nx * 31 + ny)
+    p = W.homogeneous_box(n=max(nx, ny), L=2.0, n_s=1, n_particles=2000, dt=0.1, sn_order=4, **kw)
+    p.update(nx=nx, ny=ny, x_hi=0.2 * nx, y_hi=0.25 * ny, boundary=6)
+    for f in ("sigma_s", "sigma_a"):
+        p[f] = rng.uniform(0.05, 3.0, size=(ny, nx))
+    p["q"] = np.ones((ny, nx))
+    log("one workgroup", nx, ny, kw)
+    o = oracle.HybridOracle(p)
+    s = S.Solver(p)
+    for _ in range(2):
+        r = o.step()
+        s.advance(1)
+        compare_step(S, s, r)
+        assert s.get_stats()["si_iterations"] == r["si_iters"]
+    s.destroy()
