@@ -351,7 +351,7 @@ static Sizes sizes_of(const slh_problem* p) {
   if (z.dsa) b += nc * 32;                   // nodal change of a sweep
   if (!z.diffusion) {
     b += nc * 128;                           // DG source of four quadrants
-    b += nc * (!fields || z.dg.table ? 16 : 8);  // table offsets or sigma_e
+    b += nc * 16;                            // table offsets, or sigma_e in two orders
     b += (size_t)4 * z.dg.n_grp * nc * 32;   // planes of the groups of directions
     b += dg_hand_words(z.dg) * 8;            // traces between workgroups
     if (z.dg.table) b += (size_t)z.n_mat * 8;
@@ -677,7 +677,7 @@ static slh_status setup(slh_solver* s) {
       ALLOC(s->mat_off, int, 4 * nc);
       ALLOC(s->sig_e_mat, double, z.n_mat);
     } else {
-      ALLOC(s->sig_e, double, nc);
+      ALLOC(s->sig_e, double, 2 * nc);
     }
   }
   if (z.diffusion || z.dsa) {
@@ -790,7 +790,7 @@ static slh_status setup(slh_solver* s) {
     HIP_TRY(hipMemcpyAsync(s->refl_y, s->h_refl.data() + nd, 4 * nd, hipMemcpyHostToDevice, st));
   }
   std::vector<int> mid;
-  std::vector<double> mval;
+  std::vector<double> mval, se_diag;
   if (s->mat_off) {
     mval.assign(se.begin(), se.end());
     std::sort(mval.begin(), mval.end());
@@ -806,7 +806,14 @@ static slh_status setup(slh_solver* s) {
     HIP_TRY(hipMemcpyAsync(s->mat_off, mid.data(), 16 * nc, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(s->sig_e_mat, mval.data(), 8 * z.n_mat, hipMemcpyHostToDevice, st));
   } else if (s->sig_e) {
-    HIP_TRY(hipMemcpyAsync(s->sig_e, se.data(), 8 * nc, hipMemcpyHostToDevice, st));
+    se_diag.resize(2 * nc);
+    for (int v = 0; v < z.dg.nv; ++v)
+      for (int u = 0; u < z.dg.nu; ++u) {
+        const double x = se[z.dg.swap ? (long long)u * p.nx + v : (long long)v * p.nx + u];
+        for (int anti = 0; anti < 2; ++anti)
+          se_diag[anti * nc + dg_diag(z.dg.nu, z.dg.nv, anti, u, v)] = x;
+      }
+    HIP_TRY(hipMemcpyAsync(s->sig_e, se_diag.data(), 16 * nc, hipMemcpyHostToDevice, st));
   }
   // the diffusion correction takes the vacuum condition on every side (the
   // sweep's reflected inflow lags one iteration; a zero-current side there

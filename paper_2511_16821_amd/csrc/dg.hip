@@ -340,7 +340,8 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
   const __amdgpu_buffer_rsrc_t out = buffer_of(
       reinterpret_cast<double2*>(g.psi) + (size_t)(q * g.n_grp + grp) * 2 * n, bytes);
   const __amdgpu_buffer_rsrc_t ids =
-      TABLE ? buffer_of(g.mat_off + (size_t)q * n, 4u * n) : buffer_of(g.sig_e, 8u * n);
+      TABLE ? buffer_of(g.mat_off + (size_t)q * n, 4u * n)
+            : buffer_of(g.sig_e + (unegative != vnegative ? (size_t)n : 0), 8u * n);
   constexpr double kap = kV1i;  // v1 = -1 + i kap
 
   // SPLIT: this lane's double of a block of columns, two tagged words
@@ -371,34 +372,35 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
     const bool leaves = last ? (v_out && lane == rows - 1) : lane == 63;
     double2* leave_at = leaves ? yf + PER * (kDgFront - lane) : idle + PER * lane;
     const int leave_by = leaves ? PER : 0;
-    // without a table, row-major sigma_e: cell (u, v) at cell0 + u cell_u
-    int cell0 = 0, cell_u = 0;
+    // without a table, sigma_e by diagonals (dg_diag): a step's cells lie on one,
+    // the next step's on the next (negative u: on the one before)
+    int e_lane = 0, e_off = 0, e_step = 0;
     if (!TABLE) {
       const int v = 64 * s + lr;
-      const int x0 = g.swap ? v : 0, y0 = g.swap ? 0 : v;
-      const int i0 = (q & 1) ? g.nx - 1 - x0 : x0, j0 = (q & 2) ? g.ny - 1 - y0 : y0;
-      cell0 = j0 * g.nx + i0;
-      cell_u = g.swap ? ((q & 2) ? -g.nx : g.nx) : ((q & 1) ? -1 : 1);
+      e_lane = 8 * (vnegative ? nv - 1 - v : v);
+      e_step = unegative ? -8 * nv : 8 * nv;
+      const int u0 = unegative ? nu - 1 : 0, v0 = vnegative ? nv - 1 - 64 * s : 64 * s;
+      e_off = 8 * nv * dg_diag_row(nu, unegative != vnegative, u0, v0);
     }
     double2 r1[AHEAD], r2[AHEAD];  // sources in flight
     int rk[AHEAD];                 // byte offsets of the materials' table rows
     double re[AHEAD];              // sigma_e
     int ro[AHEAD];                 // byte offset of the step's slot row
     const int row_bytes = 32 * rows, o_begin = 32 * 64 * s * nu, o_end = o_begin + nu * row_bytes;
-    int f_t = 0, f_off = o_begin;  // next step to fetch
+    int f_off = o_begin;  // the next step's to fetch
     auto fetch = [&](int k) __attribute__((always_inline)) {
       r1[k] = buffer_load2(src, 32 * lr, f_off);
       r2[k] = buffer_load2(src, 32 * lr + 16, f_off);
       if (TABLE) {
         rk[k] = (int)__builtin_amdgcn_raw_buffer_load_b32(ids, 4 * lr, f_off >> 3, 0);
       } else {
-        const int u = f_t - lane;
-        const int c = cell0 + (u < 0 ? 0 : (u < nu ? u : nu - 1)) * cell_u;
         re[k] = __builtin_bit_cast(double,
-                                   __builtin_amdgcn_raw_buffer_load_b64(ids, 8 * c, 0, 0));
+                                   __builtin_amdgcn_raw_buffer_load_b64(ids, e_lane, e_off, 0));
+        e_off += e_step;
+        e_off += e_off < 0 ? 8 * n : 0;
+        e_off -= e_off >= 8 * n ? 8 * n : 0;
       }
       ro[k] = f_off;
-      ++f_t;
       f_off += row_bytes;
       if (f_off == o_end) f_off = o_begin;
     };
