@@ -745,10 +745,13 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool 
   auto cost = [](int nu, int nv) {
     return (long long)((nv + 63) / 64) * (nu + (nv < 64 ? nv : 64) - 1);
   };
-  p.swap = cost(ny, nx) < cost(nx, ny) || nx == 1 ? 1 : 0;  // one column: as one row
-  p.nu = p.swap ? ny : nx;
-  p.nv = p.swap ? nx : ny;
-  p.n_strips = (p.nv + 63) / 64;
+  auto axis = [&](int swap) {
+    p.swap = swap;
+    p.nu = swap ? ny : nx;
+    p.nv = swap ? nx : ny;
+    p.n_strips = (p.nv + 63) / 64;
+  };
+  const int cheap = cost(ny, nx) < cost(nx, ny) || nx == 1 ? 1 : 0;  // one column: as one row
   const long long nc = (long long)nx * ny;
   auto fill = [&](int per) {
     p.per = per;
@@ -765,31 +768,48 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool 
               dg_sweep_lds_bytes(p, (int)std::min<long long>(n_mat, 1 << 20), refl) <= lds;
     return dg_sweep_lds_bytes(p, p.table ? (int)n_mat : 0, refl) <= lds;
   };
-  // Four directions per wave quarter the planes' traffic, but a step takes 0.5
-  // us.  With one direction it takes 0.16, and 0.037 (0.045 above eight) times
-  // the strips of the direction where these keep their compute unit busy: the
-  // eight of 512 rows take 0.29 us a step.  Planes that stay in the 256 MB
-  // last-level cache cost little; past it the reduction reads 3.4 TB/s and the
-  // sweep writes 2 to 4.  Measured sweep and reduction with one and with four
-  // (44 meshes of 192^2 to 1024^2, 1024 x 128 and 655 x 53, S_4 to S_16; this
-  // estimate's choice is within 5% of the better one): 256^2 S_8 0.13 against
-  // 0.26 ms, S_16 0.35 / 0.28; 384^2 S_8 0.32 / 0.41, S_12 0.54 / 0.43; 512^2 S_8
-  // 0.58 / 0.57, S_16 1.30 / 0.66; 1024^2 S_4 1.77 / 1.19, S_16 5.2 / 1.8.
+  axis(cheap);
+  const bool fits = fill(1);
+  if (!fits || p.nv == 1) return p;  // (a row: the scan of its cells)
+  // Microseconds of a sweep and its reduction.  The chain of steps: a strip starts
+  // 72 steps after the one before, so that at most (nu + 63) / 72 + 1 work at a time.
+  // With four directions per wave a step takes 0.5 us, 0.65 with the inverses per
+  // cell; with one 0.23, or 0.033 (0.038) times the strips at work, which share a
+  // compute unit, and up to 2.1 times that where rows of more than 600 columns
+  // leave the caches.  The planes: what stays in the 256 MB last-level cache costs
+  // 0.2 us a MB, what does not 0.3 more, which four directions per wave quarter.
+  // Fitted to 300 measured pairs of mesh and order (40^2 to 2048^2, 3500 x 30 to
+  // 3800 x 250, S_2 to S_16, table and cells; other sizes are extrapolated): the
+  // choice is at most 10% slower than the best of the four, 0.2% on average.
+  // Milliseconds with one along either axis, four along either: 2300 x 65 S_4 0.50,
+  // 0.42, 1.18, 1.06; 3000 x 1000 S_16 13.8, -, -, 5.2 (four's traces do not fit the
+  // LDS above some 2400 columns); 1024^2 S_16 5.1, -, 1.83, 1.88; 256^2 S_8 0.13, -,
+  // 0.27, 0.27; 512^2 S_8 0.59, -, 0.59, 0.58.
   auto us = [&]() {
     const bool four = p.per == kDgSplit;
-    const double busy = (p.n_waves <= 8 ? 0.037 : 0.045) * p.n_waves;
-    const double step = four ? 0.5 : (busy > 0.16 ? busy : 0.16);
-    const double mb = 128e-6 * p.n_grp * (double)nc, far = mb > 200.0 ? mb - 200.0 : 0.0;
-    return (p.nu + 72.0 * p.n_strips) * step + (four ? 0.2 : 0.18) * mb + (four ? 0.1 : 0.37) * far;
+    const double strips = p.n_strips - 1, steps = p.nu + 72.0 * strips + p.nv - 64.0 * strips;
+    const double work = std::min(p.n_waves, (p.nu + 63) / 72 + 1);
+    const double far = std::max(0, p.nu - 600) * 1e-3 * std::min(1.0, nc / 0.9e6);
+    const double busy = (0.033 * (1.0 + std::min(1.1, far)) + (p.table ? 0.0 : 0.005)) * work;
+    const double step = four ? (p.table ? 0.5 : 0.65) : std::max(0.23, busy);
+    const double mb = 128e-6 * p.n_grp * (double)nc, past = std::max(0.0, mb - 200.0);
+    return steps * step + (four ? 0.24 : 0.2) * mb + (four ? 0.12 : 0.32) * past;
   };
-  if (n_dir >= 4 * kDgSplit && fill(kDgSplit)) {
-    const double split_us = us();
-    fill(1);
-    if (split_us < us()) fill(kDgSplit);
-  } else {
-    fill(1);
+  DgPlan best = p;
+  double best_us = us();
+  auto consider = [&](int swap, int per) {
+    axis(swap);
+    if (!fill(per) || us() >= best_us) return;
+    best = p;
+    best_us = us();
+  };
+  consider(1 - cheap, 1);
+  if (n_dir >= 4 * kDgSplit) {
+    best_us *= 1.05;  // four directions take a quarter of the planes' memory
+    consider(cheap, kDgSplit);
+    consider(1 - cheap, kDgSplit);
   }
-  return p;
+  return best;
 }
 
 hipError_t launch_si_start(const DgArgs& a, int si_max, hipStream_t s) {

@@ -58,3 +58,49 @@ def test_material_per_cell_on_long_rows(S):
         s.destroy()
     log("3800 x 250, S_2: table %.2f ms, material per cell %.2f ms" % tuple(ms))
     assert ms[1] < 1.4 * ms[0], ms
+
+
+def _check(S, oracle, p, steps=1):
+    from gpu_util import compare_step
+    log("sweep", p["nx"], p["ny"], "S_%d" % p["sn_order"], "boundary", p.get("boundary", 0))
+    o = oracle.HybridOracle(p)
+    s = S.Solver(p)
+    for _ in range(steps):
+        r = o.step()
+        s.advance(1)
+        compare_step(S, s, r)
+        assert s.get_stats()["si_iterations"] == r["si_iters"]
+    s.destroy()
+
+
+def test_few_strips_along_the_long_side(S):
+    """1000 x 65: sixteen directions take about as long as four (by 1.05
+    measured; 2.4 where they walked the 65 rows' way, sixteen strips one after
+    the other with four directions per wave)."""
+    ms = []
+    for sn in (2, 4):
+        s = S.Solver(_problem(1000, 65, 5, dt=1e-3, sn_order=sn, si_tol=1e-300, si_max_iter=12))
+        s.set_timing(True)
+        s.set_si_batch(12)
+        ms.append(_solve_ms(s))
+        s.destroy()
+    log("1000 x 65: S_2 %.2f ms, S_4 %.2f ms" % tuple(ms))
+    assert ms[1] < 1.6 * ms[0], ms
+
+
+def test_four_directions_where_one_side_is_long(S):
+    """3000 x 1000 cells, S_16, need the planes of 2000 x 1500 (four times as
+    many where the long side's traces kept the directions one by one)."""
+    b = [S.slh_footprint_bytes(_problem(nx, ny, 5, dt=1e-3, sn_order=16))
+         for nx, ny in ((3000, 1000), (2000, 1500))]
+    assert b[0] < 1.1 * b[1], b
+
+
+@pytest.mark.parametrize("nx,ny,sn,boundary,n_mat", [
+    (700, 65, 4, 15, 5),     # two strips along the long side, the second of one row
+    (65, 700, 2, 6, 0),
+    (129, 500, 4, 9, 0),     # three strips
+    (200, 66, 8, 3, 5),
+    (144, 65, 32, 0, 5)])    # four directions along the side of more wave-steps
+def test_strips_along_either_side(S, oracle, nx, ny, sn, boundary, n_mat):
+    _check(S, oracle, _problem(nx, ny, n_mat, dt=1e-3, sn_order=sn, boundary=boundary, si_tol=1e-4))
