@@ -760,12 +760,24 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool 
     p.n_blk = per == kDgSplit ? (p.n_strips + most - 1) / most : 1;
     p.n_grp = (n_dir / 4 + per - 1) / per;
     // A table entry costs about 60 operations per material and direction in
-    // each sweep's workgroup, the inverses per cell about 25 per step and
-    // wave: the table where it is the cheaper of the two and fits (and, with
-    // 1/|z|^2 in it, where that does not underflow).
-    p.table = n_mat > 0 && n_mat * 60 <= 25ll * 64 * p.n_waves * (p.nu + p.nv) &&
-              (per == 1 || sig_max < 1e100) &&
-              dg_sweep_lds_bytes(p, (int)std::min<long long>(n_mat, 1 << 20), refl) <= lds;
+    // each sweep's workgroup, a step about 50 per wave and the inverses per cell 25
+    // more: the table where it is the cheaper of the two and fits (and, with
+    // 1/|z|^2 in it, where that does not underflow).  A large table also keeps
+    // other workgroups off the compute unit, and many directions take turns (50^2,
+    // 2500 materials, S_32: 0.16 ms an iteration with the table, 83 KB for a
+    // workgroup of one wave, in four turns; 0.09 without).
+    const int rows = (int)std::min<long long>(n_mat, 1 << 20);
+    auto turns = [&](int n) {
+      const long long here = lds / dg_sweep_lds_bytes(p, n, refl);
+      // (waves of four directions fill their SIMDs, of one need company)
+      const long long waves = (per == 1 ? 16 : 4) / p.n_waves;
+      const long long at_once = 256 * std::max(1ll, std::min(here, waves));
+      return (4 * p.n_grp * p.n_blk + at_once - 1) / at_once;
+    };
+    const long long walk = 64ll * p.n_waves * (p.nu + p.nv);
+    p.table = n_mat > 0 && (per == 1 || sig_max < 1e100) &&
+              dg_sweep_lds_bytes(p, rows, refl) <= lds &&
+              turns(rows) * (60 * n_mat + 50 * walk) <= turns(0) * 75 * walk;
     return dg_sweep_lds_bytes(p, p.table ? (int)n_mat : 0, refl) <= lds;
   };
   axis(cheap);

@@ -60,6 +60,21 @@ def test_material_per_cell_on_long_rows(S):
     assert ms[1] < 1.4 * ms[0], ms
 
 
+def test_many_materials_and_directions(S):
+    """50 x 50 cells, S_32: a material per cell takes about as long as five (by
+    1.0 measured; 2.0 where a table of 2500 materials kept other directions'
+    workgroups off the compute unit)."""
+    ms = []
+    for n_mat in (5, 0):
+        s = S.Solver(_problem(50, 50, n_mat, dt=1e-2, sn_order=32, si_tol=1e-300, si_max_iter=12))
+        s.set_timing(True)
+        s.set_si_batch(12)
+        ms.append(_solve_ms(s))
+        s.destroy()
+    log("50 x 50, S_32: five materials %.2f ms, one per cell %.2f ms" % tuple(ms))
+    assert ms[1] < 1.5 * ms[0], ms
+
+
 def _check(S, oracle, p, steps=1):
     from gpu_util import compare_step
     log("sweep", p["nx"], p["ny"], "S_%d" % p["sn_order"], "boundary", p.get("boundary", 0))
