@@ -325,7 +325,10 @@ static Sizes sizes_of(const slh_problem* p) {
     z.n_mat = (int)mats.size();
     sig_max = mats.back();
   }
-  z.dg = dg_plan(p->nx, p->ny, z.n_dir, z.n_mat, sig_max, p->boundary != 0, lds_limit());
+  const double hx = (p->x_hi - p->x_lo) / p->nx, hy = (p->y_hi - p->y_lo) / p->ny;
+  const bool squares =
+      std::min(hx, hy) > 1e-100 && std::max(hx, hy) < 1e100 && sig_max < 1e100;
+  z.dg = dg_plan(p->nx, p->ny, z.n_dir, z.n_mat, squares, p->boundary != 0, lds_limit());
   if (fields) {
     const long long m = (long long)material_pairs(p).size();
     z.n_mc_mat = m <= kMaxMatIds ? (int)m : 0;

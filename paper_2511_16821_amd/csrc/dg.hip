@@ -739,7 +739,7 @@ size_t dg_sweep_lds_bytes(const DgPlan& p, int n_mat, bool refl) {
          sizeof(int) * (size_t)(split ? p.n_waves : p.n_strips);
 }
 
-DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool refl, size_t lds) {
+DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, bool squares, bool refl, size_t lds) {
   DgPlan p;
   // wave-steps of a direction with the lanes along y or along x
   auto cost = [](int nu, int nv) {
@@ -762,7 +762,7 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool 
     // A table entry costs about 60 operations per material and direction in
     // each sweep's workgroup, a step about 50 per wave and the inverses per cell 25
     // more: the table where it is the cheaper of the two and fits (and, with
-    // 1/|z|^2 in it, where that does not underflow).  A large table also keeps
+    // 1/|z|^2 in it, where that is a normal number).  A large table also keeps
     // other workgroups off the compute unit, and many directions take turns (50^2,
     // 2500 materials, S_32: 0.16 ms an iteration with the table, 83 KB for a
     // workgroup of one wave, in four turns; 0.09 without).
@@ -775,7 +775,7 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, double sig_max, bool 
       return (4 * p.n_grp * p.n_blk + at_once - 1) / at_once;
     };
     const long long walk = 64ll * p.n_waves * (p.nu + p.nv);
-    p.table = n_mat > 0 && (per == 1 || sig_max < 1e100) &&
+    p.table = n_mat > 0 && (per == 1 || squares) &&
               dg_sweep_lds_bytes(p, rows, refl) <= lds &&
               turns(rows) * (60 * n_mat + 50 * walk) <= turns(0) * 75 * walk;
     return dg_sweep_lds_bytes(p, p.table ? (int)n_mat : 0, refl) <= lds;

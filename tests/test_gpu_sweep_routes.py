@@ -119,3 +119,11 @@ def test_four_directions_where_one_side_is_long(S):
     (144, 65, 32, 0, 5)])    # four directions along the side of more wave-steps
 def test_strips_along_either_side(S, oracle, nx, ny, sn, boundary, n_mat):
     _check(S, oracle, _problem(nx, ny, n_mat, dt=1e-3, sn_order=sn, boundary=boundary, si_tol=1e-4))
+
+
+def test_cells_of_extreme_width(S, oracle):
+    """Cells 1e-155 wide, four directions per wave: 1/|z|^2 of the element's
+    modes is no number there, the inverses themselves are."""
+    p = _problem(256, 250, 5, sn_order=16)
+    p.update(x_hi=256e-155, steady=True, horizon=30e-155, q=1e250 * p["q"])
+    _check(S, oracle, p)
