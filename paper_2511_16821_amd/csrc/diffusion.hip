@@ -503,7 +503,9 @@ hipError_t launch_dsa_start(const CgArgs& a, const double* sig_s, const double* 
 bool cg_one_block(long long n) { return n <= kCgOneBlockMax; }
 
 hipError_t launch_cg_solve_one_block(const CgArgs& a, double tol, int max_iter, hipStream_t s) {
-  const int cells = a.nx * a.ny;  // below kCgOneBlock: the waves that have cells
+  const long long n = (long long)a.nx * a.ny;
+  if (n < 1 || !cg_one_block(n)) return hipErrorInvalidValue;  // more than registers and LDS hold
+  const int cells = (int)n;  // below kCgOneBlock: the waves that have cells
   const int threads = cells < kCgOneBlock ? (cells + 63) & ~63 : kCgOneBlock;
   hipLaunchKernelGGL(k_cg_solve_one_block, dim3(1), dim3(threads), 0, s, a.nx, a.ny,
                      (const double*)a.diag, (const double*)a.cE, (const double*)a.cN, a.x,

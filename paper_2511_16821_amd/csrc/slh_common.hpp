@@ -627,7 +627,9 @@ hipError_t launch_cg_start(const CgArgs& a, const double* sig_s, const double* p
 // times the cell average of dnode (phi^{k+1/2} - phi^k, four nodes per cell)
 hipError_t launch_dsa_start(const CgArgs& a, const double* sig_s, const double* dnode,
                             int max_iter, hipStream_t s);
-// the whole (remaining) solve in one workgroup, whatever the mesh size
+// The whole solve of a mesh of at most 4096 cells (cg_one_block) in one workgroup;
+// a larger one is refused.  x and the state are written, r, z and p stay in
+// registers: the next solve starts them anew.
 hipError_t launch_cg_solve_one_block(const CgArgs& a, double tol, int max_iter, hipStream_t s);
 // one iteration (nothing once the state says done); stops at |r| <= tol |b|.
 // On meshes where cg_one_block holds, one call runs the whole solve.
