@@ -127,3 +127,14 @@ def test_cells_of_extreme_width(S, oracle):
     p = _problem(256, 250, 5, sn_order=16)
     p.update(x_hi=256e-155, steady=True, horizon=30e-155, q=1e250 * p["q"])
     _check(S, oracle, p)
+
+
+@pytest.mark.parametrize("n_mat", [4600, 5000, 5119, 5200])
+def test_as_many_materials_as_a_table_holds(S, oracle, n_mat):
+    """130 x 129 cells whose materials fill the table's LDS, or are one more
+    than it could hold, or more than are counted."""
+    p = _problem(130, 129, n_mat, dt=0.1, sn_order=2, boundary=9)
+    for k, f in enumerate(("sigma_s", "sigma_a")):  # every material in some cell
+        v = np.random.default_rng(7 + k).uniform(0.05, 3.0, size=n_mat)
+        p[f] = v[np.random.default_rng(3).permutation(130 * 129) % n_mat].reshape(129, 130)
+    _check(S, oracle, p, steps=2)
