@@ -61,12 +61,18 @@ __device__ __forceinline__ double recip(double a) {
   return r;
 }
 
-// lambda = 2 + i sqrt 2; l = (l0, l1), v = (v0, v1) as above
-constexpr double kSqrt2 = 1.4142135623730951;
+// lambda = 2 + i sqrt 2; l = (l0, l1), v = (v0, v1) as above.  A cell without
+// sources and absorption passes a constant trace on times 2 Re(v1 / lambda) = 1.
+// In doubles that is 1 + 1.3e-16 with the nearest ones to sqrt 2 and 2.5 sqrt 2, in
+// every cell alike, and a path of hundreds of cells adds it up; with the double
+// below sqrt 2 it is 1 - 2.7e-17, the least of any neighbours.  (Relative L2 error
+// of a sweep against 80-bit arithmetic: 512^2 S_16 of 0.1 per unit length 1.8e-14
+// -> 2.4e-15, 300^2 S_4 of 0.01 1.8e-14 -> 5.4e-15.)
+constexpr double kSqrt2 = 1.414213562373095;
 constexpr double kL0r = 5.0 / 18.0, kL0i = -kSqrt2 / 18.0;
 constexpr double kL1r = 1.0 / 18.0, kL1i = -2.0 * kSqrt2 / 18.0;
 constexpr double kV0r = 2.0, kV0i = -0.5 * kSqrt2;
-constexpr double kV1r = -1.0, kV1i = 2.5 * kSqrt2;
+constexpr double kV1r = -1.0, kV1i = 3.5355339059327378;
 
 // Coefficients of the mirrored nodal values s<ku><kv> of a cell.
 __device__ __forceinline__ void to_modes(double s00, double s01, double s10, double s11,
