@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from gpu_util import log
+from plan_util import sweep_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -111,13 +112,15 @@ def test_four_directions_where_one_side_is_long(S):
     assert b[0] < 1.1 * b[1], b
 
 
-@pytest.mark.parametrize("nx,ny,sn,boundary,n_mat", [
-    (700, 65, 4, 15, 5),     # two strips along the long side, the second of one row
-    (65, 700, 2, 6, 0),
-    (129, 500, 4, 9, 0),     # three strips
-    (200, 66, 8, 3, 5),
-    (144, 65, 32, 0, 5)])    # four directions along the side of more wave-steps
-def test_strips_along_either_side(S, oracle, nx, ny, sn, boundary, n_mat):
+@pytest.mark.parametrize("nx,ny,sn,boundary,n_mat,per,nu", [
+    (700, 65, 4, 15, 5, 1, 700),  # two strips along the long side, the second of one row
+    (65, 700, 2, 6, 0, 1, 700),
+    (129, 500, 4, 9, 0, 1, 500),  # three strips
+    (200, 66, 8, 3, 5, 1, 200),
+    (144, 65, 32, 0, 5, 4, 144)])  # four directions along the side of more wave-steps
+def test_strips_along_either_side(S, oracle, nx, ny, sn, boundary, n_mat, per, nu):
+    plan = sweep_plan(S, nx, ny, sn, n_mat or nx * ny, boundary != 0)
+    assert (plan.per, plan.nu) == (per, nu)
     _check(S, oracle, _problem(nx, ny, n_mat, dt=1e-3, sn_order=sn, boundary=boundary, si_tol=1e-4))
 
 
@@ -125,15 +128,17 @@ def test_cells_of_extreme_width(S, oracle):
     """Cells 1e-155 wide, four directions per wave: 1/|z|^2 of the element's
     modes is no number there, the inverses themselves are."""
     p = _problem(256, 250, 5, sn_order=16)
+    assert sweep_plan(S, 256, 250, 16, 5).per == 4
     p.update(x_hi=256e-155, steady=True, horizon=30e-155, q=1e250 * p["q"])
     _check(S, oracle, p)
 
 
-@pytest.mark.parametrize("n_mat", [4600, 5000, 5119, 5200])
+@pytest.mark.parametrize("n_mat", [4600, 4900, 5119, 5200])
 def test_as_many_materials_as_a_table_holds(S, oracle, n_mat):
     """130 x 129 cells whose materials fill the table's LDS, or are one more
     than it could hold, or more than are counted."""
     p = _problem(130, 129, n_mat, dt=0.1, sn_order=2, boundary=9)
+    assert sweep_plan(S, 130, 129, 2, n_mat, True).table == (n_mat <= 4900)
     for k, f in enumerate(("sigma_s", "sigma_a")):  # every material in some cell
         v = np.random.default_rng(7 + k).uniform(0.05, 3.0, size=n_mat)
         p[f] = v[np.random.default_rng(3).permutation(130 * 129) % n_mat].reshape(129, 130)
