@@ -1074,8 +1074,8 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
       HIP_TRY(launch_mc_pass(pass_args(s, 1), z.fp32, s->grid1, st));
       return SLH_OK;
     case kMid: {
-      HIP_TRY(launch_tally_to_flux(s->Tpre, s->phi_pre, s->Tpost, s->phi_post, nc, kTallyCopies,
-                                   cstride, s->st, inv_adt, st));
+      HIP_TRY(launch_tally_to_flux(s->Tpre, s->phi_pre, s->Tpost, s->phi_post, nc, cstride, s->st,
+                                   inv_adt, st));
       hipLaunchKernelGGL(k_snapshot, dim3(1), dim3(64), 0, st, s->st, s->bal_store + 0, 1, 0);
       if (use_cg(s)) {
         HIP_TRY(launch_cg_start(cg_args(s), s->sig_s, s->phi_post, s->si_max, &s->st->halt, st));
@@ -1112,7 +1112,7 @@ static slh_status enqueue_part(slh_solver* s, int part, hipStream_t st) {
     default: {  // kEnd: the remap census is the state at t_{n+1} (capped)
       // without a remap leg the solution is the pure-MC flux of pass 1
       HIP_TRY(launch_tally_to_flux(s->skip_remap ? s->Tpre : s->TR, s->phi_R, nullptr, nullptr,
-                                   nc, kTallyCopies, cstride, s->st, inv_adt, st));
+                                   nc, cstride, s->st, inv_adt, st));
       hipLaunchKernelGGL(k_snapshot, dim3(1), dim3(64), 0, st, s->st, s->bal_store + 1, 2,
                          n_it > 0 ? 1 : 0);
       void* nb = s->bank_mem[1 - s->cur];

@@ -38,14 +38,15 @@
 // word says that they are there.  What bounds the sweep is the chain of nu +
 // nv dependent steps on small meshes (0.16 us each, the issue of a step's
 // instructions, where a workgroup barrier per diagonal took 0.45 us; 256^2,
-// S_8: 264 -> 88 us a sweep, 140^2, S_12: 130 -> 51) and the traffic of the planes
+// S_8: 264 -> 91 us a sweep, 140^2, S_12: 130 -> 52) and the traffic of the planes
 // on large ones; there each wave sweeps four directions, which share the
 // sources and leave one plane: the sum of w_m psi_m over them.
 //
 // Every quadrant has its own copy of the source (and of the material ids) in
 // its own order of visits (dg_slot): the cells that a wave holds at one step
-// are neighbours in memory.  Cells outside the mesh take no storage: the
-// columns of a strip wrap around (slot row (u + l) mod nu).
+// are neighbours in memory; so are they in sigma_e, which is kept by diagonals
+// (dg_diag) where there is no table of materials.  Cells outside the mesh take no
+// storage: the columns of a strip wrap around (slot row (u + l) mod nu).
 #include <algorithm>
 
 #include "slh_common.hpp"
@@ -604,9 +605,9 @@ __global__ __launch_bounds__(THREADS) void k_dg_sweep(DgArgs g) {
 // since conj(X2) is linear in ux.  Such maps compose associatively, so a
 // workgroup per direction finds the inflow traces of all cells by a prefix scan
 // of the maps, a thread taking `per` successive cells (one up to 1024), where
-// the strips' walk takes a step per cell (80 cells between reflective sides,
-// S_4: 19 -> 4.4 us a sweep, the steady solve 5.0 -> 2.5 ms; what is left is
-// launch and memory latency).
+// the strips' walk takes a step per cell (S_4 with reflective sides: 5.4 us a sweep
+// of 400 cells, 7.4 of 1000, launch and memory latency for the most part; the walk
+// took 19 us for 80).
 constexpr int kRowWaves = 16;
 
 struct TraceMap {
@@ -1012,9 +1013,11 @@ __device__ __forceinline__ void add_norms(double4 v, double4 d, double r, double
 // after the cells' update (wave 0) it forms the quadrant's next source.  The
 // cells of a slot row lie on a diagonal of the mesh, so a wave takes its tile
 // along the diagonals of its quadrant: eight lanes then read, and write, two
-// whole cache lines (140x140, S_12: 29 us a reduction; cells in row-major order,
-// a line for every lane, 75 us; the two modes in arrays of their own, one line
-// for eight lanes, 40 us; tiles of 16 x 16, 33 us).
+// whole cache lines.  Bound by the planes' traffic and, with few tiles, by the
+// latency of the planes' batches; 26 us a reduction at 140x140, S_12 (the choices,
+// when they were made, in means over launches of which a quarter return at once:
+// 29 us; cells in row-major order, a line for every lane, 75; the two modes in
+// arrays of their own, one line for eight lanes, 40; tiles of 16 x 16, 33).
 constexpr int kNodeRow = kRedCells + 1;  // LDS stride of a node: [node][cell]
 
 // Tile cell of lane l in quadrant q: column (d - e) mod 8 of the u axis and row e
@@ -1046,8 +1049,8 @@ __device__ __forceinline__ int dg_tiles(const DgArgs& g) {
 // The k-th tile.  A slot row's run of eight cells belongs to two tiles that are
 // neighbours along u, and its cache lines to neighbours along v: where every
 // tile has its block, the blocks of an XCD (k mod 8) take a run of tiles in the
-// order of v, then u (333 x 187, S_8: 30 -> 24 us a reduction, 128^2, S_16: 31 ->
-// 29, 140^2, S_12: 21 -> 20).  On larger meshes the rows' order is the better
+// order of v, then u (333 x 187, S_8: 38 -> 31 us a reduction, 128^2, S_16: 31 ->
+// 28, 140^2, S_12: 27 -> 26).  On larger meshes the rows' order is the better
 // one: the runs' starts, an eighth of a power of two apart, meet in the same
 // memory channels (1024^2: 0.46 against 0.51 ms; patches of 8 x 8 tiles 0.47).
 __device__ __forceinline__ int2 dg_tile(const DgArgs& g, int k) {

@@ -120,7 +120,6 @@ template <> struct Real<float> {
   }
 };
 
-enum { EV_CENSUS = 0, EV_COLLIDE = 1, EV_XFACE = 2, EV_YFACE = 3 };
 enum { END_NONE = 0, END_CENSUS, END_LEAK, END_CUTOFF };
 
 // States of a lane: without a history, tracking one, its history at a
@@ -135,7 +134,8 @@ enum { END_NONE = 0, END_CENSUS, END_LEAK, END_CUTOFF };
 // served at once, 21.9 / 19.9 with 12 free and 8 colliding lanes, 20.5 / 18.6
 // as here, 22.3 / 18.7 with 32 and 24 (all before the segment's branches went;
 // since then 17.4 / 15.4, 17.9 / 15.9 with 18 free, and a third colliding the
-// same); 30x50 steady, where a wave has 16 histories: 0.38 ms at once, 0.43
+// same; all in a run's third step: in the mean of 50 the passes take 18.5 and
+// 15.7); 30x50 steady, where a wave has 16 histories: 0.38 ms at once, 0.43
 // with twelve colliding lanes, 0.34 with a quarter of the live ones.
 enum { LN_IDLE = 0, LN_RUN, LN_COL, LN_END };
 constexpr int kRefillAt = 24;
@@ -654,8 +654,8 @@ void k_mc_pass(PassArgs a) {
     // wave and, where its sides leave different values, cost a register copy per
     // value: the event is a set of lane masks, and the new state is selected by
     // them (290 -> 190 vector instructions a segment; 1024^2, 1e8 particles,
-    // N_s = 3: passes of 20.1 and 18.1 -> 17.4 and 15.4 ms; 256^2 FP32, 1e7: 0.86
-    // and 0.67 -> 0.76 and 0.56).
+    // N_s = 3, third step of a run: passes of 20.1 and 18.1 -> 17.4 and 15.4 ms; 256^2
+    // FP32, 1e7: 0.86 and 0.67 -> 0.76 and 0.56).
     if (ls == LN_RUN) {
       const int cell = iy * a.nx + ix;
       const R ss = m_cur.x, sa = m_cur.y, stt = sa + ss;

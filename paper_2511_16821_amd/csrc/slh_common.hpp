@@ -666,8 +666,8 @@ hipError_t launch_pass_prep(DevState* st, const double* ctree, int kind, long lo
 // phi = tally * unit / (A dt) for T0 -> phi0 and, when T1 is not null, T1 -> phi1.
 hipError_t launch_tally_to_flux(const unsigned long long* T0, double* phi0,
                                 const unsigned long long* T1, double* phi1, long long n,
-                                int n_copies, long long copy_stride, const DevState* st,
-                                double inv_adt, hipStream_t s);
+                                long long copy_stride, const DevState* st, double inv_adt,
+                                hipStream_t s);
 hipError_t launch_remap_source(long long n, const double* q, const double* sig_s,
                                const double* phi_pre, const double* phi_post,
                                const double* phi_c, double* qn, const int* halt,

@@ -97,15 +97,15 @@ hipError_t launch_pass_prep(DevState* st, const double* ctree, int kind, long lo
 }
 
 // phi = (sum of the private copies, an exact integer sum) * unit / (A dt).
-// A block takes 64 cells; its four waves each sum every fourth copy (eight
-// loads in flight per lane) and the four partial sums meet in LDS.  Integer
+// A block takes 64 cells; its four waves each sum every fourth copy (all loads
+// of a lane in flight) and the four partial sums meet in LDS.  Integer
 // addition makes the result independent of this split.
 constexpr int kT2fCells = 64;
 __global__ __launch_bounds__(256) void k_tally_to_flux(const unsigned long long* __restrict__ T0,
                                                        double* __restrict__ phi0,
                                                        const unsigned long long* __restrict__ T1,
                                                        double* __restrict__ phi1, long long n,
-                                                       int n_copies, long long copy_stride,
+                                                       long long copy_stride,
                                                        const DevState* st, double inv_adt) {
   if (st->halt) return;
   // blockIdx.y picks one of two tallies decoded by the same launch
@@ -116,16 +116,11 @@ __global__ __launch_bounds__(256) void k_tally_to_flux(const unsigned long long*
   const long long i = (long long)blockIdx.x * kT2fCells + lane;
   const long long ic = i < n ? i : n - 1;  // a real cell for every lane's loads
   const unsigned long long* p = T + kTallyStride * ic;
-  unsigned long long v = 0ull;
-  int c = w;
-  for (; c + 28 < n_copies; c += 32) {
-    unsigned long long t[8];
+  unsigned long long v = 0ull, t[kTallyCopies / 4];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = p[(long long)(c + 4 * u) * copy_stride];
+  for (int u = 0; u < kTallyCopies / 4; ++u) t[u] = p[(long long)(w + 4 * u) * copy_stride];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v += t[u];
-  }
-  for (; c < n_copies; c += 4) v += p[(long long)c * copy_stride];
+  for (int u = 0; u < kTallyCopies / 4; ++u) v += t[u];
   s_part[w][lane] = v;
   __syncthreads();
   if (w == 0 && i < n) {
@@ -136,13 +131,13 @@ __global__ __launch_bounds__(256) void k_tally_to_flux(const unsigned long long*
 
 hipError_t launch_tally_to_flux(const unsigned long long* T0, double* phi0,
                                 const unsigned long long* T1, double* phi1, long long n,
-                                int n_copies, long long copy_stride, const DevState* st,
-                                double inv_adt, hipStream_t s) {
+                                long long copy_stride, const DevState* st, double inv_adt,
+                                hipStream_t s) {
   if (n < 1) return hipSuccess;
   const long long b = (n + kT2fCells - 1) / kT2fCells;
   if (b > 0x7fffffffll) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_tally_to_flux, dim3((unsigned)b, T1 ? 2 : 1), dim3(256), 0, s, T0, phi0,
-                     T1, phi1, n, n_copies, copy_stride, st, inv_adt);
+                     T1, phi1, n, copy_stride, st, inv_adt);
   return hipGetLastError();
 }
 
