@@ -353,7 +353,8 @@ static Sizes sizes_of(const slh_problem* p) {
   const double hx = (p->x_hi - p->x_lo) / p->nx, hy = (p->y_hi - p->y_lo) / p->ny;
   const bool squares =
       std::min(hx, hy) > 1e-100 && std::max(hx, hy) < 1e100 && sig_max < 1e100;
-  z.dg = dg_plan(p->nx, p->ny, z.n_dir, z.n_mat, squares, p->boundary != 0, lds_limit());
+  z.dg = dg_plan(p->nx, p->ny, z.n_dir, fields ? z.n_mat : -1, squares, p->boundary != 0,
+                 lds_limit());
   if (fields) {
     const long long m = (long long)material_pairs(p).size();
     z.n_mc_mat = m <= kMaxMatIds ? (int)m : 0;
@@ -380,8 +381,7 @@ static Sizes sizes_of(const slh_problem* p) {
   if (!z.diffusion) {
     b += nc * 128;                           // DG source of four quadrants
     b += nc * 16;                            // table offsets, or sigma_e in two orders
-    b += (size_t)4 * z.dg.n_grp * nc * 32;   // planes of the groups of directions
-    b += dg_hand_words(z.dg) * 8;            // traces between workgroups
+    b += dg_plane_bytes(z.dg, z.n_cells);    // groups' planes, traces between workgroups
     if (z.dg.table) b += (size_t)z.n_mat * 8;
     if (!fields) b += lds_limit() / 4;       // bound: as many materials as a table holds
   }

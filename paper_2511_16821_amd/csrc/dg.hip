@@ -746,6 +746,14 @@ size_t dg_sweep_lds_bytes(const DgPlan& p, int n_mat, bool refl) {
          sizeof(int) * (size_t)(split ? p.n_waves : p.n_strips);
 }
 
+size_t dg_hand_words(const DgPlan& p) {
+  return (size_t)4 * p.n_grp * (p.n_blk - 1) * p.nu * 4 * p.per;
+}
+
+size_t dg_plane_bytes(const DgPlan& p, long long cells) {
+  return (size_t)4 * p.n_grp * cells * 32 + dg_hand_words(p) * 8;
+}
+
 DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, bool squares, bool refl, size_t lds) {
   DgPlan p;
   // wave-steps of a direction with the lanes along y or along x
@@ -787,16 +795,27 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, bool squares, bool re
               turns(rows) * (60 * n_mat + 50 * walk) <= turns(0) * 75 * walk;
     return dg_sweep_lds_bytes(p, p.table ? (int)n_mat : 0, refl) <= lds;
   };
-  axis(cheap);
-  const bool fits = fill(1);
-  if (!fits || p.nv == 1) return p;  // (a row: the scan of its cells)
+  DgPlan cand[4];
+  int n_cand = 0;
+  auto add = [&](int swap, int per) {
+    axis(swap);
+    if (fill(per)) cand[n_cand++] = p;
+    return n_cand > 0;
+  };
+  if (!add(cheap, 1) || p.nv == 1) return p;  // (a row: the scan of its cells)
+  add(1 - cheap, 1);
+  if (n_dir >= 4 * kDgSplit) {
+    add(cheap, kDgSplit);
+    add(1 - cheap, kDgSplit);
+  }
   // Microseconds of a sweep and its reduction.  The chain of steps: a strip starts
   // 72 steps after the one before, so that at most (nu + 63) / 72 + 1 work at a time.
   // With four directions per wave a step takes 0.5 us, 0.65 with the inverses per
   // cell; with one 0.23, or 0.033 (0.038) times the strips at work, which share a
   // compute unit, and up to 2.1 times that where rows of more than 600 columns
   // leave the caches.  The planes: what stays in the 256 MB last-level cache costs
-  // 0.2 us a MB, what does not 0.3 more, which four directions per wave quarter.
+  // 0.2 us a MB, what does not 0.3 more, which four directions per wave quarter;
+  // one direction per wave, with four times their memory, has to gain 5%.
   // Fitted to 300 measured pairs of mesh and order (40^2 to 2048^2, 3500 x 30 to
   // 3800 x 250, S_2 to S_16, table and cells; other sizes are extrapolated): the
   // choice is at most 10% slower than the best of the four, 0.2% on average.
@@ -804,31 +823,33 @@ DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, bool squares, bool re
   // 0.42, 1.18, 1.06; 3000 x 1000 S_16 13.8, -, -, 5.2 (four's traces do not fit the
   // LDS above some 2400 columns); 1024^2 S_16 5.1, -, 1.83, 1.88; 256^2 S_8 0.13, -,
   // 0.27, 0.27; 512^2 S_8 0.59, -, 0.59, 0.58.
-  auto us = [&]() {
-    const bool four = p.per == kDgSplit;
-    const double strips = p.n_strips - 1, steps = p.nu + 72.0 * strips + p.nv - 64.0 * strips;
-    const double work = std::min(p.n_waves, (p.nu + 63) / 72 + 1);
-    const double far = std::max(0, p.nu - 600) * 1e-3 * std::min(1.0, nc / 0.9e6);
-    const double busy = (0.033 * (1.0 + std::min(1.1, far)) + (p.table ? 0.0 : 0.005)) * work;
-    const double step = four ? (p.table ? 0.5 : 0.65) : std::max(0.23, busy);
-    const double mb = 128e-6 * p.n_grp * (double)nc, past = std::max(0.0, mb - 200.0);
-    return steps * step + (four ? 0.24 : 0.2) * mb + (four ? 0.12 : 0.32) * past;
+  auto us = [&](const DgPlan& c, bool table) {
+    const bool four = c.per == kDgSplit;
+    const double strips = c.n_strips - 1, steps = c.nu + 72.0 * strips + c.nv - 64.0 * strips;
+    const double work = std::min(c.n_waves, (c.nu + 63) / 72 + 1);
+    const double far = std::max(0, c.nu - 600) * 1e-3 * std::min(1.0, nc / 0.9e6);
+    const double busy = (0.033 * (1.0 + std::min(1.1, far)) + (table ? 0.0 : 0.005)) * work;
+    const double step = four ? (table ? 0.5 : 0.65) : std::max(0.23, busy);
+    const double mb = 128e-6 * c.n_grp * (double)nc, past = std::max(0.0, mb - 200.0);
+    const double t = steps * step + (four ? 0.24 : 0.2) * mb + (four ? 0.12 : 0.32) * past;
+    return four ? t : 1.05 * t;
   };
-  DgPlan best = p;
-  double best_us = us();
-  auto consider = [&](int swap, int per) {
-    axis(swap);
-    if (!fill(per) || us() >= best_us) return;
-    best = p;
-    best_us = us();
-  };
-  consider(1 - cheap, 1);
-  if (n_dir >= 4 * kDgSplit) {
-    best_us *= 1.05;  // four directions take a quarter of the planes' memory
-    consider(cheap, kDgSplit);
-    consider(1 - cheap, kDgSplit);
+  int best = 0;
+  if (n_mat >= 0) {
+    for (int k = 1; k < n_cand; ++k)
+      if (us(cand[k], cand[k].table) < us(cand[best], cand[best].table)) best = k;
+    return cand[best];
   }
-  return best;
+  // not known: of those that some materials would choose, the largest
+  double most = us(cand[0], false);
+  for (int k = 1; k < n_cand; ++k) most = std::min(most, us(cand[k], false));
+  size_t bytes = 0;
+  for (int k = 0; k < n_cand; ++k)
+    if (us(cand[k], true) <= most && dg_plane_bytes(cand[k], nc) > bytes) {
+      bytes = dg_plane_bytes(cand[k], nc);
+      best = k;
+    }
+  return cand[best];
 }
 
 hipError_t launch_si_start(const DgArgs& a, int si_max, hipStream_t s) {
@@ -903,10 +924,6 @@ hipError_t launch_dg_sweep(const DgArgs& a, hipStream_t s) {
     else sweep_launch<false, false>(a, lds, s);
   }
   return hipGetLastError();
-}
-
-size_t dg_hand_words(const DgPlan& p) {
-  return (size_t)4 * p.n_grp * (p.n_blk - 1) * p.nu * 4 * p.per;
 }
 
 // The reduction of a source iteration (k_dg_combine): phi_new = the nodal

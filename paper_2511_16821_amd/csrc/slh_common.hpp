@@ -574,11 +574,13 @@ __host__ __device__ __forceinline__ int dg_diag(int nu, int nv, int anti, int u,
   return dg_diag_row(nu, anti, u, v) * nv + v;
 }
 
-// The plan of a mesh with n_mat distinct sigma_e (0: not known) and lds bytes of
-// LDS per workgroup; squares: |z|^2 of the element's modes, z of the size of
+// The plan of a mesh with n_mat distinct sigma_e (negative: not known, a plan that
+// needs as much memory as any of their plans) and lds bytes of LDS per workgroup;
+// squares: |z|^2 of the element's modes, z of the size of
 // 1/hx + 1/hy + sigma_e, neither overflows nor underflows.
 DgPlan dg_plan(int nx, int ny, int n_dir, long long n_mat, bool squares, bool refl, size_t lds);
 size_t dg_hand_words(const DgPlan& p);
+size_t dg_plane_bytes(const DgPlan& p, long long cells);  // planes and hand-over
 size_t dg_sweep_lds_bytes(const DgPlan& p, int n_mat, bool refl);
 // Start of a step's source iteration: phi_c = 0, iteration state reset, the
 // first iterate's nodal source, reflected traces of the first sweep zeroed.

@@ -86,3 +86,39 @@ def test_plans_are_consistent(S, nx, sn):
                 lds += rows * (72 if p.per == 4 else 32)
                 lds += 4 * (p.n_waves if p.per == 4 else p.n_strips)
                 assert lds <= 160 * 1024, (nx, ny, sn, n_mat, refl)
+
+
+def _plane_bytes(p, cells):
+    return 4 * p.n_grp * cells * 32 + 4 * p.n_grp * (p.n_blk - 1) * p.nu * 4 * p.per * 8
+
+
+@pytest.mark.parametrize("sn", [2, 4, 8, 16, 24, 64])
+def test_plan_of_unknown_materials_bounds_all(S, sn):
+    """Without fields the footprint is a bound: the planes of no number of
+    materials need more."""
+    for nx in (4, 33, 65, 100, 144, 274, 316, 512, 667, 1000, 2047, 2251, 3000):
+        for ny in (3, 12, 36, 65, 73, 113, 129, 325, 432, 1000, 2047):
+            if nx + ny > 4096:
+                continue
+            for refl in (False, True):
+                bound = _plane_bytes(sweep_plan(S, nx, ny, sn, -1, refl), nx * ny)
+                for n_mat in (0, 1, 50, 500, 1000, 2000, 4000, 5121):
+                    for squares in (True, False):
+                        p = sweep_plan(S, nx, ny, sn, n_mat, refl, squares)
+                        assert _plane_bytes(p, nx * ny) <= bound, (nx, ny, sn, n_mat, refl, squares)
+
+
+def test_footprint_without_fields_bounds_the_one_with(S):
+    import numpy as np
+    from paper_2511_16821_amd import workloads as W
+    rng = np.random.default_rng(4)
+    for nx, ny, sn in ((20, 20, 8), (65, 300, 16), (300, 65, 8), (120, 130, 24), (1000, 65, 4)):
+        for n_mat in (1, 300, 2000):
+            p = W.homogeneous_box(n=max(nx, ny), n_particles=1000, sn_order=sn)
+            v = rng.uniform(0.1, 2.0, size=n_mat)
+            f = v[rng.integers(0, n_mat, size=(ny, nx))]
+            p.update(nx=nx, ny=ny, sigma_s=f, sigma_a=f, q=f)
+            st, keep = S.make_problem(p)
+            exact = S.lib().slh_footprint_bytes(C.byref(st))
+            st.sigma_s = st.sigma_a = None
+            assert 0 < exact <= S.lib().slh_footprint_bytes(C.byref(st)), (nx, ny, sn, n_mat)
