@@ -47,7 +47,7 @@ def _solve_ms(solver):
 
 def test_material_per_cell_on_long_rows(S):
     """Twelve iterations with a material per cell take little more than with a
-    table of five (by 1.11 measured; 1.74 where the lanes of a wave read sigma_e
+    table of five (by 1.07 measured; 1.7 where the lanes of a wave read sigma_e
     from 64 cache lines at each step)."""
     ms = []
     for n_mat in (5, 0):
